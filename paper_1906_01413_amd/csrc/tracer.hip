@@ -10,10 +10,8 @@
 // adjoint need the base emissions only, never a stored trajectory.
 //
 // Layout: fields [member][y][x] (x fastest); controls [member][time block][by][bx].
-// The sweeps run two steps per launch over (tile, member): a 64 x 16 tile of cells plus a
-// two-cell halo is staged in LDS (every row segment one coalesced run), the intermediate
-// field stays in LDS, and each thread computes four rows of the tile. An odd last step
-// uses the single-step kernels, which stage a one-cell halo.
+// A sweep runs up to eight steps per launch: a wave marches down the rows of a strip of
+// columns with all the group's steps in flight at once, one row apart, in registers.
 
 #include <algorithm>
 #include <cmath>
@@ -25,380 +23,322 @@
 namespace riot {
 namespace {
 
-// cell tile kTX x kTY, threads kTX x kWY; thread (lx, ly) owns rows ly + kWY r, r < kRY
-// (kRY ly + r in the adjoint pair kernel, for its control-block sums)
-constexpr int kTX = 64, kWY = 4, kRY = 4, kTY = kWY * kRY;
-constexpr int kThreads = kTX * kWY;
-constexpr int kHX = kTX + 2, kHY = kTY + 2;
-
 struct TracerView {
   int N, T, block, bshift, ntb, Nb, spb;  // block = 1 << bshift; spb: steps per time block
   double dt, aS, aE, aN;
   const double *a0, *aW;          // [N] row coefficients
 };
 
+// ---------------------------------------------------------------------------
+// Marching sweeps. A wave owns `width` columns (two adjacent cells per lane, 128 with a halo
+// of kHalo cells on each side) and the rows [ys, ye) of one member's field, and advances the
+// field S <= kMaxS steps in one pass over its rows: at iteration i it takes row r = ys - S + i
+// of the input (level 0), and level s finishes row r - s of the field after s steps. The
+// five-point stencil is applied in scatter form, so a level keeps one row of partial sums
+// (everything but the next row's term) and one row of its input, and the chain through the
+// levels of an iteration is one multiply-add per level. East and west neighbours come from
+// the adjacent lanes by DPP moves; lanes at the strip's ends go wrong by one cell per level,
+// which the halo absorbs, and so do the rows beyond [ys, ye) at the ends of the march.
+// No LDS and no barrier: nothing is exchanged between waves.
+//
+// All steps of a launch lie in one time block, so the emission term of a cell is the same at
+// every level: it is formed once per row and kept for the S - 1 rows until the last level
+// has used it. Likewise the adjoint adds the levels' lam of a cell first and multiplies by
+// dt W once.
+//
+// Bound: the fields' traffic, one read and one write per S steps (0.44 ms per launch at a
+// copy's 4.9 TB/s for 512 members on 512 x 512 cells), and vector issue, about 300
+// instructions per row of 8 levels at two waves per SIMD. Measured there, 96 steps: 0.60 ms
+// (forward) and 0.70 ms (adjoint) per 8 steps, the Hessian product of 512 probes 62.4 ms (two
+// steps per launch through LDS tiles, 3.1 TB/s) -> 17.5 ms; S = 6: 19.5 ms, S = 4: 27.2 ms.
+// Held to three waves per SIMD the registers spill (71 ms). One member, where a launch lasts
+// as long as one march: value and gradient 810 -> 520 us.
+// ---------------------------------------------------------------------------
+constexpr int kMaxS = 8;    // steps per launch; the register rings below have kMaxS rows
+constexpr int kHalo = 8;    // >= kMaxS, a multiple of 4 (the largest control block side)
+constexpr int kCells = 128; // cells per wave row
+constexpr int kAhead = 4;   // rows loaded ahead; divides kMaxS
+constexpr int kAheadG = 2;  // the same for what stays in L2: cell lists; adjoint: weights, old gS
+constexpr int kLevShift = 27;  // level 8 stays positive
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+struct MarchArgs {
+  int ns, width;              // strips across x, columns per strip (a multiple of 4)
+  int nch, rows;              // chunks down y, rows per chunk (a multiple of 4)
+  int m;                      // members
+  const double *in;           // input fields, or null: zero
+  double *out;                // fields after S steps, or null: not needed
+  const double *W;            // [N*N] emission weights of the time block
+  const double *bv;           // forward: [mem][Nb*Nb] control values of the time block
+  long long bv_stride;
+  double *gS;                 // adjoint: [mem][Nb*Nb] control gradient of the time block
+  long long gS_stride;
+  int gS_add;                 // 0: gS is written, 1: added to
+  // cells sampled (forward: observations) or forced (adjoint: unique cells) in this group, in
+  // the order of the march: entries [ptr[r], ptr[r + 1]) lie in rows (r - lev) mod N, which
+  // level lev finishes when row r is taken in; ent holds x + (lev << kLevShift)
+  const int *ptr, *ent;
+  const int *orig;            // forward: caller's index of each entry
+  int nobs;
+  double *obs;                // forward: [mem][nobs] out, or null
+  const double *fu;           // adjoint: [mem][nuniq] forcing of each entry's cell
+  int nuniq;
+};
+
+// value of the lane one below (shr) or above (shl); the end lane gets zero
+template <int CTRL>
+__device__ __forceinline__ double dpp_shift(double v) {
+  union { double d; int i[2]; } a, b;
+  a.d = v;
+  b.i[0] = __builtin_amdgcn_update_dpp(0, a.i[0], CTRL, 0xf, 0xf, true);
+  b.i[1] = __builtin_amdgcn_update_dpp(0, a.i[1], CTRL, 0xf, 0xf, true);
+  return b.d;
+}
+__device__ __forceinline__ double from_below(double v) { return dpp_shift<0x138>(v); }  // wave_shr:1
+__device__ __forceinline__ double from_above(double v) { return dpp_shift<0x130>(v); }  // wave_shl:1
+
+// element of a row (wave-uniform address) at a lane's byte offset
+template <typename T>
+__device__ __forceinline__ gmem<T> *row_at(double *row, unsigned off) {
+  return (gmem<T> *)((gmem<char> *)row + off);
+}
+template <typename T>
+__device__ __forceinline__ const gmem<T> *row_at(const double *row, unsigned off) {
+  return (const gmem<T> *)((const gmem<char> *)row + off);
+}
+
+// LDS written by other lanes of this wave may be read after it (a wave's LDS accesses stay in
+// order; this keeps the compiler from reordering or forwarding them)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ d2 own_copy(d2 v) {
+  d2 r;
+  asm("v_mov_b64 %0, %1" : "=v"(r.x) : "v"(v.x));
+  asm("v_mov_b64 %0, %1" : "=v"(r.y) : "v"(v.y));
+  return r;
+}
+
 __device__ __forceinline__ int wrap(int i, int N) { return i < 0 ? i + N : (i >= N ? i - N : i); }
 
-// Tile of this workgroup. Workgroups are dealt round-robin to the 8 XCDs, each with its own
-// L2; in dispatch order an XCD would get the tiles of one x column only, so its tiles'
-// x-halo lines would never be in its L2. With the remap (when the tile rows split into 8
-// bands) XCD j takes band j of tile rows for every member, x fastest: x neighbours share
-// their halo lines in one L2, and its band of the emission fields stays resident there.
-struct TileId {
-  int x0, y0, mem;
-};
-__device__ __forceinline__ TileId tile_id() {
-  const int gx = gridDim.x, gy = gridDim.y;
-  int id = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-  int bx, by, mem;
-  if ((gy & 7) == 0) {
-    const int band = gy >> 3, xcd = id & 7;
-    int q = id >> 3;  // rank of this workgroup among its XCD's
-    bx = q % gx;
-    q /= gx;
-    by = xcd * band + q % band;
-    mem = q / band;
+template <bool ADJ, int S>
+__global__ void __launch_bounds__(64, S > 4 ? 2 : 3)
+    tracer_march_kernel(TracerView tv, MarchArgs a, const double *__restrict__ ca0,
+                        const double *__restrict__ caW, const int *__restrict__ ptr) {
+  constexpr int R = S <= 4 ? 4 : kMaxS;  // rows of the rings below, unrolled iterations
+  static_assert(S >= 1 && S <= kMaxS && kHalo >= kMaxS && R % kAhead == 0, "");
+  __shared__ double rows[S][kCells];  // levels' rows sampled, or their forcing, at one iteration
+  const int N = tv.N, lane = threadIdx.x;
+  // Workgroups are dealt round-robin to the 8 XCDs: the strips of one chunk go to one XCD,
+  // one after the other, so that their overlapping columns are read into one L2.
+  const int units = a.m * a.nch;
+  int unit, strip;
+  if ((units & 7) == 0) {
+    const int q = blockIdx.x >> 3;
+    strip = q % a.ns;
+    unit = (q / a.ns) * 8 + (blockIdx.x & 7);
   } else {
-    bx = id % gx;
-    id /= gx;
-    by = id % gy;
-    mem = id / gy;
+    strip = blockIdx.x % a.ns;
+    unit = blockIdx.x / a.ns;
   }
-  return {bx * kTX, by * kTY, mem};
-}
-
-// Stage the tile of `f` with its halo in LDS (row-major, kHY x kHX).
-__device__ __forceinline__ void stage_tile(const double *__restrict__ f, int N, int x0, int y0,
-                                           double *t) {
-  for (int k = threadIdx.x; k < kHX * kHY; k += kThreads) {
-    const int ty = k / kHX, tx = k - ty * kHX;
-    t[k] = f[(size_t)wrap(y0 + ty - 1, N) * N + wrap(x0 + tx - 1, N)];
-  }
-}
-
-// out = A in + dt W * up(bv): one step of the forward model (W = E, bv = exp(s_tau)) or of
-// the tangent-linear model (W = E exp(up(s_b,tau)), bv = ds_tau). in may be nullptr (zero).
-__global__ void __launch_bounds__(kThreads)
-    tracer_step_kernel(TracerView tv, const double *__restrict__ in, double *__restrict__ out,
-                       const double *__restrict__ W, const double *__restrict__ bv,
-                       long long bv_stride) {
-  __shared__ double t[kHX * kHY];
-  const int N = tv.N;
+  const int mem = unit / a.nch, ch = unit - mem * a.nch;
+  const int xs = strip * a.width, xe = min(xs + a.width, N);
+  const int ys = ch * a.rows, ye = min(ys + a.rows, N);
+  if (xs >= N || ys >= N) return;
+  int x = xs - kHalo + 2 * lane;  // this lane's first cell, wrapped (N >= 64)
+  const bool own = x >= xs && x < xe;
+  x = x < 0 ? x + N : x;
+  while (x >= N) x -= N;
   const size_t NN = (size_t)N * N;
-  const TileId ti = tile_id();
-  const int x0 = ti.x0, y0 = ti.y0, mem = ti.mem;
-  const int lx = threadIdx.x % kTX, ly = threadIdx.x / kTX;
-  const int x = x0 + lx;
-  if (in) {
-    stage_tile(in + mem * NN, N, x0, y0, t);
-    __syncthreads();
-  }
-  const double *bvm = bv + mem * bv_stride;
-#pragma unroll
-  for (int r = 0; r < kRY; ++r) {
-    const int yl = ly + kWY * r, y = y0 + yl;
-    double acc = 0.0;
-    if (in) {
-      const int c = (yl + 1) * kHX + lx + 1;
-      acc = tv.a0[y] * t[c] + tv.aW[y] * t[c - 1] + tv.aS * t[c - kHX] + tv.aE * t[c + 1] +
-            tv.aN * t[c + kHX];
-    }
-    const double e = bvm[(size_t)(y >> tv.bshift) * tv.Nb + (x >> tv.bshift)];
-    out[mem * NN + (size_t)y * N + x] = acc + tv.dt * W[(size_t)y * N + x] * e;
-  }
-}
-
-// lam_out = A^T lam_in, and gS_tau += down(dt W * lam_in) per block x block cells
-// (each control block of the tile summed row by row by one thread: fixed order).
-__global__ void __launch_bounds__(kThreads)
-    tracer_adjoint_kernel(TracerView tv, const double *__restrict__ lam_in,
-                          double *__restrict__ lam_out, const double *__restrict__ W,
-                          double *__restrict__ gS, long long gS_stride) {
-  __shared__ double t[kHX * kHY];
-  __shared__ double w[kTY][kTX];
-  const int N = tv.N;
-  const size_t NN = (size_t)N * N;
-  const TileId ti = tile_id();
-  const int x0 = ti.x0, y0 = ti.y0, mem = ti.mem;
-  const int lx = threadIdx.x % kTX, ly = threadIdx.x / kTX;
-  const int x = x0 + lx;
-  stage_tile(lam_in + mem * NN, N, x0, y0, t);
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kRY; ++r) {
-    const int yl = ly + kWY * r, y = y0 + yl;
-    const int c = (yl + 1) * kHX + lx + 1;
-    if (lam_out)
-      lam_out[mem * NN + (size_t)y * N + x] = tv.a0[y] * t[c] + tv.aW[y] * t[c + 1] +
-                                              tv.aS * t[c + kHX] + tv.aE * t[c - 1] +
-                                              tv.aN * t[c - kHX];
-    w[yl][lx] = tv.dt * W[(size_t)y * N + x] * t[c];
-  }
-  __syncthreads();
-  const int b = tv.block;
-  const int nbx = kTX / b, nby = kTY / b;
-  for (int cb = threadIdx.x; cb < nbx * nby; cb += kThreads) {
-    const int bxl = cb % nbx, byl = cb / nbx;
-    double s = 0.0;
-    for (int r = 0; r < b; ++r)
-      for (int q = 0; q < b; ++q) s += w[byl * b + r][bxl * b + q];
-    double *g = gS + mem * gS_stride + (size_t)((y0 / b) + byl) * tv.Nb + (x0 / b) + bxl;
-    *g += s;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Two steps per launch (temporal blocking): the input tile is staged with a two-cell halo,
-// the intermediate field is computed on the tile plus a one-cell ring and kept in LDS,
-// and only the second step's field goes back to memory, so each field is read and
-// written once per two steps. Observations of the intermediate state are taken (forward)
-// or injected (adjoint) inside the launch.
-// ---------------------------------------------------------------------------
-constexpr int kGX = kTX + 4, kGY = kTY + 4;  // input tile with a two-cell halo
-
-// out = A (A in + dt W0 up(bv0)) + dt W1 up(bv1) (steps t and t + 1; in may be nullptr);
-// obs[mem nobs + orig[o]] = intermediate field at cell[o] for o in [beg, end).
-// Every global load (the input tile, both steps' emission terms, the observation list) is
-// issued before the first barrier, so a workgroup waits for memory once; the ring rows'
-// coefficients a0, aW go to LDS.
-constexpr int kStage2 = (kGX * kGY + kThreads - 1) / kThreads;
-constexpr int kRing = (kHX * kHY + kThreads - 1) / kThreads;
-
-template <bool IN>
-__global__ void __launch_bounds__(kThreads)
-    tracer_step2_kernel(TracerView tv, const double *__restrict__ in, double *__restrict__ out,
-                        const double *__restrict__ W0, const double *__restrict__ bv0,
-                        const double *__restrict__ W1, const double *__restrict__ bv1,
-                        long long bv_stride, int beg, int end, const int *__restrict__ cell,
-                        const int *__restrict__ orig, int nobs, double *__restrict__ obs) {
-  __shared__ double t0[kGX * kGY];
-  __shared__ double t1[kHX * kHY];
-  __shared__ double ca0[kHY], caW[kHY];
-  const int N = tv.N, sh = tv.bshift, tid = threadIdx.x;
-  const size_t NN = (size_t)N * N;
-  const TileId ti = tile_id();
-  const int x0 = ti.x0, y0 = ti.y0, mem = ti.mem;
-  const int lx = tid % kTX, ly = tid / kTX;
-  const int x = x0 + lx;
-  const double *b0m = bv0 + mem * bv_stride, *b1m = bv1 + mem * bv_stride;
-  // Loads past the end of a strip are clamped to its last element and their values
-  // dropped, so that every load is unconditional straight-line code and all of them are
-  // in flight together.
-  double sv[kStage2];
-  if constexpr (IN) {
-    const double *src = in + mem * NN;
-#pragma unroll
-    for (int i = 0; i < kStage2; ++i) {
-      const int k = min(tid + i * kThreads, kGX * kGY - 1);
-      const int ty = k / kGX, tx = k - ty * kGX;
-      sv[i] = src[(size_t)wrap(y0 + ty - 2, N) * N + wrap(x0 + tx - 2, N)];
-    }
-  }
-  double e0[kRing];  // emission term of the first step on the ring cells
-#pragma unroll
-  for (int i = 0; i < kRing; ++i) {
-    const int k = min(tid + i * kThreads, kHX * kHY - 1);
-    const int ry = k / kHX, rx = k - ry * kHX;
-    const int y = wrap(y0 + ry - 1, N), xr = wrap(x0 + rx - 1, N);
-    e0[i] = tv.dt * W0[(size_t)y * N + xr] * b0m[(size_t)(y >> sh) * tv.Nb + (xr >> sh)];
-  }
-  double e1[kRY];  // emission term of the second step on this thread's cells
-#pragma unroll
-  for (int r = 0; r < kRY; ++r) {
-    const int y = y0 + ly + kWY * r;
-    e1[r] = tv.dt * W1[(size_t)y * N + x] * b1m[(size_t)(y >> sh) * tv.Nb + (x >> sh)];
-  }
-  // observations of the intermediate state: one per thread prefetched (more loop below);
-  // index 0 stands in where there is none (the tables hold at least one entry)
-  const int o = beg + tid;
-  const bool has_o = obs != nullptr && o < end;
-  const int oc = cell[has_o ? o : 0], oo = orig[has_o ? o : 0];
-  const int yr = wrap(y0 + min(tid, kHY - 1) - 1, N);
-  const double a0r = tv.a0[yr], aWr = tv.aW[yr];
-  if (tid < kHY) {
-    ca0[tid] = a0r;
-    caW[tid] = aWr;
-  }
-  if constexpr (IN) {
-#pragma unroll
-    for (int i = 0; i < kStage2; ++i) {
-      const int k = tid + i * kThreads;
-      if (k < kGX * kGY) t0[k] = sv[i];
-    }
-  }
-  __syncthreads();
-  // intermediate field on the tile and a one-cell ring (kHY x kHX, wrapped coordinates)
-#pragma unroll
-  for (int i = 0; i < kRing; ++i) {
-    const int k = tid + i * kThreads;
-    if (k < kHX * kHY) {
-      const int ry = k / kHX, rx = k - ry * kHX;
-      double acc = 0.0;
-      if constexpr (IN) {
-        const int c = (ry + 1) * kGX + rx + 1;
-        acc = ca0[ry] * t0[c] + caW[ry] * t0[c - 1] + tv.aS * t0[c - kGX] + tv.aE * t0[c + 1] +
-              tv.aN * t0[c + kGX];
-      }
-      t1[k] = acc + e0[i];
-    }
-  }
-  __syncthreads();
-  if (has_o) {
-    const int cy = oc / N, cx = oc - cy * N;
-    if (cy >= y0 && cy < y0 + kTY && cx >= x0 && cx < x0 + kTX)
-      obs[(size_t)mem * nobs + oo] = t1[(cy - y0 + 1) * kHX + cx - x0 + 1];
-  }
-  if (obs) {
-    for (int o2 = o + kThreads; o2 < end; o2 += kThreads) {
-      const int cy = cell[o2] / N, cx = cell[o2] - cy * N;
-      if (cy >= y0 && cy < y0 + kTY && cx >= x0 && cx < x0 + kTX)
-        obs[(size_t)mem * nobs + orig[o2]] = t1[(cy - y0 + 1) * kHX + cx - x0 + 1];
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < kRY; ++r) {
-    const int yl = ly + kWY * r, y = y0 + yl;
-    const int c = (yl + 1) * kHX + lx + 1;
-    const double acc = ca0[yl + 1] * t1[c] + caW[yl + 1] * t1[c - 1] + tv.aS * t1[c - kHX] +
-                       tv.aE * t1[c + 1] + tv.aN * t1[c + kHX];
-    out[mem * NN + (size_t)y * N + x] = acc + e1[r];
-  }
-}
-
-// Adjoint of two steps (states t -> t-1 -> t-2): lam1 = A^T lam_in on the tile and a ring,
-// gS1 += down(dt W1 lam_in) (step t-1's emissions), the observation forcing of state t-1
-// added to lam1 (unique cells u in [ubeg, uend)), lam_out = A^T lam1 (may be nullptr),
-// gS0 += down(dt W0 lam1) (step t-2's emissions). gS1 and gS0 are the same block when both
-// steps use one control time block, so they may alias.
-//
-// Here thread (lx, ly) owns the kRY consecutive rows kRY ly + r, so a control block
-// (side 1, 2 or 4) has all its rows in one thread: its rows are summed in registers and its
-// columns across b adjacent lanes of the wave by shuffles (a fixed tree, so the sums are
-// deterministic), with no LDS for the block sums.
-__device__ __forceinline__ void block_sums_add(double v[kRY], int b, int lx, double *g,
-                                               int Nb) {
-  // g points at the control of this thread's first row and column, (y / b, x / b)
-  if (b == 1) {
-#pragma unroll
-    for (int r = 0; r < kRY; ++r) g[(size_t)r * Nb] += v[r];
-  } else if (b == 2) {
-    double s0 = v[0] + v[1], s1 = v[2] + v[3];
-    s0 += __shfl_xor(s0, 1);
-    s1 += __shfl_xor(s1, 1);
-    if ((lx & 1) == 0) {
-      g[0] += s0;
-      g[Nb] += s1;
-    }
-  } else {
-    double s = (v[0] + v[1]) + (v[2] + v[3]);
-    s += __shfl_xor(s, 1);
-    s += __shfl_xor(s, 2);
-    if ((lx & 3) == 0) g[0] += s;
-  }
-}
-
-__global__ void __launch_bounds__(kThreads)
-    tracer_adjoint2_kernel(TracerView tv, const double *__restrict__ lam_in,
-                           double *__restrict__ lam_out, const double *__restrict__ W1,
-                           const double *__restrict__ W0, double *gS1, double *gS0,
-                           long long gS_stride, int ubeg, int uend,
-                           const int *__restrict__ ucell, const double *__restrict__ fu,
-                           int nuniq) {
-  __shared__ double t0[kGX * kGY];
-  __shared__ double t1[kHX * kHY];
-  __shared__ double ca0[kHY], caW[kHY];
-  const int N = tv.N, tid = threadIdx.x;
-  const size_t NN = (size_t)N * N;
-  const TileId ti = tile_id();
-  const int x0 = ti.x0, y0 = ti.y0, mem = ti.mem;
-  const int lx = tid % kTX, ly = tid / kTX;
-  const int x = x0 + lx, yb = y0 + kRY * ly;  // this thread's first row
-  // every global load first: the input tile, both steps' emission fields on this thread's
-  // cells, one forcing entry of state t-1 (more in the loop below)
-  // (loads clamped to valid elements and unconditional, as in the forward pair)
-  double sv[kStage2];
-  {
-    const double *src = lam_in + mem * NN;
-#pragma unroll
-    for (int i = 0; i < kStage2; ++i) {
-      const int k = min(tid + i * kThreads, kGX * kGY - 1);
-      const int ty = k / kGX, tx = k - ty * kGX;
-      sv[i] = src[(size_t)wrap(y0 + ty - 2, N) * N + wrap(x0 + tx - 2, N)];
-    }
-  }
-  double w1[kRY], w0[kRY];
-#pragma unroll
-  for (int r = 0; r < kRY; ++r) {
-    w1[r] = W1[(size_t)(yb + r) * N + x];
-    w0[r] = W0[(size_t)(yb + r) * N + x];
-  }
-  const int u = ubeg + tid;
-  const bool has_u = u < uend;
-  const int uc = ucell[has_u ? u : 0];
-  const double uf = fu[(size_t)mem * nuniq + (has_u ? u : 0)];
-  const int yr = wrap(y0 + min(tid, kHY - 1) - 1, N);
-  const double a0r = tv.a0[yr], aWr = tv.aW[yr];
-  if (tid < kHY) {
-    ca0[tid] = a0r;
-    caW[tid] = aWr;
-  }
-#pragma unroll
-  for (int i = 0; i < kStage2; ++i) {
-    const int k = tid + i * kThreads;
-    if (k < kGX * kGY) t0[k] = sv[i];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kRing; ++i) {
-    const int k = tid + i * kThreads;
-    if (k < kHX * kHY) {
-      const int ry = k / kHX, rx = k - ry * kHX;
-      const int c = (ry + 1) * kGX + rx + 1;
-      t1[k] = ca0[ry] * t0[c] + caW[ry] * t0[c + 1] + tv.aS * t0[c + kGX] + tv.aE * t0[c - 1] +
-              tv.aN * t0[c - kGX];
-    }
-  }
-  double v[kRY];
-#pragma unroll
-  for (int r = 0; r < kRY; ++r)
-    v[r] = tv.dt * w1[r] * t0[(kRY * ly + r + 2) * kGX + lx + 2];
-  __syncthreads();
-  // forcing of state t-1 on the ring; a cell may sit at two ring positions when the ring
-  // spans the whole period (N = kTX): the forcing goes to every copy
-  auto add_forcing = [&](int cellu, double val) {
-    const int cy = cellu / N, cx = cellu - cy * N;
-    const int ry0 = wrap(cy - (y0 - 1), N), rx0 = wrap(cx - (x0 - 1), N);
-    for (int ry = ry0; ry < kHY; ry += N)
-      for (int rx = rx0; rx < kHX; rx += N) t1[ry * kHX + rx] += val;
-  };
-  if (has_u) add_forcing(uc, uf);
-  for (int u2 = u + kThreads; u2 < uend; u2 += kThreads)
-    add_forcing(ucell[u2], fu[(size_t)mem * nuniq + u2]);
+  const bool has_in = a.in != nullptr;  // else any field is loaded and its values dropped
+  const double *src = has_in ? a.in + mem * NN : a.W;
   const int sh = tv.bshift;
-  const size_t goff = (size_t)mem * gS_stride + (size_t)(yb >> sh) * tv.Nb + (x >> sh);
-  block_sums_add(v, tv.block, lx, gS1 + goff, tv.Nb);
-  __syncthreads();
-#pragma unroll
-  for (int r = 0; r < kRY; ++r) {
-    const int y = yb + r, rr = kRY * ly + r + 1;  // ring row of this cell
-    const int c = rr * kHX + lx + 1;
-    if (lam_out)
-      lam_out[mem * NN + (size_t)y * N + x] = ca0[rr] * t1[c] + caW[rr] * t1[c + 1] +
-                                              tv.aS * t1[c + kHX] + tv.aE * t1[c - 1] +
-                                              tv.aN * t1[c - kHX];
-    v[r] = tv.dt * w0[r] * t1[c];
-  }
-  block_sums_add(v, tv.block, lx, gS0 + goff, tv.Nb);
-}
+  const unsigned xo8 = 8u * x, xb8 = 8u * (x >> sh),
+                 xc8 = 8u * ((x + 1) >> sh);  // byte offsets of this lane in a row
+  const double *bvm = ADJ ? nullptr : a.bv + mem * a.bv_stride;
+  double *gSm = ADJ ? a.gS + mem * a.gS_stride : nullptr;
+  const int iters = ye - ys + 2 * S;
 
-// Observation samples after a step: out[orig[o] + mem nobs] = f[y_o, x_o] for the step's o.
-__global__ void tracer_sample_kernel(int N, int beg, int end, const int *__restrict__ cell,
-                                     const int *__restrict__ orig, const double *__restrict__ f,
-                                     int nobs, double *__restrict__ out) {
-  const int o = beg + blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= end) return;
-  const int mem = blockIdx.y;
-  out[(size_t)mem * nobs + orig[o]] = f[(size_t)mem * N * N + cell[o]];
+  d2 q[S], cold[S], ring[R];  // ring: emission terms (forward) or sums of lam (adjoint)
+#pragma unroll
+  for (int s = 0; s < S; ++s) q[s] = cold[s] = d2{0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < R; ++s) ring[s] = d2{0.0, 0.0};
+  double r0[R], rW[R];  // a0 and aW of the last R rows
+#pragma unroll
+  for (int s = 0; s < R; ++s) r0[s] = rW[s] = 0.0;
+
+  // rows in flight: input field and (forward: emission weights and controls of the same row;
+  // adjoint: weights of the row whose sums complete at that iteration)
+  constexpr int kAW = ADJ ? kAheadG : kAhead;
+  d2 fb[kAhead], wb[kAW], eb[kAW];  // eb: controls (forward), old gS of that row (adjoint)
+  int rl = wrap(ys - S, N), rw = ADJ ? wrap(wrap(ys - S - (S - 1), N), N) : rl;  // next rows to load
+  auto issue_f = [&](int k) {
+    fb[k] = *row_at<d2>(src + (size_t)rl * N, xo8);
+    rl = rl + 1 == N ? 0 : rl + 1;
+  };
+  auto issue_w = [&](int k) {
+    wb[k] = *row_at<d2>(a.W + (size_t)rw * N, xo8);
+    const double *bp = (ADJ ? gSm : bvm) + (size_t)(rw >> sh) * tv.Nb;
+    eb[k].x = *row_at<double>(bp, xb8);
+    eb[k].y = *row_at<double>(bp, xc8);
+    rw = rw + 1 == N ? 0 : rw + 1;
+  };
+  int rc = wrap(ys - S, N);            // row taken in by this iteration
+  // cell list of the rows in flight, one entry per lane (beyond 64: loaded when needed); the
+  // row pointers are read one row ahead of the entries
+  int eb0[kAheadG], eb1[kAheadG], ee[kAheadG], eo[kAheadG];
+  double ef[kAheadG];
+  int rp = rc, np0 = ptr[rp], np1 = ptr[rp + 1];
+  const double *fum = ADJ ? a.fu + (size_t)mem * a.nuniq : nullptr;
+  auto issue_e = [&](int k) {
+    eb0[k] = np0;
+    eb1[k] = np1;
+    const int e = min(np0 + lane, max(np1 - 1, 0));  // (the lists hold at least one element)
+    ee[k] = a.ent[e];
+    if constexpr (ADJ) ef[k] = fum[e];
+    else eo[k] = a.orig[e];
+    rp = rp + 1 == N ? 0 : rp + 1;
+    np0 = ptr[rp];
+    np1 = ptr[rp + 1];
+  };
+#pragma unroll
+  for (int k = 0; k < kAhead; ++k) {
+    issue_f(k);
+    if (k < kAW) issue_w(k);
+    if (k < kAheadG) issue_e(k);
+  }
+  double na0 = ca0[rc], naW = caW[rc];
+  d2 bsum = {0.0, 0.0};
+
+  for (int i0 = 0; i0 < iters; i0 += R) {
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      const int i = i0 + u;
+      // (a copy, so that the next load into this slot needs no copy at the end of the loop,
+      // which would wait for it)
+      d2 cin = own_copy(fb[u % kAhead]);
+      if (!has_in) cin = d2{0.0, 0.0};
+      const d2 wrow = wb[u % kAW];
+      const d2 ev = eb[u % kAW];
+      issue_f(u % kAhead);
+      if constexpr (!ADJ) issue_w(u % kAW);
+      r0[u] = na0;
+      rW[u] = naW;
+      const int beg = eb0[u % kAheadG], end = eb1[u % kAheadG];
+      const int en = ee[u % kAheadG], eno = ADJ ? 0 : eo[u % kAheadG];
+      const double enf = ADJ ? ef[u % kAheadG] : 0.0;
+      issue_e(u % kAheadG);
+      const int rn = rc + 1 == N ? 0 : rc + 1;
+      na0 = ca0[rn];
+      naW = caW[rn];
+      // does the strip hold any of this iteration's cells?
+      auto column = [&](int e) { return e & ((1 << kLevShift) - 1); };
+      bool some = false;
+      if (end > beg) {
+        const int xe0 = column(en);
+        const bool in = ADJ ? wrap(xe0 - (xs - kHalo), N) < kCells : xe0 >= xs && xe0 < xe;
+        some = __any(in && beg + lane < end) || end - beg > 64;
+      }
+      if constexpr (!ADJ) {
+        ring[u] = d2{tv.dt * wrow.x * ev.x, tv.dt * wrow.y * ev.y};
+      } else if (some) {
+        // forcing of the levels' rows, scattered in LDS (a cell may sit at several places of
+        // the strip when the strip is wider than the period)
+#pragma unroll
+        for (int s = 0; s < S; ++s) rows[s][2 * lane] = rows[s][2 * lane + 1] = 0.0;
+        wave_lds_fence();
+        auto scatter = [&](int e, double f) {
+          for (int pos = wrap(column(e) - (xs - kHalo), N); pos < kCells; pos += N)
+            rows[e >> kLevShift][pos] = f;
+        };
+        if (beg + lane < end) scatter(en, enf);
+        for (int k = beg + 64 + lane; k < end; k += 64) scatter(a.ent[k], fum[k]);
+        wave_lds_fence();
+        cin += d2{rows[0][2 * lane], rows[0][2 * lane + 1]};
+      }
+#pragma unroll
+      for (int s = 1; s <= S; ++s) {
+        const int d = (u - (s - 1)) & (R - 1);  // ring slot of the row this level takes in
+        const double xm = from_below(cin.y), xp = from_above(cin.x);
+        const double cm = ADJ ? tv.aE : rW[d], cp = ADJ ? rW[d] : tv.aE;
+        const double cym = ADJ ? tv.aN : tv.aS, cyp = ADJ ? tv.aS : tv.aN;
+        d2 o;
+        o.x = fma(cyp, cin.x, q[s - 1].x);
+        o.y = fma(cyp, cin.y, q[s - 1].y);
+        d2 t;
+        t.x = fma(cm, xm, r0[d] * cin.x);
+        t.y = fma(cm, cin.x, r0[d] * cin.y);
+        t.x = fma(cym, cold[s - 1].x, t.x);
+        t.y = fma(cym, cold[s - 1].y, t.y);
+        t.x = fma(cp, cin.y, t.x);
+        t.y = fma(cp, xp, t.y);
+        if constexpr (ADJ) {
+          ring[d] = s == 1 ? cin : d2{ring[d].x + cin.x, ring[d].y + cin.y};
+        } else {
+          t.x += ring[d].x;
+          t.y += ring[d].y;
+        }
+        q[s - 1] = t;
+        cold[s - 1] = cin;
+        cin = o;
+        if constexpr (ADJ) {
+          const int k = s < S ? s : 0;
+          if (s < S && some) cin += d2{rows[k][2 * lane], rows[k][2 * lane + 1]};
+        }
+      }
+      if constexpr (!ADJ) {
+        if (some) {
+#pragma unroll
+          for (int s = 1; s <= S; ++s) {
+            const d2 v = s < S ? cold[s < S ? s : 0] : cin;  // level s + 1 took it in
+            rows[s - 1][2 * lane] = v.x;
+            rows[s - 1][2 * lane + 1] = v.y;
+          }
+          wave_lds_fence();
+          auto sample = [&](int e, int o) {
+            const int lv = e >> kLevShift, xo = column(e), yu = ys - S + i - lv;
+            if (yu >= ys && yu < ye && xo >= xs && xo < xe && a.obs)
+              a.obs[(size_t)mem * a.nobs + o] = rows[lv - 1][xo - xs + kHalo];
+          };
+          if (beg + lane < end) sample(en, eno);
+          for (int k = beg + 64 + lane; k < end; k += 64) sample(a.ent[k], a.orig[k]);
+          wave_lds_fence();
+        }
+      }
+      const int yo = ys - 2 * S + i;  // row of the last level
+      if (a.out && yo >= ys && yo < ye && own)
+        *row_at<d2>(a.out + mem * NN + (size_t)yo * N, xo8) = cin;
+      if constexpr (ADJ) {
+        const int yg = yo + 1;  // row whose sums of lam are complete
+        issue_w(u % kAW);
+        if (yg >= ys && yg < ye) {
+          const d2 sl = ring[(u - (S - 1)) & (R - 1)];
+          const d2 w = {tv.dt * wrow.x * sl.x, tv.dt * wrow.y * sl.y};
+          const int bm = (1 << sh) - 1;
+          bsum = (yg & bm) == 0 ? w : bsum + w;
+          if ((yg & bm) == bm) {  // last row of its control blocks
+            const d2 old = a.gS_add ? ev : d2{0.0, 0.0};
+            gmem<double> *g = row_at<double>(gSm + (size_t)(yg >> sh) * tv.Nb, xb8);
+            if (sh == 0) {
+              if (own) {
+                g[0] = old.x + bsum.x;
+                g[1] = old.y + bsum.y;
+              }
+            } else {
+              double t = bsum.x + bsum.y;
+              if (sh == 2) t += dpp_shift<0xB1>(t);  // the other lane of the pair
+              if (own && (sh < 2 || (lane & 1) == 0)) g[0] = old.x + t;
+            }
+          }
+        }
+      }
+      rc = rn;
+    }
+  }
 }
 
 // Observation forcing gathered per unique cell: fu[mem nuniq + u] = sum of f over the
@@ -412,16 +352,6 @@ __global__ void tracer_gather_kernel(int nuniq, const int *__restrict__ uptr,
   double s = 0.0;
   for (int k = uptr[u]; k < uptr[u + 1]; ++k) s += f[(size_t)mem * nobs + orig[k]];
   fu[(size_t)mem * nuniq + u] = s;
-}
-
-// Observation forcing of one step: lam[cell_u] += fu[u] for the step's unique cells.
-__global__ void tracer_inject_kernel(int N, int beg, int end, const int *__restrict__ ucell,
-                                     const double *__restrict__ fu, int nuniq,
-                                     double *__restrict__ lam) {
-  const int u = beg + blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= end) return;
-  const int mem = blockIdx.y;
-  lam[(size_t)mem * N * N + ucell[u]] += fu[(size_t)mem * nuniq + u];
 }
 
 // Elementwise helpers.
@@ -440,11 +370,6 @@ __global__ void base_emission_kernel(TracerView tv, const double *__restrict__ E
   const size_t c = i - (size_t)tau * NN;
   const int y = (int)(c / tv.N), x = (int)(c - (size_t)y * tv.N);
   W[i] = E[c] * exp(sb[(size_t)tau * tv.Nb * tv.Nb + (size_t)(y >> tv.bshift) * tv.Nb + (x >> tv.bshift)]);
-}
-
-__global__ void zero_kernel(long long n, double *__restrict__ a) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) a[i] = 0.0;
 }
 
 // d = y - hx; f = rinv d (observation space, one column)
@@ -505,14 +430,15 @@ struct riot_tracer {
   double *a0 = nullptr, *aW = nullptr, *E = nullptr, *Wb = nullptr, *sb = nullptr,
          *expS = nullptr;
   double *y = nullptr, *rinv = nullptr, *L1 = nullptr;
-  int *cell = nullptr, *orig = nullptr, *ucell = nullptr, *uptr = nullptr;
+  int *orig = nullptr, *uptr = nullptr;
+  int *ent = nullptr, *forig = nullptr, *uent = nullptr;  // see MarchArgs
+  int *optr = nullptr, *gptr = nullptr;  // [group][N + 1] entries of observations and unique cells
   double *F0 = nullptr, *F1 = nullptr;           // m_max fields each (ping-pong)
   double *CA = nullptr, *CB = nullptr, *CC = nullptr;  // m_max control blocks each
   double *OA = nullptr;                          // m_max observation columns
   double *FU = nullptr;                          // m_max forcing columns per unique cell
   double *hx = nullptr, *dvec = nullptr, *fvec = nullptr, *scal = nullptr;
-  // host tables: observations sorted by step (offsets per step), unique cells per step
-  std::vector<int> obs_off, u_off;
+  std::vector<int> gstep;  // first step of each group of steps, then nsteps
   bool has_base = false;
 };
 
@@ -549,6 +475,17 @@ bool tracer_desc_ok(const riot_tracer_desc *d) {
   return true;
 }
 
+// The launches of a sweep: each time block's steps in equal groups of at most kMaxS (a group
+// does not cross a time block: one emission field per launch). First steps, then nsteps.
+std::vector<int> step_groups(const riot_tracer_desc &d) {
+  std::vector<int> g;
+  const int spb = d.nsteps / d.ntb, ng = (spb + riot::kMaxS - 1) / riot::kMaxS;
+  for (int b = 0; b < d.ntb; ++b)
+    for (int k = 0; k < ng; ++k) g.push_back(b * spb + (int)((long long)spb * k / ng));
+  g.push_back(d.nsteps);
+  return g;
+}
+
 size_t tracer_carve(riot_tracer &h, void *base) {
   TCarve c(base);
   const riot_tracer_desc &d = h.d;
@@ -564,10 +501,13 @@ size_t tracer_carve(riot_tracer &h, void *base) {
   h.y = c.take<double>(d.nobs);
   h.rinv = c.take<double>(d.nobs);
   h.L1 = c.take<double>((size_t)Nb * Nb);
-  h.cell = c.take<int>(d.nobs);
   h.orig = c.take<int>(d.nobs);
-  h.ucell = c.take<int>(d.nobs);
   h.uptr = c.take<int>(d.nobs + 1);
+  h.ent = c.take<int>(d.nobs);
+  h.forig = c.take<int>(d.nobs);
+  h.uent = c.take<int>(d.nobs);
+  h.optr = c.take<int>(step_groups(d).size() * (d.N + 1));
+  h.gptr = c.take<int>(step_groups(d).size() * (d.N + 1));
   h.F0 = c.take<double>(NN * m);
   h.F1 = c.take<double>(NN * m);
   h.CA = c.take<double>(nc * m);
@@ -587,47 +527,66 @@ size_t tracer_carve(riot_tracer &h, void *base) {
     if ((call) != hipSuccess) return RIOT_E_HIP; \
   } while (0)
 
+// Strips and chunks of a sweep over m members. Strips: as few as hold the width with the
+// halo. Chunks: a wave's march costs 2 S rows on top of its own, so a chunk is as tall as
+// leaves kWaves waves in the launch (two per SIMD, twice over so that the last ones even
+// out: 512 members at 512 x 512 take 17.1 ms per product with 4096, 19.4 with 2048, 17.4
+// with 8192), and at least kMinRows rows (value and gradient of one member at 512 x 512:
+// 16 rows 15 % slower than 8; 4 rows gain 2 % there and lose 25 % at 64 x 64).
+constexpr long long kWaves = 4096;
+constexpr int kMinRows = 8;
+
+void march_geometry(const riot_tracer *h, int m, riot::MarchArgs &a) {
+  const int N = h->d.N, use = riot::kCells - 2 * riot::kHalo;
+  a.m = m;
+  a.ns = (N + use - 1) / use;
+  a.width = ((N + a.ns - 1) / a.ns + 3) / 4 * 4;
+  const long long per = (long long)m * a.ns;  // waves per chunk row
+  const int want = (int)std::min<long long>((kWaves + per - 1) / per, N / kMinRows);
+  a.rows = ((N + want - 1) / want + 7) / 8 * 8;
+  a.nch = (N + a.rows - 1) / a.rows;
+}
+
+template <bool ADJ>
+riot_status launch_march(const riot_tracer *h, int S, const riot::MarchArgs &a) {
+  const dim3 grid((unsigned)((long long)a.m * a.nch * a.ns));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(64), 0, h->st, h->tv, a, h->tv.a0, h->tv.aW, a.ptr);
+  };
+  switch (S) {
+    case 1: go(riot::tracer_march_kernel<ADJ, 1>); break;
+    case 2: go(riot::tracer_march_kernel<ADJ, 2>); break;
+    case 3: go(riot::tracer_march_kernel<ADJ, 3>); break;
+    case 4: go(riot::tracer_march_kernel<ADJ, 4>); break;
+    case 5: go(riot::tracer_march_kernel<ADJ, 5>); break;
+    case 6: go(riot::tracer_march_kernel<ADJ, 6>); break;
+    case 7: go(riot::tracer_march_kernel<ADJ, 7>); break;
+    default: go(riot::tracer_march_kernel<ADJ, 8>); break;
+  }
+  TR_HIP(hipGetLastError());
+  return RIOT_OK;
+}
+
 // One sweep of the forward or tangent model over all members: fields start at zero,
 // step t uses control block tau(t); observation samples into obs [nobs x m].
 riot_status tracer_forward_sweep(riot_tracer *h, int m, const double *Wfield, long long Wstride,
                                  const double *bv, long long bv_stride, double *obs) {
   const riot_tracer_desc &d = h->d;
-  const TracerView &tv = h->tv;
-  const dim3 grid(d.N / riot::kTX, d.N / riot::kTY, m);
-  double *cur = nullptr, *bufs[2] = {h->F0, h->F1};
-  const int Nbb = h->Nb * h->Nb;
-  int nb = 0;  // buffers written so far
-  // observations of state s (the field after step s - 1) are [obs_off[s + 1], obs_off[s + 2])
-  auto sample = [&](int s, const double *f) -> riot_status {
-    const int beg = h->obs_off[s + 1], end = h->obs_off[s + 2];
-    if (end > beg && obs) {
-      hipLaunchKernelGGL(riot::tracer_sample_kernel, dim3(riot::blocks_for(end - beg), m),
-                         dim3(256), 0, h->st, d.N, beg, end, h->cell, h->orig, f, d.nobs, obs);
-      TR_HIP(hipGetLastError());
-    }
-    return RIOT_OK;
-  };
-  int t = 0;
-  for (; t + 1 < d.nsteps; t += 2) {  // steps t and t + 1 in one launch
-    const int tau0 = t / tv.spb, tau1 = (t + 1) / tv.spb;
-    double *next = bufs[(nb++) & 1];
-    hipLaunchKernelGGL(cur ? riot::tracer_step2_kernel<true> : riot::tracer_step2_kernel<false>,
-                       grid, dim3(riot::kThreads), 0, h->st, tv, cur,
-                       next, Wfield + Wstride * tau0, bv + (size_t)tau0 * Nbb,
-                       Wfield + Wstride * tau1, bv + (size_t)tau1 * Nbb, bv_stride,
-                       h->obs_off[t + 2], h->obs_off[t + 3], h->cell, h->orig, d.nobs, obs);
-    TR_HIP(hipGetLastError());
-    riot_status rs = sample(t + 2, next);
-    if (rs != RIOT_OK) return rs;
-    cur = next;
-  }
-  if (t < d.nsteps) {  // odd number of steps: the last one alone
-    const int tau = t / tv.spb;
-    double *next = bufs[(nb++) & 1];
-    hipLaunchKernelGGL(riot::tracer_step_kernel, grid, dim3(riot::kThreads), 0, h->st, tv, cur,
-                       next, Wfield + Wstride * tau, bv + (size_t)tau * Nbb, bv_stride);
-    TR_HIP(hipGetLastError());
-    riot_status rs = sample(t + 1, next);
+  const int Nbb = h->Nb * h->Nb, ng = (int)h->gstep.size() - 1;
+  riot::MarchArgs a{};
+  march_geometry(h, m, a);
+  a.bv_stride = bv_stride;
+  a.ent = h->ent, a.orig = h->forig, a.nobs = d.nobs;
+  a.obs = d.nobs > 0 ? obs : nullptr;
+  double *bufs[2] = {h->F0, h->F1};
+  for (int g = 0; g < ng; ++g) {
+    const int t = h->gstep[g], tau = t / h->tv.spb;
+    a.in = g ? bufs[(g - 1) & 1] : nullptr;
+    a.out = g + 1 < ng ? bufs[g & 1] : nullptr;
+    a.W = Wfield + Wstride * tau;
+    a.bv = bv + (size_t)tau * Nbb;
+    a.ptr = h->optr + (size_t)g * (d.N + 1);
+    riot_status rs = launch_march<false>(h, h->gstep[g + 1] - t, a);
     if (rs != RIOT_OK) return rs;
   }
   return RIOT_OK;
@@ -636,50 +595,28 @@ riot_status tracer_forward_sweep(riot_tracer *h, int m, const double *Wfield, lo
 // Adjoint sweep: gS [ncontrol x m] = G^T f for observation-space f [nobs x m].
 riot_status tracer_adjoint_sweep(riot_tracer *h, int m, const double *f, double *gS) {
   const riot_tracer_desc &d = h->d;
-  const TracerView &tv = h->tv;
   const size_t NN = (size_t)d.N * d.N;
-  const dim3 grid(d.N / riot::kTX, d.N / riot::kTY, m);
-  hipLaunchKernelGGL(riot::zero_kernel, dim3(riot::blocks_for((long long)NN * m)), dim3(256), 0,
-                     h->st, (long long)NN * m, h->F0);
-  TR_HIP(hipGetLastError());
-  hipLaunchKernelGGL(riot::zero_kernel, dim3(riot::blocks_for((long long)h->ncontrol * m)),
-                     dim3(256), 0, h->st, (long long)h->ncontrol * m, gS);
-  TR_HIP(hipGetLastError());
+  const int Nbb = h->Nb * h->Nb, ng = (int)h->gstep.size() - 1;
   if (h->nuniq > 0) {
     hipLaunchKernelGGL(riot::tracer_gather_kernel, dim3(riot::blocks_for(h->nuniq), m), dim3(256),
                        0, h->st, h->nuniq, h->uptr, h->orig, f, d.nobs, h->FU);
     TR_HIP(hipGetLastError());
   }
-  double *lam = h->F0, *other = h->F1;
-  const int Nbb = h->Nb * h->Nb;
-  // forcing of state t: unique cells [u_off[t], u_off[t + 1])
-  auto inject = [&](int t) -> riot_status {
-    const int beg = h->u_off[t], end = h->u_off[t + 1];
-    if (end > beg) {
-      hipLaunchKernelGGL(riot::tracer_inject_kernel, dim3(riot::blocks_for(end - beg), m),
-                         dim3(256), 0, h->st, d.N, beg, end, h->ucell, h->FU, h->nuniq, lam);
-      TR_HIP(hipGetLastError());
-    }
-    return RIOT_OK;
-  };
-  int t = d.nsteps;
-  for (; t >= 2; t -= 2) {  // states t -> t-1 -> t-2 in one launch
-    riot_status rs = inject(t);
+  riot::MarchArgs a{};
+  march_geometry(h, m, a);
+  a.gS_stride = h->ncontrol;
+  a.ent = h->uent, a.fu = h->FU, a.nuniq = h->nuniq;
+  double *bufs[2] = {h->F0, h->F1};
+  for (int g = ng - 1, k = 0; g >= 0; --g, ++k) {  // states gstep[g + 1] -> gstep[g]
+    const int t = h->gstep[g], tau = t / h->tv.spb;
+    a.in = k ? bufs[(k - 1) & 1] : nullptr;
+    a.out = g ? bufs[k & 1] : nullptr;
+    a.W = h->Wb + NN * tau;
+    a.gS = gS + (size_t)tau * Nbb;
+    a.gS_add = g + 1 < ng && h->gstep[g + 1] / h->tv.spb == tau;  // not the block's first launch
+    a.ptr = h->gptr + (size_t)g * (d.N + 1);
+    riot_status rs = launch_march<true>(h, h->gstep[g + 1] - t, a);
     if (rs != RIOT_OK) return rs;
-    const int tau1 = (t - 1) / tv.spb, tau0 = (t - 2) / tv.spb;
-    hipLaunchKernelGGL(riot::tracer_adjoint2_kernel, grid, dim3(riot::kThreads), 0, h->st, tv,
-                       lam, t > 2 ? other : nullptr, h->Wb + NN * tau1, h->Wb + NN * tau0,
-                       gS + (size_t)tau1 * Nbb, gS + (size_t)tau0 * Nbb, (long long)h->ncontrol,
-                       h->u_off[t - 1], h->u_off[t], h->ucell, h->FU, h->nuniq);
-    TR_HIP(hipGetLastError());
-    std::swap(lam, other);
-  }
-  if (t == 1) {  // odd number of steps: the first one alone
-    riot_status rs = inject(1);
-    if (rs != RIOT_OK) return rs;
-    hipLaunchKernelGGL(riot::tracer_adjoint_kernel, grid, dim3(riot::kThreads), 0, h->st, tv, lam,
-                       nullptr, h->Wb, gS, (long long)h->ncontrol);
-    TR_HIP(hipGetLastError());
   }
   return RIOT_OK;
 }
@@ -736,32 +673,51 @@ riot_status riot_tracer_init(const riot_tracer_desc *desc, void *workspace, size
   tv.spb = d.nsteps / d.ntb;
   tv.dt = d.dt, tv.aS = d.dt * (d.v + d.K), tv.aE = d.dt * d.K, tv.aN = d.dt * d.K;
   tv.a0 = h->a0, tv.aW = h->aW;
-  // observations sorted by step; per step, unique cells with lists of observations.
-  // obs_off[t + 1] .. obs_off[t + 2]: sorted observations of step t; u_off[t] .. u_off[t + 1]:
-  // unique cells of step t
-  std::vector<int> ord(d.nobs);
-  for (int o = 0; o < d.nobs; ++o) ord[o] = o;
-  std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) {
-    if (d.obs_t[a] != d.obs_t[b]) return d.obs_t[a] < d.obs_t[b];
-    return (long long)d.obs_y[a] * d.N + d.obs_x[a] < (long long)d.obs_y[b] * d.N + d.obs_x[b];
-  });
-  std::vector<int> cell(d.nobs), ucell, uptr{0};
-  h->obs_off.assign(d.nsteps + 3, 0);
-  h->u_off.assign(d.nsteps + 2, 0);
+  // Observations in the order of the march: by group of steps, by the row taken in when their
+  // level finishes theirs, by level and column. Forward: state t + lev of the group's first
+  // state t, lev = 1 .. S; adjoint: state t + S - lev, lev = 0 .. S - 1. Both put an
+  // observation of state t + k in the same group for 1 <= k <= S.
+  h->gstep = step_groups(d);
+  const int ng = (int)h->gstep.size() - 1;
+  struct Entry {
+    int g, r, lev, cell, o;
+  };
+  std::vector<Entry> fe(d.nobs), ae(d.nobs);
+  for (int o = 0; o < d.nobs; ++o) {
+    const int g = (int)(std::lower_bound(h->gstep.begin(), h->gstep.end(), d.obs_t[o]) -
+                        h->gstep.begin()) - 1;
+    const int c = d.obs_y[o] * d.N + d.obs_x[o];
+    const int lf = d.obs_t[o] - h->gstep[g], la = h->gstep[g + 1] - d.obs_t[o];
+    fe[o] = {g, (d.obs_y[o] + lf) % d.N, lf, c, o};
+    ae[o] = {g, (d.obs_y[o] + la) % d.N, la, c, o};
+  }
+  auto before = [](const Entry &a, const Entry &b) {
+    if (a.g != b.g) return a.g < b.g;
+    if (a.r != b.r) return a.r < b.r;
+    if (a.lev != b.lev) return a.lev < b.lev;
+    return a.cell != b.cell ? a.cell < b.cell : a.o < b.o;
+  };
+  std::sort(fe.begin(), fe.end(), before);
+  std::sort(ae.begin(), ae.end(), before);
+  const size_t n1 = (size_t)d.N + 1;
+  std::vector<int> ent(d.nobs), forig(d.nobs), ord(d.nobs), uent, uptr{0};
+  auto pack = [&](const Entry &e) { return e.cell % d.N + (e.lev << riot::kLevShift); };
+  std::vector<int> optr((ng + 1) * n1, 0), gptr((ng + 1) * n1, 0);
   for (int k = 0; k < d.nobs; ++k) {
-    const int o = ord[k];
-    cell[k] = d.obs_y[o] * d.N + d.obs_x[o];
-    h->obs_off[d.obs_t[o] + 2]++;
-    if (k == 0 || d.obs_t[ord[k - 1]] != d.obs_t[o] || cell[k - 1] != cell[k]) {
-      ucell.push_back(cell[k]);
+    ent[k] = pack(fe[k]);
+    forig[k] = fe[k].o;
+    optr[fe[k].g * n1 + fe[k].r + 1]++;
+    ord[k] = ae[k].o;
+    if (k == 0 || before({ae[k - 1].g, ae[k - 1].r, ae[k - 1].lev, ae[k - 1].cell, 0},
+                         {ae[k].g, ae[k].r, ae[k].lev, ae[k].cell, 0})) {
+      uent.push_back(pack(ae[k]));
       uptr.push_back(uptr.back());
-      h->u_off[d.obs_t[o] + 1]++;
+      gptr[ae[k].g * n1 + ae[k].r + 1]++;
     }
     uptr.back()++;
   }
-  for (int t = 1; t < (int)h->obs_off.size(); ++t) h->obs_off[t] += h->obs_off[t - 1];
-  for (int t = 1; t < (int)h->u_off.size(); ++t) h->u_off[t] += h->u_off[t - 1];
-  h->nuniq = (int)ucell.size();
+  for (size_t k = 1; k < optr.size(); ++k) optr[k] += optr[k - 1], gptr[k] += gptr[k - 1];
+  h->nuniq = (int)uent.size();
   riot_status rs = RIOT_OK;
   auto cp = [&](void *dst, const void *src, size_t b) {
     if (b && hipMemcpyAsync(dst, src, b, hipMemcpyHostToDevice, h->st) != hipSuccess)
@@ -772,10 +728,13 @@ riot_status riot_tracer_init(const riot_tracer_desc *desc, void *workspace, size
   cp(h->aW, aW.data(), d.N * sizeof(double));
   cp(h->E, d.E, NN * sizeof(double));
   cp(h->L1, d.L1, (size_t)h->Nb * h->Nb * sizeof(double));
-  cp(h->cell, cell.data(), cell.size() * sizeof(int));
   cp(h->orig, ord.data(), ord.size() * sizeof(int));
-  cp(h->ucell, ucell.data(), ucell.size() * sizeof(int));
   cp(h->uptr, uptr.data(), uptr.size() * sizeof(int));
+  cp(h->ent, ent.data(), ent.size() * sizeof(int));
+  cp(h->forig, forig.data(), forig.size() * sizeof(int));
+  cp(h->uent, uent.data(), uent.size() * sizeof(int));
+  cp(h->optr, optr.data(), optr.size() * sizeof(int));
+  cp(h->gptr, gptr.data(), gptr.size() * sizeof(int));
   cp(h->y, d.y, (size_t)d.nobs * sizeof(double));
   cp(h->rinv, d.rinv, (size_t)d.nobs * sizeof(double));
   if (hipStreamSynchronize(h->st) != hipSuccess) rs = RIOT_E_HIP;
