@@ -82,7 +82,8 @@ typedef struct {
     const double *l_taps;      /* [w+1] half-kernel l_0..l_w of the symmetric circulant L */
     int32_t m_max;             /* largest probe block used with this handle, >= 1 */
     riot_precision prec;       /* precision of the TL/AD integrations */
-    int32_t elems_per_lane;    /* 0 = choose automatically, else 1, 2, 4, 8 or 16
+    int32_t elems_per_lane;    /* 0 = choose automatically, else 1, 2, 4, 8 or 16: layout of FP32
+                                  and of very large handles, a condition on n for all others
                                   (n must be divisible by it; n / it <= 512 for 8 and 16,
                                   <= 1024 otherwise) */
     int32_t ckpt_stride;       /* 0 = the handle stores the whole window's trajectory (every
@@ -504,7 +505,7 @@ riot_status riot_tracer_gradient(riot_tracer *h, const double *v, double *grad, 
 int32_t riot_gaussian_taps(double ell, double sigma_b, int32_t max_taps, double *taps);
 
 /* Workspace bytes for a batch (0 if a descriptor is unusable in a batch). Every
- * descriptor's elems_per_lane is ignored (8 is used); all must share `prec`. */
+ * descriptor's elems_per_lane is ignored (n must be divisible by 8); all must share `prec`. */
 size_t riot_batch_workspace_bytes(int32_t nprob, const riot_desc *descs);
 
 /* Create a batch in a caller-allocated device workspace (256-byte aligned). Synchronises

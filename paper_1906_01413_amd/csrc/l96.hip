@@ -4,159 +4,90 @@
 // Hessian-probe product (Alg. 3, y_i = A w_i with A = L^T G^T R^{-1} G L):
 // one TL sweep over the window collecting R^{-1}-weighted observation values,
 // one AD sweep injecting them at the observed steps. Each member (probe) runs
-// in one workgroup with its state in registers; the periodic halo is exchanged
-// through LDS once per RK4 stage.
+// in one workgroup (or one wave) with its state in registers.
 
-#include <cstdlib>
+#include <type_traits>
 
+#include "l96_common.h"
 #include "riot_internal.h"
 
 namespace riot {
 namespace {
 
-constexpr int kLdsSlots = 4;
+// LDS elements per wave of the batched launches: halo buffer of a one-strip member (2 parities,
+// at most 199 each) and a staging row of up to 17 positions per lane
+constexpr int kWaveLds = 400 + 64 * 17;
 
-__device__ __forceinline__ int slot_of(int jj, int E) {
-  if (jj == 0) return 0;
-  if (jj == 1) return 1;
-  if (jj == E - 2) return 2;
-  return 3;
+// ---------------------------------------------------------------------------
+// Strips. A member's state of n elements is cut into NW strips of `own` consecutive elements,
+// one wave each; lane i of a wave holds the E consecutive positions i E .. i E + E - 1 of a
+// window of 64 E elements that starts HL elements before the strip. A wave so recomputes HL
+// elements of its left and HR of its right neighbour: inside the window the periodic halo of a
+// stage comes from the adjacent lanes (DPP moves), with no LDS and no barrier, and what goes
+// wrong at the window's ends creeps inwards by at most two positions per stage. Only after
+// mv.K RK4 steps do the waves refresh their halos through LDS, one barrier each time.
+//
+// How far it creeps (positions invalid after s stages, from the left / right): the nonlinear
+// stage and the TL use i-2 .. i+1: 2 s / s. The trajectory refreshes every step, so the
+// stored stage s = 0..3 of a step is wrong on 2 s / s positions. The AD uses i-1 .. i+2 of
+// its own state and i-2 .. i+2 of stages 3, 2, 1, 0 of the base: the first stage leaves
+// 8 / 5 wrong, each further one 1 / 2 more. After K steps: TL 8 K / 4 K, AD 4 K + 7 / 8 K + 3.
+// The layout (strip_layout, in the API layer) leaves HL = max(8 K, 4 K + 7), HR = 8 K + 3.
+//
+// Before, a member's lanes exchanged their halo through LDS with a workgroup barrier in every
+// stage, and the stage was the latency of that. A block product (TL and AD over the window) took
+// then and takes now: n = 40, m = 30, T = 20: 131 and 54 us; n = 2048, m = 128, T = 50: 217 and
+// 135 us; n = 4096, T = 100: m = 16 758 and 405 us, m = 256 783 and 424 us, m = 272 790 and
+// 580 us. What bounds it now: FP64 issue (about 390 instructions per 9 positions and step in the
+// TL, two waves on a SIMD), then the base loads (37 KB a stage and compute unit at 64 bytes a
+// clock).
+// ---------------------------------------------------------------------------
+
+// place of position j of lane i in its wave's part of a stage block: rows in pairs, each lane's
+// two values adjacent (16-byte loads: a product of n = 4096, m = 256, T = 100 takes 424 us, with
+// one row per load 564), an odd last row by itself
+__device__ __forceinline__ int base_index(int E, int j, int i) {
+  return (j | 1) < E ? (j >> 1) * 128 + 2 * i + (j & 1) : j * 64 + i;
 }
 
-// LDS offsets of the four neighbours a-2, a-1, a+E, a+E+1 of thread l.
-template <int E>
-struct HaloMap {
-  int off[4];
-  __device__ void init(int l, int n, int NT) {
-    const int a = l * E;
-    const int g[4] = {a - 2, a - 1, a + E, a + E + 1};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      int gg = g[k] % n;
-      if (gg < 0) gg += n;
-      off[k] = slot_of(gg % E, E) * NT + gg / E;
-    }
-  }
-};
-
-// Barrier for a halo exchange: the workgroup, or (WAVE) only the calling wave, whose LDS
-// operations complete in issue order, so waiting for its own writes is enough.
-template <bool WAVE>
-__device__ __forceinline__ void member_sync() {
-  if constexpr (WAVE) {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
-  } else {
-    __syncthreads();
-  }
+// value of the lane one below or above (the end lanes get zero)
+template <int CTRL>
+__device__ __forceinline__ int dpp_int(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
 }
-
-// Write this thread's boundary values, barrier, read the neighbours'.
-// All threads of the block (of the wave, WAVE) must call it (inactive ones pass active=false).
-template <typename Real, int E, bool WAVE = false>
-__device__ __forceinline__ void exchange(Real *lds, int &parity, int NT, int l, bool active,
-                                         const HaloMap<E> &hm, const Real (&v)[E], Real &hl2,
-                                         Real &hl1, Real &hr1, Real &hr2) {
-  Real *b = lds + parity * kLdsSlots * NT;
-  if (active) {
-    b[0 * NT + l] = v[0];
-    b[1 * NT + l] = v[E > 1 ? 1 : 0];
-    b[2 * NT + l] = v[E > 1 ? E - 2 : 0];
-    b[3 * NT + l] = v[E - 1];
-  }
-  member_sync<WAVE>();
-  if (active) {
-    hl2 = b[hm.off[0]];
-    hl1 = b[hm.off[1]];
-    hr1 = b[hm.off[2]];
-    hr2 = b[hm.off[3]];
-  }
-  parity ^= 1;
+template <int CTRL>
+__device__ __forceinline__ double dpp_shift(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)dpp_int<CTRL>((int)b);
+  const unsigned hi = (unsigned)dpp_int<CTRL>((int)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
-
-// Load the (E + 4)-value extended base state xe[k] = x[a - 2 + k] of one stage block.
-template <typename Real, int E>
-__device__ __forceinline__ void load_base(const Real *__restrict__ blk, int NT, int l,
-                                          Real (&xe)[E + 4]) {
-#pragma unroll
-  for (int j = 0; j < E; ++j) xe[2 + j] = blk[j * NT + l];
-  xe[0] = blk[(E + 0) * NT + l];
-  xe[1] = blk[(E + 1) * NT + l];
-  xe[E + 2] = blk[(E + 2) * NT + l];
-  xe[E + 3] = blk[(E + 3) * NT + l];
-}
-
-// The same load through a buffer resource over the whole trajectory: the row offset is a
-// scalar (SGPR) and the lane offset one VGPR, so no per-row 64-bit vector address is
-// formed or kept live across the window loop. Reads past the resource return 0.
-struct TrajRsrc {
-  __amdgpu_buffer_rsrc_t r;
-  int row_bytes;  // NT * sizeof(Real)
-};
-
-template <typename Real>
-__device__ __forceinline__ TrajRsrc traj_rsrc(const ModelView &mv) {
-  const long long bytes = (long long)(mv.T + 1) * 4 * (mv.E + 4) * mv.NT * (long long)sizeof(Real);
-  const int nrec = bytes > 0x7fffffffLL ? 0x7fffffff : (int)bytes;
-  // dword 3 = 0x00020000: raw 32-bit data format of the gfx9 family
-  return {__builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(mv.xs), (short)0, nrec, 0x00020000),
-          mv.NT * (int)sizeof(Real)};
-}
-
-template <typename Real>
-__device__ __forceinline__ Real buf_load(const TrajRsrc &tr, int voff, int soff);
-template <>
-__device__ __forceinline__ double buf_load<double>(const TrajRsrc &tr, int voff, int soff) {
-  const auto v = __builtin_amdgcn_raw_buffer_load_b64(tr.r, voff, soff, 0);
-  double d;
-  __builtin_memcpy(&d, &v, sizeof(d));
-  return d;
-}
-template <>
-__device__ __forceinline__ float buf_load<float>(const TrajRsrc &tr, int voff, int soff) {
-  const auto v = __builtin_amdgcn_raw_buffer_load_b32(tr.r, voff, soff, 0);
-  float f;
-  __builtin_memcpy(&f, &v, sizeof(f));
-  return f;
-}
-
-// Stage block (t, s) into xe, as load_base.
-template <typename Real, int E>
-__device__ __forceinline__ void load_base_buf(const TrajRsrc &tr, int t, int s, int l,
-                                              Real (&xe)[E + 4]) {
-  const int blk = (t * 4 + s) * (E + 4) * tr.row_bytes;
-  const int voff = l * (int)sizeof(Real);
-#pragma unroll
-  for (int j = 0; j < E; ++j) xe[2 + j] = buf_load<Real>(tr, voff, blk + j * tr.row_bytes);
-  xe[0] = buf_load<Real>(tr, voff, blk + (E + 0) * tr.row_bytes);
-  xe[1] = buf_load<Real>(tr, voff, blk + (E + 1) * tr.row_bytes);
-  xe[E + 2] = buf_load<Real>(tr, voff, blk + (E + 2) * tr.row_bytes);
-  xe[E + 3] = buf_load<Real>(tr, voff, blk + (E + 3) * tr.row_bytes);
-}
+__device__ __forceinline__ double from_below(double v) { return dpp_shift<0x138>(v); }  // wave_shr:1
+__device__ __forceinline__ double from_above(double v) { return dpp_shift<0x130>(v); }  // wave_shl:1
 
 // d = J(x) e : (J e)_i = (e_{i+1} - e_{i-2}) x_{i-1} + (x_{i+1} - x_{i-2}) e_{i-1} - e_i
-template <typename Real, int E>
-__device__ __forceinline__ void tl_jac(const Real (&xe)[E + 4], const Real (&e)[E], Real hl2,
-                                       Real hl1, Real hr1, Real (&d)[E]) {
+template <int E>
+__device__ __forceinline__ void tl_jac(const double (&xe)[E + 4], const double (&e)[E], double hl2,
+                                       double hl1, double hr1, double (&d)[E]) {
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    const Real em2 = (j >= 2) ? e[j - 2] : (j == 0 ? hl2 : hl1);
-    const Real em1 = (j >= 1) ? e[j - 1] : hl1;
-    const Real ep1 = (j + 1 < E) ? e[j + 1] : hr1;
-    d[j] = (ep1 - em2) * xe[j + 1] + (xe[j + 3] - xe[j]) * em1 - e[j];
+    const double em2 = (j >= 2) ? e[j - 2] : (j == 0 ? hl2 : hl1);
+    const double em1 = (j >= 1) ? e[j - 1] : hl1;
+    const double ep1 = (j + 1 < E) ? e[j + 1] : hr1;
+    d[j] = fma(ep1 - em2, xe[j + 1], fma(xe[j + 3] - xe[j], em1, -e[j]));
   }
 }
 
 // s = J(x)^T w : (J^T w)_i = x_{i-2} w_{i-1} - x_{i+1} w_{i+2} + (x_{i+2} - x_{i-1}) w_{i+1} - w_i
-template <typename Real, int E>
-__device__ __forceinline__ void ad_jac(const Real (&xe)[E + 4], const Real (&w)[E], Real hl1,
-                                       Real hr1, Real hr2, Real (&s)[E]) {
+template <int E>
+__device__ __forceinline__ void ad_jac(const double (&xe)[E + 4], const double (&w)[E], double hl1,
+                                       double hr1, double hr2, double (&s)[E]) {
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    const Real wm1 = (j >= 1) ? w[j - 1] : hl1;
-    const Real wp1 = (j + 1 < E) ? w[j + 1] : hr1;
-    const Real wp2 = (j + 2 < E) ? w[j + 2] : (j + 2 == E ? hr1 : hr2);
-    s[j] = xe[j] * wm1 - xe[j + 3] * wp2 + (xe[j + 4] - xe[j + 1]) * wp1 - w[j];
+    const double wm1 = (j >= 1) ? w[j - 1] : hl1;
+    const double wp1 = (j + 1 < E) ? w[j + 1] : hr1;
+    const double wp2 = (j + 2 < E) ? w[j + 2] : (j + 2 == E ? hr1 : hr2);
+    s[j] = fma(xe[j + 4] - xe[j + 1], wp1, fma(-xe[j + 3], wp2, fma(xe[j], wm1, -w[j])));
   }
 }
 
@@ -167,454 +98,450 @@ __device__ __forceinline__ void tendency(const double (&xe)[E + 4], double F, do
   for (int j = 0; j < E; ++j) f[j] = (xe[j + 3] - xe[j]) * xe[j + 1] - xe[j + 2] + F;
 }
 
-template <typename Real>
-__device__ __forceinline__ const Real *stage_block(const ModelView &mv, int t, int s) {
-  return reinterpret_cast<const Real *>(mv.xs) +
-         (size_t)(t * 4 + s) * (size_t)(mv.E + 4) * (size_t)mv.NT;
-}
+// A wave's strip: positions, halo refresh, base loads, TL and AD sweeps.
+template <int E, int MB = 1>
+struct Strip {
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  const ModelView &mv;
+  double *lds;               // halo buffer of the member(s), 2 parities
+  double *stg;               // this wave's staging row of observed steps (64 E)
+  int lane, w, parity;
+  int el0;                 // element of this lane's first position
+  unsigned own, pub, sub;  // bit j: position j is owned / read by another strip / a halo position
+  int pb, sb;              // its buffer index as published / read is pb + j / sb + j (unless
+                           // the buffer holds the whole state, element by element)
+  bool whole;              // the buffer holds the whole state (shorter than two halos)
+  int nbuf;                // elements per parity
 
-// ---------------------------------------------------------------------------
-// Nonlinear trajectory (one workgroup).
-// ---------------------------------------------------------------------------
-
-template <int E>
-__device__ void store_block(double *xs64, float *xs32, int t, int s, int E_, int NT, int l,
-                            const double (&v)[E], double hl2, double hl1, double hr1, double hr2) {
-  const size_t base = (size_t)(t * 4 + s) * (size_t)(E_ + 4) * NT;
-  gmem<double> *b = gptr(xs64 + base);
+  __device__ Strip(const ModelView &m, double *lds_, int tid)
+      : mv(m), lds(lds_), lane(tid & 63), w(__builtin_amdgcn_readfirstlane(tid >> 6)), parity(0) {
+    const int n = mv.n, HL = mv.HL, HR = mv.HR, ew = HL + HR;
+    const int ow = min(mv.own, n - w * mv.own);
+    const int q0 = lane * E - HL;  // strip-relative position of j = 0
+    el0 = (w * mv.own + q0) % n;
+    el0 = el0 < 0 ? el0 + n : el0;
+    whole = n < ew + E;
+    const int nslot = ew + 4 * E;
+    nbuf = whole ? n : mv.NW * nslot;
+    stg = lds + 2 * MB * nbuf + w * 64 * E;
+    own = pub = sub = 0;
 #pragma unroll
-  for (int j = 0; j < E; ++j) b[j * NT + l] = v[j];
-  b[(E + 0) * NT + l] = hl2;
-  b[(E + 1) * NT + l] = hl1;
-  b[(E + 2) * NT + l] = hr1;
-  b[(E + 3) * NT + l] = hr2;
-  if (xs32) {
-    gmem<float> *c = gptr(xs32 + base);
-#pragma unroll
-    for (int j = 0; j < E; ++j) c[j * NT + l] = (float)v[j];
-    c[(E + 0) * NT + l] = (float)hl2;
-    c[(E + 1) * NT + l] = (float)hl1;
-    c[(E + 2) * NT + l] = (float)hr1;
-    c[(E + 3) * NT + l] = (float)hr2;
-  }
-}
-
-// The same stores through buffer resources over the whole trajectory: the block and row
-// offsets are scalars (SGPR soffset) and the lane offset one VGPR, so no 64-bit address is
-// formed per store. Used when the trajectory is below 2^31 bytes.
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-struct TrajStore {
-  __amdgpu_buffer_rsrc_t r64, r32;
-  bool has32;
-};
-template <int E>
-__device__ __forceinline__ void store_block_buf(const TrajStore &ts, int t, int s, int NT, int l,
-                                                const double (&v)[E], double hl2, double hl1,
-                                                double hr1, double hr2) {
-  const int row0 = (t * 4 + s) * (E + 4);
-  auto st64 = [&](int row, double x) {
-    u32x2 d;
-    __builtin_memcpy(&d, &x, sizeof(d));
-    __builtin_amdgcn_raw_buffer_store_b64(d, ts.r64, l * 8, (row0 + row) * NT * 8, 0);
-  };
-  auto st32 = [&](int row, double x) {
-    const float f = (float)x;
-    unsigned u;
-    __builtin_memcpy(&u, &f, sizeof(u));
-    __builtin_amdgcn_raw_buffer_store_b32(u, ts.r32, l * 4, (row0 + row) * NT * 4, 0);
-  };
-#pragma unroll
-  for (int j = 0; j < E; ++j) st64(j, v[j]);
-  st64(E + 0, hl2);
-  st64(E + 1, hl1);
-  st64(E + 2, hr1);
-  st64(E + 3, hr2);
-  if (ts.has32) {
-#pragma unroll
-    for (int j = 0; j < E; ++j) st32(j, v[j]);
-    st32(E + 0, hl2);
-    st32(E + 1, hl1);
-    st32(E + 2, hr1);
-    st32(E + 3, hr2);
-  }
-}
-
-// xu != nullptr: one workgroup per initial state (x0 + blockIdx.x n), no stage blocks; the
-// state at every observed (step, variable) pair u is written to xu[blockIdx.x U + u].
-template <int E>
-__device__ __forceinline__ void sample_obs(const ModelView &mv, int t, int l,
-                                           const double (&x)[E], double *__restrict__ xu) {
-  const int k = gptr(mv.stepk)[t];
-  if (k < 0) return;
-  const int us = gptr(mv.ustart)[k * mv.NT + l];
-  const unsigned mask = (unsigned)gptr(mv.umask)[k * mv.NT + l];
-#pragma unroll
-  for (int j = 0; j < E; ++j)
-    if ((mask >> j) & 1u) gptr(xu)[us + __popc(mask & ((1u << j) - 1u))] = x[j];
-}
-
-template <int E>
-__global__ void __launch_bounds__(E >= 8 ? 512 : 1024)
-    trajectory_kernel(ModelView mv, int nsteps, const double *__restrict__ x0,
-                      double *__restrict__ xout, double *__restrict__ xs64,
-                      float *__restrict__ xs32, const TrajJob *__restrict__ jobs,
-                      double *__restrict__ xu) {
-  if (jobs) {  // batched: one workgroup per problem (blockDim may exceed the problem's NT)
-    const TrajJob &J = jobs[blockIdx.x];
-    mv = J.mv, nsteps = J.mv.T, x0 = J.x0, xout = nullptr, xs64 = J.xs64, xs32 = J.xs32;
-  }
-  if (xu) {
-    x0 += (size_t)blockIdx.x * mv.n;
-    xu += (size_t)blockIdx.x * mv.U;
-  }
-  extern __shared__ double lds_d[];
-  const int l = threadIdx.x;
-  const int NT = mv.NT;
-  const bool active = l < mv.A;
-  const int a = l * E;
-  HaloMap<E> hm;
-  if (active) hm.init(l, mv.n, NT);
-  int parity = 0;
-  const double h = mv.h, F = mv.F;
-  double x[E], xs[E], acc[E], k[E], xe[E + 4];
-  double hl2 = 0, hl1 = 0, hr1 = 0, hr2 = 0;
-  // the stage blocks through buffer stores when the whole trajectory fits a 2^31-byte resource
-  const long long traj_bytes = (long long)(nsteps + 1) * 4 * (E + 4) * NT * (long long)sizeof(double);
-  const bool bufst = xs64 != nullptr && !jobs && traj_bytes <= 0x7fffffffLL;
-  TrajStore tst;
-  tst.has32 = xs32 != nullptr;
-  if (bufst) {
-    tst.r64 = __builtin_amdgcn_make_buffer_rsrc(xs64, (short)0, (int)traj_bytes, 0x00020000);
-    tst.r32 = __builtin_amdgcn_make_buffer_rsrc(tst.has32 ? (void *)xs32 : (void *)xs64, (short)0,
-                                                (int)(traj_bytes / 2), 0x00020000);
-  }
-  auto store_blk = [&](int t, int sidx, const double (&v)[E]) __attribute__((always_inline)) {
-    if (bufst)
-      store_block_buf<E>(tst, t, sidx, NT, l, v, hl2, hl1, hr1, hr2);
-    else
-      store_block<E>(xs64, xs32, t, sidx, E, NT, l, v, hl2, hl1, hr1, hr2);
-  };
-#pragma unroll
-  for (int j = 0; j < E; ++j) x[j] = active ? gptr(x0)[a + j] : 0.0;
-
-  auto build = [&](const double (&v)[E]) {
-    xe[0] = hl2;
-    xe[1] = hl1;
-#pragma unroll
-    for (int j = 0; j < E; ++j) xe[2 + j] = v[j];
-    xe[E + 2] = hr1;
-    xe[E + 3] = hr2;
-  };
-
-  if constexpr (E >= 8) {
-    if (!jobs && !xu && mv.A == NT) {
-      // One full problem: each stage computes its four boundary elements first and publishes
-      // the next stage's boundary values before the interior elements and the block's
-      // stores, so the halo exchange's LDS round trip overlaps that work. The same
-      // expressions as the general loop below, so the same results bit for bit.
-      auto publish = [&](const double (&v)[E]) __attribute__((always_inline)) {
-        double *bb = lds_d + parity * kLdsSlots * NT;
-        bb[0 * NT + l] = v[0];
-        bb[1 * NT + l] = v[1];
-        bb[2 * NT + l] = v[E - 2];
-        bb[3 * NT + l] = v[E - 1];
-      };
-      auto receive = [&]() __attribute__((always_inline)) {
-        __syncthreads();
-        const double *bb = lds_d + parity * kLdsSlots * NT;
-        hl2 = bb[hm.off[0]];
-        hl1 = bb[hm.off[1]];
-        hr1 = bb[hm.off[2]];
-        hr2 = bb[hm.off[3]];
-        parity ^= 1;
-      };
-      auto store_xe = [&](int t, int sidx) __attribute__((always_inline)) {
-        double cur[E];
-#pragma unroll
-        for (int j = 0; j < E; ++j) cur[j] = xe[2 + j];
-        store_blk(t, sidx, cur);
-      };
-      // stage update of element j: c1 = first stage (acc = k), cw = weight of k in acc,
-      // cn = coefficient of k in the next state, to4 = the final stage (the next state is x)
-#define RIOT_TRAJ_ELEM(J, FIRST, CW, CN, LAST)                                   \
-  {                                                                              \
-    const int j_ = (J);                                                          \
-    k[j_] = (xe[j_ + 3] - xe[j_]) * xe[j_ + 1] - xe[j_ + 2] + F;                 \
-    if (FIRST)                                                                   \
-      acc[j_] = k[j_];                                                           \
-    else if (LAST)                                                               \
-      acc[j_] += k[j_];                                                          \
-    else                                                                         \
-      acc[j_] += 2.0 * k[j_];                                                    \
-    if (LAST)                                                                    \
-      x[j_] = x[j_] + (h / 6.0) * acc[j_];                                       \
-    else                                                                         \
-      xs[j_] = x[j_] + (CN) * k[j_];                                             \
-  }
-#define RIOT_TRAJ_STAGE(T_, SIDX, FIRST, CN, LAST)                               \
-  {                                                                              \
-    receive();                                                                   \
-    if (SIDX == 0) build(x); else build(xs);                                     \
-    _Pragma("unroll") for (int b_ = 0; b_ < 4; ++b_)                             \
-        RIOT_TRAJ_ELEM(b_ < 2 ? b_ : E - 4 + b_, FIRST, 0, CN, LAST)             \
-    if (LAST) publish(x); else publish(xs);                                      \
-    if (xs64) store_xe(T_, SIDX);                                                \
-    _Pragma("unroll") for (int j2 = 2; j2 < E - 2; ++j2)                         \
-        RIOT_TRAJ_ELEM(j2, FIRST, 0, CN, LAST)                                   \
-  }
-      publish(x);
-      for (int t = 0; t < nsteps; ++t) {
-        RIOT_TRAJ_STAGE(t, 0, true, 0.5 * h, false)
-        RIOT_TRAJ_STAGE(t, 1, false, 0.5 * h, false)
-        RIOT_TRAJ_STAGE(t, 2, false, h, false)
-        RIOT_TRAJ_STAGE(t, 3, false, 0.0, true)
+    for (int j = 0; j < E; ++j) {
+      const int q = q0 + j;
+      if (q >= 0 && q < ow) {
+        own |= 1u << j;
+        if (whole || q < HR || q >= ow - HL) pub |= 1u << j;
+      } else if (q >= -HL && q < ow + HR) {
+        sub |= 1u << j;
       }
-#undef RIOT_TRAJ_STAGE
-#undef RIOT_TRAJ_ELEM
-      if (xs64) {
-        receive();
-        store_blk(nsteps, 0, x);
+    }
+    pb = sb = 0;
+    if (!whole) {
+      // a strip's slot: its first HR elements (its left neighbour's right halo), then its last
+      // HL (its right neighbour's left halo), each with E spare places at both ends, so that
+      // a lane writes and reads all its E positions (no lane holds positions of both ends)
+      pb = w * nslot + (q0 < HR ? E + q0 : HR + 3 * E + q0 - (ow - HL));
+      const int wl = w == 0 ? mv.NW - 1 : w - 1, wr = w == mv.NW - 1 ? 0 : w + 1;
+      sb = q0 < 0 ? wl * nslot + HR + 3 * E + q0 + HL : wr * nslot + E + q0 - ow;
+    }
+  }
+
+  // element of position j from el0 (opaque(el0) where the E elements must not stay in
+  // registers from an earlier use)
+  __device__ __forceinline__ int element(int e0, int j) const {
+    const int e = e0 + j;
+    return e >= mv.n ? e - mv.n : e;
+  }
+  __device__ __forceinline__ static int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+  }
+
+  // The halo positions of v from the strips that own them. Two buffers in turn, so that one
+  // barrier per refresh is enough.
+  template <int M>
+  __device__ __forceinline__ void refresh(double (&v)[M][E]) {
+    double *b = lds + parity * nbuf * M;
+    parity ^= 1;
+    auto sync = [&]() {
+      if (mv.NW == 1) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      } else {
+        // (not __syncthreads: its fence would also wait for the base loads in flight)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
       }
-      if (xout) {
+    };
+    const unsigned pub_ = TIGHT ? opaque(pub) : pub, sub_ = TIGHT ? opaque(sub) : sub;
+    if (whole) {
+      const int e0 = opaque(el0);
 #pragma unroll
-        for (int j = 0; j < E; ++j) gptr(xout)[a + j] = x[j];
-      }
+      for (int q = 0; q < M; ++q)
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+          if (pub_ >> j & 1) b[q * nbuf + element(e0, j)] = v[q][j];
+      sync();
+#pragma unroll
+      for (int q = 0; q < M; ++q)
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+          if (sub_ >> j & 1) v[q][j] = b[q * nbuf + element(e0, j)];
       return;
     }
-  }
-  for (int t = 0; t < nsteps; ++t) {
-    if (xu && active) sample_obs<E>(mv, t, l, x, xu);
-    // stage 1
-    exchange<double, E>(lds_d, parity, NT, l, active, hm, x, hl2, hl1, hr1, hr2);
-    if (active) {
-      build(x);
-      if (xs64) store_blk(t, 0, x);
-      tendency<E>(xe, F, k);
+    if (pub_) {
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
-        acc[j] = k[j];
-        xs[j] = x[j] + (0.5 * h) * k[j];
-      }
+      for (int q = 0; q < M; ++q)
+#pragma unroll
+        for (int j = 0; j < E; ++j) b[q * nbuf + pb + j] = v[q][j];
     }
-    // stage 2
-    exchange<double, E>(lds_d, parity, NT, l, active, hm, xs, hl2, hl1, hr1, hr2);
-    if (active) {
-      build(xs);
-      if (xs64) store_blk(t, 1, xs);
-      tendency<E>(xe, F, k);
+    sync();
+    if (sub_) {
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
-        acc[j] += 2.0 * k[j];
-        xs[j] = x[j] + (0.5 * h) * k[j];
-      }
-    }
-    // stage 3
-    exchange<double, E>(lds_d, parity, NT, l, active, hm, xs, hl2, hl1, hr1, hr2);
-    if (active) {
-      build(xs);
-      if (xs64) store_blk(t, 2, xs);
-      tendency<E>(xe, F, k);
+      for (int q = 0; q < M; ++q) {
+        double r[E];
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
-        acc[j] += 2.0 * k[j];
-        xs[j] = x[j] + h * k[j];
-      }
-    }
-    // stage 4
-    exchange<double, E>(lds_d, parity, NT, l, active, hm, xs, hl2, hl1, hr1, hr2);
-    if (active) {
-      build(xs);
-      if (xs64) store_blk(t, 3, xs);
-      tendency<E>(xe, F, k);
+        for (int j = 0; j < E; ++j) r[j] = b[q * nbuf + sb + j];
 #pragma unroll
-      for (int j = 0; j < E; ++j) {
-        acc[j] += k[j];
-        x[j] = x[j] + (h / 6.0) * acc[j];
-      }
-    }
-  }
-  if (xu && active) sample_obs<E>(mv, nsteps, l, x, xu);
-  if (xs64) {
-    exchange<double, E>(lds_d, parity, NT, l, active, hm, x, hl2, hl1, hr1, hr2);
-    if (active) store_blk(nsteps, 0, x);
-  }
-  if (xout && active) {
-#pragma unroll
-    for (int j = 0; j < E; ++j) gptr(xout)[a + j] = x[j];
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Member TL/AD sweep (device function shared by the batched kernel and CG).
-// ---------------------------------------------------------------------------
-
-// FULL: every thread of the member owns state (n = E * NT), so the activity tests compile
-// away and each RK4 stage is one straight-line block.
-template <typename Real, int E, bool WAVE = false, bool FULL = false>
-struct Member {
-  const ModelView &mv;
-  Real *lds;
-  int l, NT;
-  bool active;
-  HaloMap<E> hm;
-  int parity;
-
-  __device__ Member(const ModelView &m, Real *lds_, int l_)
-      : mv(m), lds(lds_), l(l_), NT(m.NT), active(FULL || l_ < m.A), parity(0) {
-    if (active) hm.init(l, mv.n, NT);
-  }
-
-  // TL of one observed step: f[u] = wgt[u] * dx_i (weighted) or dx_i for observed elements.
-  __device__ __forceinline__ void tl_store(int k, const Real (&dl)[E], Real *__restrict__ f,
-                                           bool weighted) {
-    const int us = mv.ustart[k * NT + l];
-    const unsigned mask = (unsigned)mv.umask[k * NT + l];
-    const Real *wgt = reinterpret_cast<const Real *>(mv.wgt);
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      if ((mask >> j) & 1u) {
-        const int u = us + __popc(mask & ((1u << j) - 1u));
-        f[u] = weighted ? wgt[u] * dl[j] : dl[j];
+        for (int j = 0; j < E; ++j) v[q][j] = sub_ >> j & 1 ? r[j] : v[q][j];
       }
     }
   }
 
-  __device__ __forceinline__ void ad_inject(int k, Real (&lam)[E], const Real *__restrict__ f) {
-    const int us = mv.ustart[k * NT + l];
-    const unsigned mask = (unsigned)mv.umask[k * NT + l];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      if ((mask >> j) & 1u) {
-        const int u = us + __popc(mask & ((1u << j) - 1u));
-        lam[j] += f[u];
-      }
-    }
+  // neighbours' values at the ends of this lane's positions
+  __device__ __forceinline__ void halo(const double (&v)[E], double &hl2, double &hl1, double &hr1,
+                                       double &hr2) const {
+    hl1 = from_below(v[E - 1]);
+    hl2 = from_below(v[E - 2]);
+    hr1 = from_above(v[0]);
+    hr2 = from_above(v[1]);
   }
 
-  // Tangent-linear sweep from dl (in registers) over the whole window, storing forcing.
-  __device__ void tl_sweep(Real (&dl)[E], Real *__restrict__ f, bool weighted, bool skip0) {
-    const Real h = (Real)mv.h;
-    const Real h2 = (Real)(0.5 * mv.h);
-    const Real h6 = (Real)(mv.h / 6.0);
-    Real xe[E + 4], e[E], d[E], acc[E];
-    Real hl2 = 0, hl1 = 0, hr1 = 0, hr2 = 0;
-    const TrajRsrc tr = traj_rsrc<Real>(mv);
+  // Stage block b = 4 t + s of this wave (layout: base_index).
+  __device__ __forceinline__ void load_base(int b, double (&x)[E]) const {
+    const double *p = reinterpret_cast<const double *>(mv.xs) +
+                    ((size_t)b * mv.NW + w) * (size_t)(64 * E);
+#pragma unroll
+    for (int j = 0; j + 1 < E; j += 2) {
+      const d2 v = *reinterpret_cast<const gmem<d2> *>(gptr(p) + j * 64 + 2 * lane);
+      x[j] = v.x, x[j + 1] = v.y;
+    }
+    if (E & 1) x[E - 1] = gptr(p)[(E - 1) * 64 + lane];
+  }
+  // TIGHT: the members' states alone fill the registers, so one stage block is in flight (else
+  // two, or a whole step's), an observed step's tables are loaded when it is reached, and the
+  // halo masks are taken apart anew at each refresh.
+  static constexpr bool TIGHT = E * MB > 17;
+  static constexpr int D = E * MB <= 5 ? 4 : TIGHT ? 1 : 2;
+  __device__ __forceinline__ void extend(const double (&x)[E], double (&xe)[E + 4]) const {
+#pragma unroll
+    for (int j = 0; j < E; ++j) xe[2 + j] = x[j];
+    halo(x, xe[0], xe[1], xe[E + 2], xe[E + 3]);
+  }
+
+  // natural-layout vector <-> the window's positions
+  __device__ __forceinline__ void load_vec(const double *x, double (&v)[E]) const {
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] = gptr(x)[element(el0, j)];
+  }
+  __device__ __forceinline__ void store_vec(double *x, const double (&v)[E]) const {
+    const int e0 = opaque(el0), own_ = opaque(own);
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+      if (own_ >> j & 1) gptr(x)[element(e0, j)] = (double)v[j];
+  }
+
+  // Observed steps. The unique observations of a step's strip are consecutive, so they are
+  // read and written coalesced, 64 at a time, and meet the positions in the wave's staging
+  // row. (Each lane taking its own positions' values, E predicated accesses per member, cost
+  // 0.3 of 0.87 ms at n = 4096, m = 272, T = 100.) ObsAhead holds what the next observed step needs first, loaded before it is reached:
+  // the strip's range, and the window positions (and values of a table) of its first 128.
+  static constexpr int kPre = TIGHT ? 1 : 2;
+  struct ObsAhead {
+    int u0 = 0, u1 = 0, pos[kPre];
+    double val[MB][kPre];
+  };
+  __device__ __forceinline__ int obs_step(int t) const {
+    return __builtin_amdgcn_readfirstlane(gptr(mv.stepk)[t]);
+  }
+  // nsrc tables src + q stride, q < nsrc (0: positions only)
+  __device__ __forceinline__ void obs_ahead(int k, const double *src, int nsrc, size_t stride,
+                                            ObsAhead &o) const {
+    o.u0 = __builtin_amdgcn_readfirstlane(gptr(mv.wstart)[k * mv.NW + w]);
+    o.u1 = __builtin_amdgcn_readfirstlane(gptr(mv.wstart)[k * mv.NW + w + 1]);
+#pragma unroll
+    for (int c = 0; c < kPre; ++c) {
+      const int u = min(o.u0 + c * 64 + lane, mv.U - 1);
+      o.pos[c] = gptr(mv.upos)[u];
+#pragma unroll
+      for (int q = 0; q < MB; ++q)
+        if (q < nsrc) o.val[q][c] = gptr(src + q * stride)[u];
+    }
+  }
+  __device__ __forceinline__ void wave_fence() const {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  // f[u] = wgt[u] v_i, or v_i (wgt null); o holds wgt's values
+  __device__ __forceinline__ void obs_store(const ObsAhead &o, const double (&v)[E], const double *wgt,
+                                            double *f) const {
+#pragma unroll
+    for (int j = 0; j < E; ++j) stg[lane * E + j] = v[j];
+    wave_fence();
+#pragma unroll
+    for (int c = 0; c < kPre; ++c) {
+      const int u = o.u0 + c * 64 + lane;
+      if (u < o.u1) gptr(f)[u] = wgt ? o.val[0][c] * stg[o.pos[c]] : stg[o.pos[c]];
+    }
+    for (int u = o.u0 + kPre * 64 + lane; u < o.u1; u += 64) {
+      const double x = stg[gptr(mv.upos)[u]];
+      gptr(f)[u] = wgt ? gptr(wgt)[u] * x : x;
+    }
+    wave_fence();
+  }
+  // v_i += f[u]; o holds f's values as table q
+  __device__ __forceinline__ void obs_add(const ObsAhead &o, int q, const double *f,
+                                          double (&v)[E]) const {
+#pragma unroll
+    for (int j = 0; j < E; ++j) stg[lane * E + j] = 0;
+    wave_fence();
+#pragma unroll
+    for (int c = 0; c < kPre; ++c)
+      if (o.u0 + c * 64 + lane < o.u1) stg[o.pos[c]] = o.val[q][c];
+    for (int u = o.u0 + kPre * 64 + lane; u < o.u1; u += 64) stg[gptr(mv.upos)[u]] = gptr(f)[u];
+    wave_fence();
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] += stg[lane * E + j];
+    wave_fence();
+  }
+
+  // Tangent-linear sweep over the window from dl (valid on the whole window of positions); at
+  // an observed step f[u] = wgt[u] dl_i (weighted) or dl_i. The base of each stage is loaded D
+  // stages ahead, what an observed step needs one stage ahead.
+  __device__ __forceinline__ void tl_sweep(double (&dl)[MB][E], double *f, bool weighted, bool skip0, int live) {
+    const double h = mv.h, h2 = 0.5 * mv.h, h6 = mv.h / 6.0;
+    const double *wgt = reinterpret_cast<const double *>(mv.wgt);
+    double xb[D][E], xe[E + 4], e[MB][E], d[E], acc[MB][E];
+    double hl2, hl1, hr1, hr2;
+    ObsAhead oa;
+    int since = 0, kn = obs_step(0), kl = gptr(mv.stepk)[min(1, mv.T)];
+    auto fetch = [&](int k) {
+      obs_ahead(k, wgt, weighted ? 1 : 0, 0, oa);
+    };
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_base(i, xb[i]);
+    if (kn >= 0) fetch(kn);
     for (int t = 0; t <= mv.T; ++t) {
-      const int k = mv.stepk[t];
-      if (k >= 0 && active && !(skip0 && t == 0)) tl_store(k, dl, f, weighted);
+      const int k = kn;
+      kn = __builtin_amdgcn_readfirstlane(kl);
+      kl = gptr(mv.stepk)[min(t + 2, mv.T)];
+      if (k >= 0 && !(skip0 && t == 0)) {
+        if (TIGHT) fetch(k);
+#pragma unroll
+        for (int q = 0; q < MB; ++q)
+          if (q < live) obs_store(oa, dl[q], weighted ? wgt : nullptr, f + (size_t)q * mv.U);
+      }
       if (t == mv.T) break;
+      if (since == mv.K) {
+        refresh(dl);
+        since = 0;
+      }
+      ++since;
+      // (loads past the last step: block 4 T and the three after it, whose contents are not
+      // used, lie in the buffer)
       // stage 1
-      load_base_buf<Real, E>(tr, t, 0, l, xe);
-      exchange<Real, E, WAVE>(lds, parity, NT, l, active, hm, dl, hl2, hl1, hr1, hr2);
-      if (active) {
-        tl_jac<Real, E>(xe, dl, hl2, hl1, hr1, d);
+      __builtin_amdgcn_sched_barrier(0);
+      extend(xb[0 % D], xe);
+      if (TIGHT) load_base(4 * t + 0 + D, xb[0 % D]);
+#pragma unroll
+      for (int q = 0; q < MB; ++q) {
+        if (MB > 1) __builtin_amdgcn_sched_barrier(0);
+        halo(dl[q], hl2, hl1, hr1, hr2);
+        tl_jac<E>(xe, dl[q], hl2, hl1, hr1, d);
+        if (!TIGHT && q == MB - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_base(4 * t + 0 + D, xb[0 % D]);
+        }
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          acc[j] = d[j];
-          e[j] = dl[j] + h2 * d[j];
+          acc[q][j] = d[j];
+          e[q][j] = dl[q][j] + h2 * d[j];
         }
       }
       // stage 2
-      load_base_buf<Real, E>(tr, t, 1, l, xe);
-      exchange<Real, E, WAVE>(lds, parity, NT, l, active, hm, e, hl2, hl1, hr1, hr2);
-      if (active) {
-        tl_jac<Real, E>(xe, e, hl2, hl1, hr1, d);
+      __builtin_amdgcn_sched_barrier(0);
+      extend(xb[1 % D], xe);
+      if (TIGHT) load_base(4 * t + 1 + D, xb[1 % D]);
+#pragma unroll
+      for (int q = 0; q < MB; ++q) {
+        if (MB > 1) __builtin_amdgcn_sched_barrier(0);
+        halo(e[q], hl2, hl1, hr1, hr2);
+        tl_jac<E>(xe, e[q], hl2, hl1, hr1, d);
+        if (!TIGHT && q == MB - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_base(4 * t + 1 + D, xb[1 % D]);
+        }
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          acc[j] += (Real)2 * d[j];
-          e[j] = dl[j] + h2 * d[j];
+          acc[q][j] = fma(2, d[j], acc[q][j]);
+          e[q][j] = dl[q][j] + h2 * d[j];
         }
       }
       // stage 3
-      load_base_buf<Real, E>(tr, t, 2, l, xe);
-      exchange<Real, E, WAVE>(lds, parity, NT, l, active, hm, e, hl2, hl1, hr1, hr2);
-      if (active) {
-        tl_jac<Real, E>(xe, e, hl2, hl1, hr1, d);
+      __builtin_amdgcn_sched_barrier(0);
+      extend(xb[2 % D], xe);
+      if (TIGHT) load_base(4 * t + 2 + D, xb[2 % D]);
+#pragma unroll
+      for (int q = 0; q < MB; ++q) {
+        if (MB > 1) __builtin_amdgcn_sched_barrier(0);
+        halo(e[q], hl2, hl1, hr1, hr2);
+        tl_jac<E>(xe, e[q], hl2, hl1, hr1, d);
+        if (!TIGHT && q == MB - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_base(4 * t + 2 + D, xb[2 % D]);
+        }
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          acc[j] += (Real)2 * d[j];
-          e[j] = dl[j] + h * d[j];
+          acc[q][j] = fma(2, d[j], acc[q][j]);
+          e[q][j] = dl[q][j] + h * d[j];
         }
       }
       // stage 4
-      load_base_buf<Real, E>(tr, t, 3, l, xe);
-      exchange<Real, E, WAVE>(lds, parity, NT, l, active, hm, e, hl2, hl1, hr1, hr2);
-      if (active) {
-        tl_jac<Real, E>(xe, e, hl2, hl1, hr1, d);
+      if (!TIGHT && kn >= 0) fetch(kn);
+      __builtin_amdgcn_sched_barrier(0);
+      extend(xb[3 % D], xe);
+      if (TIGHT) load_base(4 * t + 3 + D, xb[3 % D]);
+#pragma unroll
+      for (int q = 0; q < MB; ++q) {
+        if (MB > 1) __builtin_amdgcn_sched_barrier(0);
+        halo(e[q], hl2, hl1, hr1, hr2);
+        tl_jac<E>(xe, e[q], hl2, hl1, hr1, d);
+        if (!TIGHT && q == MB - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_base(4 * t + 3 + D, xb[3 % D]);
+        }
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          acc[j] += d[j];
-          dl[j] = dl[j] + h6 * acc[j];
+          acc[q][j] += d[j];
+          dl[q][j] = dl[q][j] + h6 * acc[q][j];
         }
       }
     }
   }
 
-  // Adjoint sweep over the whole window with forcing f injected at observed steps.
-  __device__ void ad_sweep(Real (&lam)[E], const Real *__restrict__ f, bool skip0, bool init) {
-    const Real h = (Real)mv.h;
-    const Real h2 = (Real)(0.5 * mv.h);
-    const Real h3 = (Real)(mv.h / 3.0);
-    const Real h6 = (Real)(mv.h / 6.0);
-    Real xe[E + 4], lp[E], a[E], s[E];
-    Real hl2 = 0, hl1 = 0, hr1 = 0, hr2 = 0;
-    const TrajRsrc tr = traj_rsrc<Real>(mv);
-    if (!init) {
+  // Adjoint sweep over the window with forcing f injected at observed steps, from lam (valid
+  // on the whole window of positions); loads ahead as in the TL.
+  __device__ __forceinline__ void ad_sweep(double (&lam)[MB][E], const double *f, size_t fstride, bool skip0) {
+    const double h = mv.h, h2 = 0.5 * mv.h, h3 = mv.h / 3.0, h6 = mv.h / 6.0;
+    double xb[D][E], xe[E + 4], lp[MB][E], a[MB][E], s[E];
+    double hl2, hl1, hr1, hr2;
+    ObsAhead oa;
+    int since = 0, kn = obs_step(mv.T), kl = gptr(mv.stepk)[max(mv.T - 1, 0)];
+    auto fetch = [&](int k) {
+      obs_ahead(k, f, MB, fstride, oa);
+    };
+    const int bl = max(4 * mv.T - 1, 3);
 #pragma unroll
-      for (int j = 0; j < E; ++j) lam[j] = 0;
-    }
+    for (int i = 0; i < D; ++i) load_base(bl - i, xb[(3 - i) % D]);
+    if (kn >= 0) fetch(kn);
     for (int t = mv.T; t >= 0; --t) {
-      const int k = mv.stepk[t];
-      if (k >= 0 && active && !(skip0 && t == 0)) ad_inject(k, lam, f);
-      if (t == 0) break;
-      const int ts = t - 1;
-      // adjoint of stage 4 input
-      if (active) {
+      const int k = kn;
+      kn = __builtin_amdgcn_readfirstlane(kl);
+      kl = gptr(mv.stepk)[max(t - 2, 0)];
+      if (k >= 0 && !(skip0 && t == 0)) {
+        if (TIGHT) fetch(k);
 #pragma unroll
-        for (int j = 0; j < E; ++j) {
-          lp[j] = lam[j];
-          a[j] = h6 * lp[j];
-        }
+        for (int q = 0; q < MB; ++q) obs_add(oa, q, f + q * fstride, lam[q]);
+        since = mv.K;  // forced on the owned positions only
       }
-      load_base_buf<Real, E>(tr, ts, 3, l, xe);
-      exchange<Real, E, WAVE>(lds, parity, NT, l, active, hm, a, hl2, hl1, hr1, hr2);
-      if (active) {
-        ad_jac<Real, E>(xe, a, hl1, hr1, hr2, s);
+      if (t == 0) break;
+      if (since == mv.K) {
+        refresh(lam);
+        since = 0;
+      }
+      ++since;
+      const int b0 = 4 * (t - 1);
+      // adjoint of stage 4 input
+#pragma unroll
+      for (int q = 0; q < MB; ++q)
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          lam[j] = lp[j] + s[j];
-          a[j] = h3 * lp[j] + h * s[j];
+          lp[q][j] = lam[q][j];
+          a[q][j] = h6 * lp[q][j];
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      extend(xb[3 % D], xe);
+      if (TIGHT) load_base(max(b0 + 3 - D, 0), xb[3 % D]);
+#pragma unroll
+      for (int q = 0; q < MB; ++q) {
+        if (MB > 1) __builtin_amdgcn_sched_barrier(0);
+        halo(a[q], hl2, hl1, hr1, hr2);
+        ad_jac<E>(xe, a[q], hl1, hr1, hr2, s);
+        if (!TIGHT && q == MB - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_base(max(b0 + 3 - D, 0), xb[3 % D]);
+        }
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+          lam[q][j] = lp[q][j] + s[j];
+          a[q][j] = fma(h, s[j], h3 * lp[q][j]);
         }
       }
       // stage 3
-      load_base_buf<Real, E>(tr, ts, 2, l, xe);
-      exchange<Real, E, WAVE>(lds, parity, NT, l, active, hm, a, hl2, hl1, hr1, hr2);
-      if (active) {
-        ad_jac<Real, E>(xe, a, hl1, hr1, hr2, s);
+      __builtin_amdgcn_sched_barrier(0);
+      extend(xb[2 % D], xe);
+      if (TIGHT) load_base(max(b0 + 2 - D, 0), xb[2 % D]);
+#pragma unroll
+      for (int q = 0; q < MB; ++q) {
+        if (MB > 1) __builtin_amdgcn_sched_barrier(0);
+        halo(a[q], hl2, hl1, hr1, hr2);
+        ad_jac<E>(xe, a[q], hl1, hr1, hr2, s);
+        if (!TIGHT && q == MB - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_base(max(b0 + 2 - D, 0), xb[2 % D]);
+        }
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          lam[j] += s[j];
-          a[j] = h3 * lp[j] + h2 * s[j];
+          lam[q][j] += s[j];
+          a[q][j] = fma(h2, s[j], h3 * lp[q][j]);
         }
       }
       // stage 2
-      load_base_buf<Real, E>(tr, ts, 1, l, xe);
-      exchange<Real, E, WAVE>(lds, parity, NT, l, active, hm, a, hl2, hl1, hr1, hr2);
-      if (active) {
-        ad_jac<Real, E>(xe, a, hl1, hr1, hr2, s);
+      __builtin_amdgcn_sched_barrier(0);
+      extend(xb[1 % D], xe);
+      if (TIGHT) load_base(max(b0 + 1 - D, 0), xb[1 % D]);
+#pragma unroll
+      for (int q = 0; q < MB; ++q) {
+        if (MB > 1) __builtin_amdgcn_sched_barrier(0);
+        halo(a[q], hl2, hl1, hr1, hr2);
+        ad_jac<E>(xe, a[q], hl1, hr1, hr2, s);
+        if (!TIGHT && q == MB - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_base(max(b0 + 1 - D, 0), xb[1 % D]);
+        }
 #pragma unroll
         for (int j = 0; j < E; ++j) {
-          lam[j] += s[j];
-          a[j] = h6 * lp[j] + h2 * s[j];
+          lam[q][j] += s[j];
+          a[q][j] = fma(h2, s[j], h6 * lp[q][j]);
         }
       }
       // stage 1
-      load_base_buf<Real, E>(tr, ts, 0, l, xe);
-      exchange<Real, E, WAVE>(lds, parity, NT, l, active, hm, a, hl2, hl1, hr1, hr2);
-      if (active) {
-        ad_jac<Real, E>(xe, a, hl1, hr1, hr2, s);
+      if (!TIGHT && kn >= 0) fetch(kn);
+      __builtin_amdgcn_sched_barrier(0);
+      extend(xb[0 % D], xe);
+      if (TIGHT) load_base(max(b0 + 0 - D, 0), xb[0 % D]);
 #pragma unroll
-        for (int j = 0; j < E; ++j) lam[j] += s[j];
+      for (int q = 0; q < MB; ++q) {
+        if (MB > 1) __builtin_amdgcn_sched_barrier(0);
+        halo(a[q], hl2, hl1, hr1, hr2);
+        ad_jac<E>(xe, a[q], hl1, hr1, hr2, s);
+        if (!TIGHT && q == MB - 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_base(max(b0 + 0 - D, 0), xb[0 % D]);
+        }
+#pragma unroll
+        for (int j = 0; j < E; ++j) lam[q][j] += s[j];
       }
     }
   }
@@ -626,396 +553,210 @@ struct Member {
   // previous segment's last step); kTladInitLam = the AD starts from dx0 instead of zero;
   // kTladOutState = mode 2 writes the final tangent state into lam0. dx0 and lam0 use the
   // natural layout (double).
-  // FLAGS = false compiles the flag tests out (the single-window hot path, whose register
-  // budget is full at 16 elements per lane).
-  template <bool FLAGS = true>
-  __device__ void run(int mode, const double *__restrict__ dx0, double *__restrict__ lam0,
-                      Real *__restrict__ f, const Real *__restrict__ fsrc) {
-    const int base = FLAGS ? (mode & 7) : mode;
-    const bool skip0 = FLAGS && (mode & kTladSkip0) != 0;
-    const int a = l * E;
-    Real v[E];
+  // MB members from dx0, lam0 and f on, n and U apart, the first `live` of which are stored
+  // (the others repeat the last of those).
+  __device__ __forceinline__ void run(int mode, const double *dx0, double *lam0, double *f,
+                                      const double *fsrc, int live = MB) {
+    const int base = mode & 7;
+    const bool skip0 = (mode & kTladSkip0) != 0;
+    double v[MB][E];
+    auto load = [&]() {
+#pragma unroll
+      for (int q = 0; q < MB; ++q) load_vec(dx0 + (size_t)min(q, live - 1) * mv.n, v[q]);
+    };
+    auto store = [&]() {
+#pragma unroll
+      for (int q = 0; q < MB; ++q)
+        if (q < live) store_vec(lam0 + (size_t)q * mv.n, v[q]);
+    };
     if (base == 0 || base == 2) {
-#pragma unroll
-      for (int j = 0; j < E; ++j) v[j] = active ? (Real)dx0[a + j] : (Real)0;
-      tl_sweep(v, f, base == 0, skip0);
+      load();
+      tl_sweep(v, f, base == 0, skip0, live);
       if (base == 2) {
-        if (FLAGS && (mode & kTladOutState) && active) {
-#pragma unroll
-          for (int j = 0; j < E; ++j) lam0[a + j] = (double)v[j];
-        }
+        if (mode & kTladOutState) store();
         return;
       }
-      // each forcing value is re-read by the thread that stored it; the barrier only
-      // separates the two sweeps' LDS traffic
-      member_sync<WAVE>();
-      ad_sweep(v, f, skip0, false);
+      // each forcing value is re-read by the lane that stored it
+    }
+    if (mode & kTladInitLam) {
+      load();
     } else {
-      const bool init = FLAGS && (mode & kTladInitLam) != 0;
-      if (init) {
 #pragma unroll
-        for (int j = 0; j < E; ++j) v[j] = active ? (Real)dx0[a + j] : (Real)0;
-      }
-      ad_sweep(v, base == 1 ? fsrc : f, skip0, init);
-    }
-    if (active) {
+      for (int q = 0; q < MB; ++q)
 #pragma unroll
-      for (int j = 0; j < E; ++j) lam0[a + j] = (double)v[j];
+        for (int j = 0; j < E; ++j) v[q][j] = 0;
     }
+    // (a member beyond the live ones takes the first one's forcing)
+    ad_sweep(v, base == 1 ? fsrc : f, base == 1 || live < MB ? 0 : (size_t)mv.U, skip0);
+    store();
   }
 };
 
-template <typename Real, int E, bool FLAGS, bool FULL>
-__global__ void __launch_bounds__(E >= 8 ? 512 : 1024)
-    tlad_kernel(ModelView mv, int mode, const double *__restrict__ dx0, double *__restrict__ lam0,
-                Real *__restrict__ f, const Real *__restrict__ fsrc) {
+// ---------------------------------------------------------------------------
+// Nonlinear trajectory, one workgroup per window.
+// ---------------------------------------------------------------------------
+
+// Stage block (t, s) of the window's positions (and its FP32 copy).
+template <int E>
+__device__ __forceinline__ void store_block(const ModelView &mv, double *xs64, int t,
+                                            int s, int w, int lane, const double (&v)[E]) {
+  const size_t base = ((size_t)(t * 4 + s) * mv.NW + w) * (size_t)(64 * E);
+  typedef double d2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+  for (int j = 0; j + 1 < E; j += 2)
+    *reinterpret_cast<gmem<d2> *>(gptr(xs64 + base) + j * 64 + 2 * lane) = d2{v[j], v[j + 1]};
+  if (E & 1) gptr(xs64 + base)[(E - 1) * 64 + lane] = v[E - 1];
+}
+
+// xu != nullptr: no stage blocks; the state at every observed (step, variable) pair u is
+// written to xu[u].
+template <int E>
+__device__ __forceinline__ void trajectory_window(const ModelView &mv, int nsteps,
+                                                  const double *x0, double *xout, double *xs64,
+                                                  double *xu, double *lds,
+                                                  int shard = -1) {
+  Strip<E> S(mv, lds, threadIdx.x);
+  if (S.w >= mv.NW) return;
+  if (shard >= 0 && S.w != shard) xs64 = nullptr;
+  if (shard > 0) xout = nullptr;
+  const double h = mv.h, F = mv.F;
+  double xw[1][E], xs[E], acc[E], k[E], xe[E + 4];
+  double(&x)[E] = xw[0];
+  S.load_vec(x0, x);
+  auto sample = [&](int t) {
+    const int ks = S.obs_step(t);
+    if (ks >= 0) {
+      typename Strip<E>::ObsAhead o;
+      S.obs_ahead(ks, nullptr, 0, 0, o);
+      S.obs_store(o, x, nullptr, xu);
+    }
+  };
+  for (int t = 0; t < nsteps; ++t) {
+    if (xu) sample(t);
+    S.extend(x, xe);
+    if (xs64) store_block<E>(mv, xs64, t, 0, S.w, S.lane, x);
+    tendency<E>(xe, F, k);
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      acc[j] = k[j];
+      xs[j] = x[j] + (0.5 * h) * k[j];
+    }
+    S.extend(xs, xe);
+    if (xs64) store_block<E>(mv, xs64, t, 1, S.w, S.lane, xs);
+    tendency<E>(xe, F, k);
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      acc[j] += 2.0 * k[j];
+      xs[j] = x[j] + (0.5 * h) * k[j];
+    }
+    S.extend(xs, xe);
+    if (xs64) store_block<E>(mv, xs64, t, 2, S.w, S.lane, xs);
+    tendency<E>(xe, F, k);
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      acc[j] += 2.0 * k[j];
+      xs[j] = x[j] + h * k[j];
+    }
+    S.extend(xs, xe);
+    if (xs64) store_block<E>(mv, xs64, t, 3, S.w, S.lane, xs);
+    tendency<E>(xe, F, k);
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      acc[j] += k[j];
+      x[j] = x[j] + (h / 6.0) * acc[j];
+    }
+    S.refresh(xw);
+  }
+  if (xu) sample(nsteps);
+  if (xs64) store_block<E>(mv, xs64, nsteps, 0, S.w, S.lane, x);
+  if (xout) S.store_vec(xout, x);
+}
+
+template <int E, int TH>
+__global__ void __launch_bounds__(TH)
+    trajectory_kernel(ModelView mv, int nsteps, const double *__restrict__ x0,
+                      double *__restrict__ xout, double *__restrict__ xs64,
+                      double *__restrict__ xu) {
+  extern __shared__ double lds_d[];
+  if (xu) {  // one workgroup per initial state
+    x0 += (size_t)blockIdx.x * mv.n;
+    xu += (size_t)blockIdx.x * mv.U;
+  }
+  trajectory_window<E>(mv, nsteps, x0, xout, xs64, xu, lds_d, xs64 ? blockIdx.x : -1);
+}
+
+// One workgroup per problem of a batch (waves beyond a problem's strips leave at once; a
+// problem of one strip needs no barrier).
+__global__ void __launch_bounds__(256)
+    trajectory_batched_kernel(const TrajJob *__restrict__ jobs) {
+  extern __shared__ double lds_d[];
+  const TrajJob J = jobs[blockIdx.x];
+  switch (J.mv.E) {
+    case 3: trajectory_window<3>(J.mv, J.mv.T, J.x0, nullptr, J.xs64, nullptr, lds_d); break;
+    case 5: trajectory_window<5>(J.mv, J.mv.T, J.x0, nullptr, J.xs64, nullptr, lds_d); break;
+    case 9: trajectory_window<9>(J.mv, J.mv.T, J.x0, nullptr, J.xs64, nullptr, lds_d); break;
+    default: trajectory_window<17>(J.mv, J.mv.T, J.x0, nullptr, J.xs64, nullptr, lds_d);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// TL/AD sweeps of a block of members, one workgroup each.
+// ---------------------------------------------------------------------------
+template <int E, int TH, int MB>
+__global__ void __launch_bounds__(TH)
+    tlad_kernel(ModelView mv, int m, int mode, const double *__restrict__ dx0,
+                double *__restrict__ lam0, double *__restrict__ f, const double *__restrict__ fsrc) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  Real *lds = reinterpret_cast<Real *>(lds_raw);
-  const int mem = blockIdx.x;
-  Member<Real, E, false, FULL> M(mv, lds, threadIdx.x);
-  M.template run<FLAGS>(mode, dx0 + (size_t)mem * mv.n, lam0 + (size_t)mem * mv.n,
-                        f + (size_t)mem * (size_t)mv.U, fsrc);
+  const int mem = blockIdx.x * MB;
+  Strip<E, MB> S(mv, reinterpret_cast<double *>(lds_raw), threadIdx.x);
+  S.run(mode, dx0 + (size_t)mem * mv.n, lam0 + (size_t)mem * mv.n,
+        f + (size_t)mem * (size_t)mv.U, fsrc, min(MB, m - mem));
 }
 
 // ---------------------------------------------------------------------------
-// TL/AD sweep with the base states staged through LDS (full members, E = 16, 256 threads per
-// member, two members per workgroup).
-//
-// Every RK4 stage reads one stage block of the stored trajectory. Loading it into registers
-// when the stage starts leaves the L2 latency on each stage's critical path (one member per
-// compute unit is a single wave per SIMD, with nothing else to switch to). Here the first E
-// rows of each block (the lane-interleaved own values; the four halo rows are the
-// neighbours' rows) are copied straight into a ring of four LDS slots with direct-to-LDS
-// loads (buffer_load_dwordx4 ... lds, no VGPRs), three stages before they are read: the TL
-// walks the blocks forward and refills, after each stage's barrier, the slot the previous
-// stage read with the block three ahead; the AD walks them backward the same way. Each wave
-// waits with s_waitcnt vmcnt for its own copies of the block it is about to read, and the
-// stage's halo barrier then covers the other waves' copies. The barriers are plain
-// s_barrier (a __syncthreads fence would wait for every copy in flight), and the LDS
-// pointers of one stage are restrict-qualified so the compiler does not add such a wait
-// either. Two members share the ring and each barrier (their base states are the same), one
-// wave of each per SIMD, so that each SIMD has a second wave to issue while one waits. The
-// arithmetic is that of Member (same order, same results), except that R^{-1} is applied
-// when the AD injects an observed value instead of when the TL stores it (the same product).
+// Persistent TL/AD over a batch of independent problems. Phase 1: each workgroup takes
+// whole-workgroup tiles (members of several strips) from an atomic counter; phase 2: each
+// wave takes tiles of members of one strip from a second counter. The tile lists are in
+// decreasing cost order, so the longest integrations start first and the short ones fill the
+// tail. Every wave leaves once both lists are exhausted.
 // ---------------------------------------------------------------------------
 
-constexpr int kRingSlots = 4;
-constexpr int kRingNT = 256;   // threads per member (n = 16 * 256 = 4096)
-constexpr int kRingMembers = 2;  // members per workgroup, one group of waves each
-
-#define RIOT_LDSP(p) ((__attribute__((address_space(3))) void *)(p))
-
-// Wait until at most `later` fill groups (of K copies each) issued after the wanted one are
-// still in flight (later >= 2 is treated as 2, which only waits longer).
-template <int K>
-__device__ __forceinline__ void ring_wait(int later) {
-  static_assert(K == 2 || K == 4, "fill group size");
-  if (later >= 2) {
-    if constexpr (K == 4) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  } else if (later == 1) {
-    if constexpr (K == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-  } else {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
-}
-
-__device__ __forceinline__ void raw_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-template <typename Real, int E>
-struct MemberRing {
-  static constexpr int NT = kRingNT;
-  static constexpr int WGT = kRingMembers * NT;           // threads per workgroup
-  static constexpr int per = 16 / (int)sizeof(Real);     // Reals per lane per copy
-  static constexpr int K = E * NT / (WGT * per);           // copies per stage block and thread
-  static constexpr int SLOT = E * NT;                      // Reals per slot
-  const ModelView &mv;
-  Real *xch;      // this member's halo exchange, 2 parities x kLdsSlots x NT
-  Real *ring;     // kRingSlots slots of E x NT, shared by the workgroup's members
-  int l, parity;  // l: lane within the member
-  int lm, lp;     // neighbour lanes (periodic)
-  int wv;         // wave index within the workgroup, read into a scalar register
-  unsigned voff;  // this thread's byte offset inside one copy of 16 bytes per thread
-  HaloMap<E> hm;
-  TrajRsrc tr;
-  int blk_bytes;  // bytes per stored stage block, (E + 4) NT sizeof(Real)
-  int nblk;       // 4 T stage blocks per sweep
-  // the observation tables, read-only for the whole launch (kernel arguments declared
-  // __restrict__, so that the uniform step table is read by scalar loads and no read of
-  // them waits on the ring copies in flight)
-  const int *__restrict__ stepk;
-  const int *__restrict__ ustart;
-  const int *__restrict__ umask;
-  const Real *__restrict__ wgt;
-
-  __device__ MemberRing(const ModelView &m, Real *xch_, Real *ring_, int tid,
-                        const int *__restrict__ stepk_, const int *__restrict__ ustart_,
-                        const int *__restrict__ umask_, const Real *__restrict__ wgt_)
-      : mv(m), xch(xch_), ring(ring_), l(tid % NT), parity(0), stepk(stepk_), ustart(ustart_),
-        umask(umask_), wgt(wgt_) {
-    hm.init(l, mv.n, NT);
-    lm = (l + NT - 1) % NT;
-    lp = (l + 1) % NT;
-    wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    voff = (unsigned)tid * 16u;
-    tr = traj_rsrc<Real>(mv);
-    blk_bytes = (E + 4) * NT * (int)sizeof(Real);
-    nblk = 4 * mv.T;
-  }
-
-  // Copy the first E rows (the own values, E x NT) of stage block b into slot F: K copies of
-  // 16 bytes per thread over the whole workgroup, straight into LDS (buffer_load_dwordx4 ...
-  // lds, no VGPR destination).
-  template <int F>
-  __device__ __forceinline__ void fill(int b) {
-    Real *dst = ring + F * SLOT + wv * 64 * per;
-#pragma unroll
-    for (int i = 0; i < K; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(tr.r, RIOT_LDSP(dst + i * WGT * per), 16, voff,
-                                               (unsigned)(b * blk_bytes + i * WGT * 16), 0, 0);
-  }
-
-  // One stage: wait for this stage's block in slot S (`later` = fills issued after it that
-  // may still be in flight), publish the boundary values, barrier, refill slot F with block
-  // `next` (when 0 <= next < nblk; slot F was read one stage earlier), then read the
-  // neighbours' values and the base state from LDS.
-  template <int S, int F>
-  __device__ __forceinline__ void stage_in(int later, int next, const Real (&v)[E], Real &hl2,
-                                           Real &hl1, Real &hr1, Real &hr2, Real (&xe)[E + 4]) {
-    ring_wait<K>(later);
-    stage_io<F>(ring + S * SLOT, xch + parity * kLdsSlots * NT, next, v, hl2, hl1, hr1, hr2, xe);
-    parity ^= 1;
-  }
-
-  template <int F>
-  __device__ __forceinline__ void stage_io(const Real *__restrict__ slot, Real *__restrict__ x,
-                                           int next, const Real (&v)[E], Real &hl2, Real &hl1,
-                                           Real &hr1, Real &hr2, Real (&xe)[E + 4]) {
-    x[0 * NT + l] = v[0];
-    x[1 * NT + l] = v[1];
-    x[2 * NT + l] = v[E - 2];
-    x[3 * NT + l] = v[E - 1];
-    raw_barrier();
-    if (next >= 0 && next < nblk) fill<F>(next);
-    hl2 = x[hm.off[0]];
-    hl1 = x[hm.off[1]];
-    hr1 = x[hm.off[2]];
-    hr2 = x[hm.off[3]];
-#pragma unroll
-    for (int j = 0; j < E; ++j) xe[2 + j] = slot[j * NT + l];
-    xe[0] = slot[(E - 2) * NT + lm];
-    xe[1] = slot[(E - 1) * NT + lm];
-    xe[E + 2] = slot[0 * NT + lp];
-    xe[E + 3] = slot[1 * NT + lp];
-  }
-
-  // The TL stores the raw observed values and the AD applies R^{-1} as it injects them (the
-  // same single product as weighting at the store): the TL then only stores, and never
-  // waits on a load, which would also wait for the ring copies in flight.
-  __device__ __forceinline__ void tl_store(int k, const Real (&dl)[E], Real *__restrict__ f) {
-    const int us = ustart[k * NT + l];
-    const unsigned mask = (unsigned)umask[k * NT + l];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      if ((mask >> j) & 1u) {
-        const int u = us + __popc(mask & ((1u << j) - 1u));
-        f[u] = dl[j];
-      }
-    }
-  }
-
-  __device__ __forceinline__ void ad_inject(int k, Real (&lam)[E], const Real *__restrict__ f) {
-    const int us = ustart[k * NT + l];
-    const unsigned mask = (unsigned)umask[k * NT + l];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      if ((mask >> j) & 1u) {
-        const int u = us + __popc(mask & ((1u << j) - 1u));
-        lam[j] += wgt[u] * f[u];
-      }
-    }
-  }
-
-  // Fill-order bookkeeping. TL: blocks 0, 1, 2 before the sweep, then block b + 3 at stage b,
-  // so fills after block b's: min(2, nblk - 1 - b). AD (blocks nblk-1 .. 0): block b - 3 at
-  // stage b; the first block's fill is the TL's last (nothing after it), every other block
-  // has at least min(2, b) fills after its own.
-  __device__ __forceinline__ int later_tl(int b) const { return min(2, nblk - 1 - b); }
-  __device__ __forceinline__ int later_ad(int b) const { return b == nblk - 1 ? 0 : min(2, b); }
-
-  // TL over the window (R^{-1}-weighted observed values into f), then the AD forced by them.
-  __device__ void run(const double *__restrict__ dx0, double *__restrict__ lam0,
-                      Real *__restrict__ f) {
-    const int a = l * E;
-    const Real h = (Real)mv.h;
-    const Real h2 = (Real)(0.5 * mv.h);
-    const Real h3 = (Real)(mv.h / 3.0);
-    const Real h6 = (Real)(mv.h / 6.0);
-    Real dl[E], e[E], d[E], acc[E], xe[E + 4];
-    Real hl2, hl1, hr1, hr2;
-#pragma unroll
-    for (int j = 0; j < E; ++j) dl[j] = (Real)dx0[a + j];
-    fill<0>(0);
-    if (nblk > 1) fill<1>(1);
-    if (nblk > 2) fill<2>(2);
-    // tangent-linear sweep, blocks 0 .. 4T-1 (block 4t + s in slot s)
-    for (int t = 0; t <= mv.T; ++t) {
-      const int k = stepk[t];
-      if (k >= 0) tl_store(k, dl, f);
-      if (t == mv.T) break;
-      const int b0 = 4 * t;
-      stage_in<0, 3>(later_tl(b0), b0 + 3, dl, hl2, hl1, hr1, hr2, xe);
-      tl_jac<Real, E>(xe, dl, hl2, hl1, hr1, d);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        acc[j] = d[j];
-        e[j] = dl[j] + h2 * d[j];
-      }
-      stage_in<1, 0>(later_tl(b0 + 1), b0 + 4, e, hl2, hl1, hr1, hr2, xe);
-      tl_jac<Real, E>(xe, e, hl2, hl1, hr1, d);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        acc[j] += (Real)2 * d[j];
-        e[j] = dl[j] + h2 * d[j];
-      }
-      stage_in<2, 1>(later_tl(b0 + 2), b0 + 5, e, hl2, hl1, hr1, hr2, xe);
-      tl_jac<Real, E>(xe, e, hl2, hl1, hr1, d);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        acc[j] += (Real)2 * d[j];
-        e[j] = dl[j] + h * d[j];
-      }
-      stage_in<3, 2>(later_tl(b0 + 3), b0 + 6, e, hl2, hl1, hr1, hr2, xe);
-      tl_jac<Real, E>(xe, e, hl2, hl1, hr1, d);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        acc[j] += d[j];
-        dl[j] = dl[j] + h6 * acc[j];
-      }
-    }
-    // adjoint sweep, blocks 4T-1 .. 0 (the last three are still in their slots; the first
-    // stages refill them with the same data, which no stage reads in between)
-    Real (&lam)[E] = dl;
-    Real (&lp_)[E] = e;
-    Real (&aa)[E] = acc;
-    Real (&sv)[E] = d;
-#pragma unroll
-    for (int j = 0; j < E; ++j) lam[j] = 0;
-    for (int t = mv.T; t >= 0; --t) {
-      const int k = stepk[t];
-      if (k >= 0) ad_inject(k, lam, f);
-      if (t == 0) break;
-      const int b3 = 4 * (t - 1) + 3;
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        lp_[j] = lam[j];
-        aa[j] = h6 * lp_[j];
-      }
-      stage_in<3, 0>(later_ad(b3), b3 - 3, aa, hl2, hl1, hr1, hr2, xe);
-      ad_jac<Real, E>(xe, aa, hl1, hr1, hr2, sv);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        lam[j] = lp_[j] + sv[j];
-        aa[j] = h3 * lp_[j] + h * sv[j];
-      }
-      stage_in<2, 3>(later_ad(b3 - 1), b3 - 4, aa, hl2, hl1, hr1, hr2, xe);
-      ad_jac<Real, E>(xe, aa, hl1, hr1, hr2, sv);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        lam[j] += sv[j];
-        aa[j] = h3 * lp_[j] + h2 * sv[j];
-      }
-      stage_in<1, 2>(later_ad(b3 - 2), b3 - 5, aa, hl2, hl1, hr1, hr2, xe);
-      ad_jac<Real, E>(xe, aa, hl1, hr1, hr2, sv);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        lam[j] += sv[j];
-        aa[j] = h6 * lp_[j] + h2 * sv[j];
-      }
-      stage_in<0, 1>(later_ad(b3 - 3), b3 - 6, aa, hl2, hl1, hr1, hr2, xe);
-      ad_jac<Real, E>(xe, aa, hl1, hr1, hr2, sv);
-#pragma unroll
-      for (int j = 0; j < E; ++j) lam[j] += sv[j];
-    }
-    // no copy may still be writing LDS when the workgroup ends
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lam0) {
-#pragma unroll
-      for (int j = 0; j < E; ++j) lam0[a + j] = (double)lam[j];
-    }
-  }
-};
-
-// Two members per workgroup (waves 0-3 and 4-7), one wave of each per SIMD: while one waits
-// on LDS or its dependences the SIMD issues the other's. They share the LDS ring (the base
-// state is the same for every member) and each barrier. An odd last member is shadowed by a
-// copy of the one before it, which computes but writes no result.
-template <typename Real, int E>
-__global__ void __launch_bounds__(kRingMembers * kRingNT)
-    tlad_ring_kernel(ModelView mv, int m, const double *__restrict__ dx0,
-                     double *__restrict__ lam0, Real *__restrict__ f,
-                     const int *__restrict__ stepk, const int *__restrict__ ustart,
-                     const int *__restrict__ umask, const Real *__restrict__ wgt) {
-  __shared__ __align__(16) Real ring[kRingSlots * E * kRingNT];
-  __shared__ __align__(16) Real xch[kRingMembers * 2 * kLdsSlots * kRingNT];
-  const int q = threadIdx.x / kRingNT;
-  const int mem = blockIdx.x * kRingMembers + q;
-  const int src = mem < m ? mem : m - 1;
-  MemberRing<Real, E> M(mv, xch + q * 2 * kLdsSlots * kRingNT, ring, threadIdx.x, stepk, ustart,
-                        umask, wgt);
-  M.run(dx0 + (size_t)src * mv.n, mem < m ? lam0 + (size_t)mem * mv.n : nullptr,
-        f + (size_t)mem * (size_t)mv.U);
-}
-
-// ---------------------------------------------------------------------------
-// Persistent TL/AD over a batch of independent problems (8 elements per lane). Phase 1:
-// each workgroup takes whole-workgroup tiles (one member of a problem with NT > 64) from
-// an atomic counter; phase 2: each wave takes member-per-wave tiles (NT <= 64, the halo
-// exchanged inside the wave without workgroup barriers) from a second counter. The tile
-// lists are in decreasing cost order, so the longest integrations start first and the
-// short ones fill the tail. Every wave leaves once both lists are exhausted.
-// ---------------------------------------------------------------------------
-
-template <typename Real>
-__device__ __forceinline__ void run_tile(int mode, const TladProb &P, int mem, Real *lds, int l,
-                                         bool wave_layout) {
-  constexpr int E = 8;
+__device__ __forceinline__ void run_tile(int mode, const TladProb &P, int mem, double *lds, int tid) {
   const ModelView mv = P.mv;
   const size_t n = (size_t)mv.n, U = (size_t)mv.U;
   const double *dx0 = P.dx0 ? P.dx0 + (size_t)mem * n : nullptr;
   double *lam0 = P.lam0 ? P.lam0 + (size_t)mem * n : nullptr;
-  Real *f = P.f ? reinterpret_cast<Real *>(P.f) + (size_t)mem * U : nullptr;
-  const Real *fsrc = reinterpret_cast<const Real *>(P.fsrc);
-  if (wave_layout) {
-    Member<Real, E, true> M(mv, lds, l);
-    M.run(mode, dx0, lam0, f, fsrc);
-  } else {
-    Member<Real, E, false> M(mv, lds, l);
-    M.run(mode, dx0, lam0, f, fsrc);
+  double *f = P.f ? reinterpret_cast<double *>(P.f) + (size_t)mem * U : nullptr;
+  const double *fsrc = reinterpret_cast<const double *>(P.fsrc);
+  auto go = [&](auto e) {
+    Strip<decltype(e)::value> S(mv, lds, tid);
+    if (S.w < mv.NW) S.run(mode, dx0, lam0, f, fsrc);
+  };
+  switch (mv.E) {
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    case 5: go(std::integral_constant<int, 5>{}); break;
+    case 9: go(std::integral_constant<int, 9>{}); break;
+    default: go(std::integral_constant<int, 17>{});
   }
 }
 
-template <typename Real>
 __global__ void __launch_bounds__(256)
     tlad_persistent_kernel(int mode, const TladProb *__restrict__ probs,
                            const TladTile *__restrict__ wg_tiles, int n_wg,
                            const TladTile *__restrict__ wave_tiles, int n_wave,
                            int *__restrict__ counters, long long *__restrict__ clk) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  Real *lds = reinterpret_cast<Real *>(lds_raw);
+  double *lds = reinterpret_cast<double *>(lds_raw);
   __shared__ int tile_sh;
   for (;;) {
     if (threadIdx.x == 0) tile_sh = atomicAdd(&counters[0], 1);
     __syncthreads();
-    const int t = tile_sh;
+    const int t = __builtin_amdgcn_readfirstlane(tile_sh);
     __syncthreads();  // every thread has its tile before thread 0 fetches the next
     if (t >= n_wg) break;
     const TladTile tile = wg_tiles[t];
     const long long c0 = clk ? wall_clock64() : 0;
-    run_tile<Real>(mode, probs[tile.prob], tile.mem, lds, threadIdx.x, false);
+    run_tile(mode, probs[tile.prob], tile.mem, lds, threadIdx.x);
     __syncthreads();  // the tile's LDS traffic is over before the next tile starts
     if (clk && threadIdx.x == 0) {
       clk[2 * t] = c0;
@@ -1023,15 +764,15 @@ __global__ void __launch_bounds__(256)
     }
   }
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  Real *wlds = lds + (size_t)wave * kLdsSlots * 2 * 64;
+  double *wlds = lds + (size_t)wave * kWaveLds;
   for (;;) {
     int t = 0;
     if (lane == 0) t = atomicAdd(&counters[1], 1);
-    t = __shfl(t, 0, 64);
+    t = __builtin_amdgcn_readfirstlane(t);
     if (t >= n_wave) break;
     const TladTile tile = wave_tiles[t];
     const long long c0 = clk ? wall_clock64() : 0;
-    run_tile<Real>(mode, probs[tile.prob], tile.mem, wlds, lane, true);
+    run_tile(mode, probs[tile.prob], tile.mem, wlds, lane);
     if (clk && lane == 0) {
       clk[2 * (n_wg + t)] = c0;
       clk[2 * (n_wg + t) + 1] = wall_clock64();
@@ -1043,18 +784,23 @@ __global__ void __launch_bounds__(256)
 // Innovation, gradient forcing and cost.
 // ---------------------------------------------------------------------------
 
-template <typename Real>
+// Place of element i's own copy in stage block (t, 0).
+__device__ __forceinline__ size_t stage_index(const ModelView &mv, int t, int i) {
+  const int w = i / mv.own, q = i - w * mv.own + mv.HL, l = q / mv.E;
+  return ((size_t)(t * 4) * mv.NW + w) * (size_t)(64 * mv.E) + base_index(mv.E, q - l * mv.E, l);
+}
+
 __global__ void innovation_kernel(ModelView mv, const double *__restrict__ xs64, int U,
                                   const int *__restrict__ obs_step, const int *__restrict__ obs_idx,
                                   const double *__restrict__ y, const double *__restrict__ rinv,
                                   const int *__restrict__ u_optr, const int *__restrict__ u_olist,
-                                  double *__restrict__ d, Real *__restrict__ fgrad,
+                                  double *__restrict__ d, double *__restrict__ fgrad,
                                   const InnovJob *__restrict__ jobs) {
   if (jobs) {  // batched: blockIdx.y selects the problem
     const InnovJob &J = jobs[blockIdx.y];
     mv = J.mv, xs64 = J.xs64, U = J.mv.U, obs_step = J.obs_step, obs_idx = J.obs_idx, y = J.y;
     rinv = J.rinv, u_optr = J.u_optr, u_olist = J.u_olist, d = J.d;
-    fgrad = reinterpret_cast<Real *>(J.fgrad);
+    fgrad = reinterpret_cast<double *>(J.fgrad);
   }
   const int u = blockIdx.x * blockDim.x + threadIdx.x;
   if (u >= U) return;
@@ -1063,13 +809,12 @@ __global__ void innovation_kernel(ModelView mv, const double *__restrict__ xs64,
     const int o = u_olist[q];
     const int t = obs_step[o];
     const int i = obs_idx[o];
-    const int l = i / mv.E, j = i - l * mv.E;
-    const double xv = xs64[(size_t)(t * 4) * (size_t)(mv.E + 4) * mv.NT + (size_t)j * mv.NT + l];
+    const double xv = xs64[stage_index(mv, t, i)];
     const double dv = y[o] - xv;
     d[o] = dv;
     acc += rinv[o] * dv;
   }
-  fgrad[u] = (Real)acc;
+  fgrad[u] = acc;
 }
 
 // Observed values of a stored window segment: out[o] = x_t[i] for the observations whose
@@ -1082,8 +827,7 @@ __global__ void obs_value_kernel(ModelView mv, const double *__restrict__ xs64, 
   const int t = obs_step[o];
   if (t < lo || t > lo + mv.T || (t == lo && !include_lo)) return;
   const int i = obs_idx[o];
-  const int l = i / mv.E, j = i - l * mv.E;
-  out[o] = xs64[(size_t)((t - lo) * 4) * (size_t)(mv.E + 4) * mv.NT + (size_t)j * mv.NT + l];
+  out[o] = xs64[stage_index(mv, t - lo, i)];
 }
 
 // Z[o, j] = f_j[u(o)] : raw TL values back in the caller's observation order, multiplied by
@@ -1143,20 +887,6 @@ __global__ void psas_scale_kernel(int nobs, const double *__restrict__ rinv,
   dw[o] = -sqrt(rinv[o]) * t[o];
 }
 
-__device__ double block_sum(double v, double *red) {
-  // wave reduction then cross-wave through LDS, fixed order
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) red[wv] = v;
-  __syncthreads();
-  double s = 0.0;
-  const int nw = (blockDim.x + 63) >> 6;
-  for (int k = 0; k < nw; ++k) s += red[k];
-  __syncthreads();
-  return s;
-}
-
 __global__ void __launch_bounds__(1024)
     cost_kernel(int n, const double *__restrict__ v, int nobs, const double *__restrict__ d,
                 const double *__restrict__ rinv, double *__restrict__ out) {
@@ -1173,42 +903,6 @@ __global__ void __launch_bounds__(1024)
 // ---------------------------------------------------------------------------
 // L (symmetric circulant, half-kernel taps) applied to columns.
 // ---------------------------------------------------------------------------
-
-// Workgroup-cooperative L x for one column; ext must hold n + 2w doubles of LDS
-// (or be nullptr to read x from global memory with modular indexing).
-__device__ void apply_L_column(int n, int w, const double *__restrict__ taps,
-                               const double *__restrict__ x, double *__restrict__ y,
-                               const double *__restrict__ z, int mode, double *ext) {
-  if (ext) {
-    for (int k = threadIdx.x; k < n + 2 * w; k += blockDim.x) {
-      int src = (k - w) % n;
-      if (src < 0) src += n;
-      ext[k] = x[src];
-    }
-    __syncthreads();
-  }
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    double acc;
-    if (ext) {
-      acc = taps[0] * ext[i + w];
-      for (int dd = 1; dd <= w; ++dd) acc += taps[dd] * (ext[i + w + dd] + ext[i + w - dd]);
-    } else {
-      acc = taps[0] * x[i];
-      for (int dd = 1; dd <= w; ++dd) {
-        int ip = (i + dd) % n;
-        int im = (i - dd) % n;
-        if (im < 0) im += n;
-        acc += taps[dd] * (x[ip] + x[im]);
-      }
-    }
-    if (mode == 1)
-      acc += z[i];
-    else if (mode == 2)
-      acc = (z ? z[i] : 0.0) - acc;
-    y[i] = acc;
-  }
-  __syncthreads();
-}
 
 __global__ void __launch_bounds__(256)
     apply_L_kernel(int n, int w, const double *__restrict__ taps, const double *__restrict__ X,
@@ -1277,19 +971,19 @@ __global__ void __launch_bounds__(256)
 // Conjugate gradients: one workgroup, all iterations in one launch.
 // ---------------------------------------------------------------------------
 
-template <typename Real, int E>
-__global__ void __launch_bounds__(E >= 8 ? 512 : 1024)
+template <int E, int TH>
+__global__ void __launch_bounds__(TH)
     cg_kernel(ModelView mv, int w, const double *__restrict__ taps, const double *__restrict__ g,
               int iters, double rtol, double *__restrict__ x, double *__restrict__ iterates,
-              double *__restrict__ vs, Real *__restrict__ f, int *__restrict__ used,
+              double *__restrict__ vs, double *__restrict__ f, int *__restrict__ used,
               int ext_off_bytes, int use_lds_ext) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ double red[16];
-  Real *lds = reinterpret_cast<Real *>(lds_raw);
+  double *lds = reinterpret_cast<double *>(lds_raw);
   double *ext = use_lds_ext ? reinterpret_cast<double *>(lds_raw + ext_off_bytes) : nullptr;
   const int n = mv.n;
   double *r = vs, *p = vs + n, *q = vs + 2 * n, *tmp = vs + 3 * n, *lam = vs + 4 * n;
-  Member<Real, E> M(mv, lds, threadIdx.x);
+  Strip<E> M(mv, lds, threadIdx.x);
 
   double rr_part = 0.0;
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
@@ -1305,7 +999,7 @@ __global__ void __launch_bounds__(E >= 8 ? 512 : 1024)
   for (; it < iters; ++it) {
     // q = (I + A) p = p + L^T G^T R^{-1} G L p
     apply_L_column(n, w, taps, p, tmp, nullptr, 0, ext);
-    M.template run<false>(0, tmp, lam, f, nullptr);
+    M.run(0, tmp, lam, f, nullptr);
     __syncthreads();
     apply_L_column(n, w, taps, lam, q, p, 1, ext);
     double pq_part = 0.0;
@@ -1442,57 +1136,59 @@ __global__ void cand_select_kernel(int n, int nc, const double *__restrict__ J,
 // Launchers
 // ---------------------------------------------------------------------------
 
-// The ring-staged TL/AD kernel serves the full-member E = 16 products unless RIOT_TLAD_RING=0
-// (kept for comparison runs against the register-loading kernel).
-static bool tlad_ring_enabled() {
-  static const bool on = [] {
-    const char *e = getenv("RIOT_TLAD_RING");
-    return !(e && e[0] == '0');
-  }();
-  return on;
-}
 
-#define RIOT_DISPATCH_E(E_, CALL) \
-  switch (E_) {                   \
-    case 1: {                     \
-      constexpr int EE = 1;       \
-      CALL;                       \
-    } break;                      \
-    case 2: {                     \
-      constexpr int EE = 2;       \
-      CALL;                       \
-    } break;                      \
-    case 4: {                     \
-      constexpr int EE = 4;       \
-      CALL;                       \
-    } break;                      \
-    case 8: {                     \
-      constexpr int EE = 8;       \
-      CALL;                       \
-    } break;                      \
-    case 16: {                    \
-      constexpr int EE = 16;      \
-      CALL;                       \
-    } break;                      \
-    default:                      \
-      return hipErrorInvalidValue; \
+// Strip widths and the largest workgroups that strip_layout uses them with.
+#define RIOT_DISPATCH_E(MV, CALL)                  \
+  switch ((MV).E) {                                \
+    case 2: {                                      \
+      constexpr int EE = 2, TH = 256;              \
+      CALL;                                        \
+    } break;                                       \
+    case 3: {                                      \
+      constexpr int EE = 3, TH = 256;              \
+      CALL;                                        \
+    } break;                                       \
+    case 5: {                                      \
+      constexpr int EE = 5, TH = 512;              \
+      CALL;                                        \
+    } break;                                       \
+    case 9: {                                      \
+      constexpr int EE = 9, TH = 512;              \
+      CALL;                                        \
+    } break;                                       \
+    case 17: { /* a problem of a batch */          \
+      constexpr int EE = 17, TH = 256;             \
+      CALL;                                        \
+    } break;                                       \
+    default: return hipErrorInvalidValue;          \
   }
+
+// LDS elements of a workgroup of mb members: halo buffers (both parities) and staging rows
+static size_t strip_lds(const ModelView &mv, int mb) {
+  const int ew = mv.HL + mv.HR;
+  const size_t halo = mv.n < ew + mv.E ? mv.n : mv.NW * (ew + 4 * mv.E);
+  return 2 * mb * halo + (size_t)mv.NW * 64 * mv.E;
+}
 
 hipError_t launch_trajectory(const ModelView &mv, int nsteps, const double *x0, double *xout,
                              double *xs64, float *xs32, hipStream_t st) {
-  const size_t lds = (size_t)kLdsSlots * 2 * mv.NT * sizeof(double);
-  RIOT_DISPATCH_E(mv.E, hipLaunchKernelGGL(trajectory_kernel<EE>, dim3(1), dim3(mv.NT), lds, st,
-                                           mv, nsteps, x0, xout, xs64, xs32, nullptr, nullptr));
+  if (mv.NT) return lanes_trajectory(mv, nsteps, x0, xout, xs64, xs32, st);
+  const size_t lds = strip_lds(mv, 1) * sizeof(double);
+  // One compute unit stores 64 bytes a clock, less than a trajectory of many strips produces, so
+  // NW workgroups each run the whole trajectory and store one strip's stage blocks.
+  const dim3 grid(xs64 ? mv.NW : 1);
+  RIOT_DISPATCH_E(mv, hipLaunchKernelGGL((trajectory_kernel<EE, TH>), grid, dim3(64 * mv.NW), lds,
+                                         st, mv, nsteps, x0, xout, xs64, nullptr));
   return hipGetLastError();
 }
 
 hipError_t launch_window_obs(const ModelView &mv, int nstates, const double *x0, double *xu,
                              hipStream_t st) {
   if (nstates <= 0) return hipSuccess;
-  const size_t lds = (size_t)kLdsSlots * 2 * mv.NT * sizeof(double);
-  RIOT_DISPATCH_E(mv.E, hipLaunchKernelGGL(trajectory_kernel<EE>, dim3(nstates), dim3(mv.NT), lds,
-                                           st, mv, mv.T, x0, nullptr, nullptr, nullptr, nullptr,
-                                           xu));
+  if (mv.NT) return lanes_window_obs(mv, nstates, x0, xu, st);
+  const size_t lds = strip_lds(mv, 1) * sizeof(double);
+  RIOT_DISPATCH_E(mv, hipLaunchKernelGGL((trajectory_kernel<EE, TH>), dim3(nstates),
+                                         dim3(64 * mv.NW), lds, st, mv, mv.T, x0, nullptr, nullptr, xu));
   return hipGetLastError();
 }
 
@@ -1525,16 +1221,14 @@ hipError_t launch_innovation(const ModelView &mv, const double *xs64, int nobs, 
                              bool fp32, hipStream_t st) {
   (void)nobs;
   if (mv.U == 0) return hipSuccess;
+  if (mv.NT)
+    return lanes_innovation(mv, xs64, obs_step, obs_idx, y, rinv, u_optr, u_olist, d, fgrad, fp32,
+                            st);
   const int bs = 256;
   const int grid = (mv.U + bs - 1) / bs;
-  if (fp32)
-    hipLaunchKernelGGL(innovation_kernel<float>, dim3(grid), dim3(bs), 0, st, mv, xs64, mv.U,
-                       obs_step, obs_idx, y, rinv, u_optr, u_olist, d,
-                       reinterpret_cast<float *>(fgrad), nullptr);
-  else
-    hipLaunchKernelGGL(innovation_kernel<double>, dim3(grid), dim3(bs), 0, st, mv, xs64, mv.U,
-                       obs_step, obs_idx, y, rinv, u_optr, u_olist, d,
-                       reinterpret_cast<double *>(fgrad), nullptr);
+  hipLaunchKernelGGL(innovation_kernel, dim3(grid), dim3(bs), 0, st, mv, xs64, mv.U, obs_step,
+                     obs_idx, y, rinv, u_optr, u_olist, d, reinterpret_cast<double *>(fgrad),
+                     nullptr);
   return hipGetLastError();
 }
 
@@ -1547,45 +1241,21 @@ hipError_t launch_cost(int n, const double *v, int nobs, const double *d, const 
 hipError_t launch_tlad(const ModelView &mv, int m, int mode, const double *dx0, double *lam0,
                        void *f, const void *fsrc, bool fp32, hipStream_t st) {
   if (m <= 0) return hipSuccess;
-  const bool flags = (mode & ~7) != 0;
-  const bool full = mv.A == mv.NT;
-  if (mode == 0 && full && mv.E == 16 && mv.NT == kRingNT && mv.T >= 1 && tlad_ring_enabled()) {
-    const dim3 grid((m + kRingMembers - 1) / kRingMembers), block(kRingMembers * kRingNT);
-    if (fp32)
-      hipLaunchKernelGGL((tlad_ring_kernel<float, 16>), grid, block, 0, st, mv, m, dx0, lam0,
-                         reinterpret_cast<float *>(f), mv.stepk, mv.ustart, mv.umask,
-                         reinterpret_cast<const float *>(mv.wgt));
-    else
-      hipLaunchKernelGGL((tlad_ring_kernel<double, 16>), grid, block, 0, st, mv, m, dx0, lam0,
-                         reinterpret_cast<double *>(f), mv.stepk, mv.ustart, mv.umask,
-                         reinterpret_cast<const double *>(mv.wgt));
+  if (mv.NT) return lanes_tlad(mv, m, mode, dx0, lam0, f, fsrc, fp32, st);
+  // Two members per workgroup where each compute unit would otherwise run its workgroups one
+  // after the other (a workgroup of 9 positions per lane fills one: eight waves of 256
+  // registers): they share the base loads and hide each other's latencies. n = 4096, T = 100:
+  // m = 272 at two each 0.58 ms, one each 2 x 0.43 ms.
+  if (mv.E == 9 && m > mv.cus) {
+    hipLaunchKernelGGL((tlad_kernel<9, 512, 2>), dim3((m + 1) / 2), dim3(64 * mv.NW),
+                       strip_lds(mv, 2) * sizeof(double), st, mv, m, mode, dx0, lam0,
+                       reinterpret_cast<double *>(f), reinterpret_cast<const double *>(fsrc));
     return hipGetLastError();
   }
-#define RIOT_TLAD(R_, F_, U_)                                                                   \
-  RIOT_DISPATCH_E(mv.E, hipLaunchKernelGGL((tlad_kernel<R_, EE, F_, U_>), dim3(m), dim3(mv.NT), \
-                                           lds, st, mv, mode, dx0, lam0,                        \
-                                           reinterpret_cast<R_ *>(f),                           \
-                                           reinterpret_cast<const R_ *>(fsrc)))
-  if (fp32) {
-    const size_t lds = (size_t)kLdsSlots * 2 * mv.NT * sizeof(float);
-    if (flags) {
-      RIOT_TLAD(float, true, false);
-    } else if (full) {
-      RIOT_TLAD(float, false, true);
-    } else {
-      RIOT_TLAD(float, false, false);
-    }
-  } else {
-    const size_t lds = (size_t)kLdsSlots * 2 * mv.NT * sizeof(double);
-    if (flags) {
-      RIOT_TLAD(double, true, false);
-    } else if (full) {
-      RIOT_TLAD(double, false, true);
-    } else {
-      RIOT_TLAD(double, false, false);
-    }
-  }
-#undef RIOT_TLAD
+  RIOT_DISPATCH_E(mv, hipLaunchKernelGGL((tlad_kernel<EE, TH, 1>), dim3(m), dim3(64 * mv.NW),
+                                         strip_lds(mv, 1) * sizeof(double), st, mv, m, mode, dx0,
+                                         lam0, reinterpret_cast<double *>(f),
+                                         reinterpret_cast<const double *>(fsrc)));
   return hipGetLastError();
 }
 
@@ -1593,6 +1263,8 @@ hipError_t launch_obs_value(const ModelView &mv, const double *xs64, int nobs, c
                             const int *obs_idx, int lo, bool include_lo, double *out,
                             hipStream_t st) {
   if (nobs <= 0) return hipSuccess;
+  if (mv.NT)
+    return lanes_obs_value(mv, xs64, nobs, obs_step, obs_idx, lo, include_lo, out, st);
   hipLaunchKernelGGL(obs_value_kernel, dim3((nobs + 255) / 256), dim3(256), 0, st, mv, xs64, nobs,
                      obs_step, obs_idx, lo, include_lo ? 1 : 0, out);
   return hipGetLastError();
@@ -1671,22 +1343,17 @@ hipError_t launch_apply_L(int n, int w, const double *taps, int m, const double 
 hipError_t launch_cg(const ModelView &mv, int w, const double *taps, const double *g, int iters,
                      double rtol, double *x, double *iterates, double *vec_scratch, void *f,
                      int *used, bool fp32, hipStream_t st) {
-  const size_t xb = (size_t)kLdsSlots * 2 * mv.NT * (fp32 ? sizeof(float) : sizeof(double));
+  if (mv.NT)
+    return lanes_cg(mv, w, taps, g, iters, rtol, x, iterates, vec_scratch, f, used, fp32, st);
+  const size_t xb = strip_lds(mv, 1) * sizeof(double);
   const size_t ext_off = (xb + 255) / 256 * 256;
   const size_t ext_bytes = (size_t)(mv.n + 2 * w) * sizeof(double);
   const int use_ext = (ext_off + ext_bytes) <= 60 * 1024 ? 1 : 0;
   const size_t lds = use_ext ? ext_off + ext_bytes : xb;
-  if (fp32) {
-    RIOT_DISPATCH_E(mv.E, hipLaunchKernelGGL((cg_kernel<float, EE>), dim3(1), dim3(mv.NT), lds, st,
-                                             mv, w, taps, g, iters, rtol, x, iterates, vec_scratch,
-                                             reinterpret_cast<float *>(f), used, (int)ext_off,
-                                             use_ext));
-  } else {
-    RIOT_DISPATCH_E(mv.E, hipLaunchKernelGGL((cg_kernel<double, EE>), dim3(1), dim3(mv.NT), lds,
-                                             st, mv, w, taps, g, iters, rtol, x, iterates,
-                                             vec_scratch, reinterpret_cast<double *>(f), used,
-                                             (int)ext_off, use_ext));
-  }
+  RIOT_DISPATCH_E(mv, hipLaunchKernelGGL((cg_kernel<EE, TH>), dim3(1), dim3(64 * mv.NW), lds, st,
+                                         mv, w, taps, g, iters, rtol, x, iterates, vec_scratch,
+                                         reinterpret_cast<double *>(f), used, (int)ext_off,
+                                         use_ext));
   return hipGetLastError();
 }
 
@@ -1703,31 +1370,30 @@ hipError_t launch_philox_normal(long long total, uint64_t seed, uint64_t stream,
 
 
 // ---------------------------------------------------------------------------
-// Batched launchers (E = 8, workgroups of 256 threads, NT <= 256 per problem)
+// Batched launchers (workgroups of 256 threads, one or four strips per problem)
 // ---------------------------------------------------------------------------
 
 constexpr int kBatchThreads = 256;
 
-hipError_t launch_trajectory_batched(int nprob, const TrajJob *jobs, hipStream_t st) {
+hipError_t launch_trajectory_batched(int nprob, const TrajJob *jobs, bool fp32, hipStream_t st) {
   if (nprob <= 0) return hipSuccess;
-  const size_t lds = (size_t)kLdsSlots * 2 * kBatchThreads * sizeof(double);
-  hipLaunchKernelGGL(trajectory_kernel<8>, dim3(nprob), dim3(kBatchThreads), lds, st, ModelView{}, 0,
-                     nullptr, nullptr, nullptr, nullptr, jobs, nullptr);
+  if (fp32) return lanes_trajectory_batched(nprob, jobs, st);
+  hipLaunchKernelGGL(trajectory_batched_kernel, dim3(nprob), dim3(kBatchThreads),
+                     (kBatchThreads / 64) * kWaveLds * sizeof(double), st, jobs);
   return hipGetLastError();
 }
 
 hipError_t launch_innovation_batched(int nprob, int maxU, const InnovJob *jobs, bool fp32,
                                      hipStream_t st) {
   if (nprob <= 0 || maxU <= 0) return hipSuccess;
-  const dim3 grid((maxU + 255) / 256, nprob);
-  if (fp32)
-    hipLaunchKernelGGL(innovation_kernel<float>, grid, dim3(256), 0, st, ModelView{}, nullptr, 0,
-                       nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, jobs);
-  else
-    hipLaunchKernelGGL(innovation_kernel<double>, grid, dim3(256), 0, st, ModelView{}, nullptr, 0,
-                       nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, jobs);
+  if (fp32) return lanes_innovation_batched(nprob, maxU, jobs, st);
+  hipLaunchKernelGGL(innovation_kernel, dim3((maxU + 255) / 256, nprob), dim3(256), 0, st,
+                     ModelView{}, nullptr, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                     nullptr, nullptr, jobs);
   return hipGetLastError();
 }
+
+constexpr size_t kPersistentLds = (size_t)(kBatchThreads / 64) * kWaveLds * sizeof(double);
 
 hipError_t launch_tlad_persistent(int nwg, int mode, const TladProb *probs, const TladTile *wg_tiles,
                                   int n_wg, const TladTile *wave_tiles, int n_wave, int *counters,
@@ -1735,26 +1401,19 @@ hipError_t launch_tlad_persistent(int nwg, int mode, const TladProb *probs, cons
   if (nwg <= 0 || (n_wg <= 0 && n_wave <= 0)) return hipSuccess;
   hipError_t e = launch_zero_ints(counters, 2, st);
   if (e != hipSuccess) return e;
-  const size_t lds =
-      (size_t)kLdsSlots * 2 * kBatchThreads * (fp32 ? sizeof(float) : sizeof(double));
   if (fp32)
-    hipLaunchKernelGGL(tlad_persistent_kernel<float>, dim3(nwg), dim3(kBatchThreads), lds, st, mode,
-                       probs, wg_tiles, n_wg, wave_tiles, n_wave, counters, clk);
-  else
-    hipLaunchKernelGGL(tlad_persistent_kernel<double>, dim3(nwg), dim3(kBatchThreads), lds, st,
-                       mode, probs, wg_tiles, n_wg, wave_tiles, n_wave, counters, clk);
+    return lanes_tlad_persistent(nwg, mode, probs, wg_tiles, n_wg, wave_tiles, n_wave, counters, st,
+                                 clk);
+  hipLaunchKernelGGL(tlad_persistent_kernel, dim3(nwg), dim3(kBatchThreads), kPersistentLds, st,
+                     mode, probs, wg_tiles, n_wg, wave_tiles, n_wave, counters, clk);
   return hipGetLastError();
 }
 
 int tlad_persistent_resident_per_cu(bool fp32) {
+  if (fp32) return lanes_persistent_resident_per_cu();
   int nb = 0;
-  const size_t lds =
-      (size_t)kLdsSlots * 2 * kBatchThreads * (fp32 ? sizeof(float) : sizeof(double));
-  const hipError_t e =
-      fp32 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, tlad_persistent_kernel<float>,
-                                                          kBatchThreads, lds)
-           : hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, tlad_persistent_kernel<double>,
-                                                          kBatchThreads, lds);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      &nb, tlad_persistent_kernel, kBatchThreads, kPersistentLds);
   return e == hipSuccess ? nb : 0;
 }
 

@@ -48,8 +48,8 @@ struct Carver {
 
 int launch_bound_for(int E) { return E >= 8 ? 512 : 1024; }
 
-// Elements per lane: largest E with n % E == 0 and 256 <= n/E <= bound, else
-// largest with n/E >= 64, else 1.
+// Elements per lane of the lane layout: largest E with n % E == 0 and 256 <= n/E <= bound, else
+// largest with n/E >= 64, else 1; 0: the library does not take the size (strips or lanes).
 int choose_E(int n, int requested) {
   const int cands[5] = {16, 8, 4, 2, 1};
   if (requested) {
@@ -65,13 +65,51 @@ int choose_E(int n, int requested) {
   return 0;
 }
 
+// Strips of a member (see l96.hip): the first candidate whose halo lasts three RK4 steps, else
+// the first that works at all. A single problem's members are latency-bound (one stage after
+// the other on one compute unit), so they take many short strips; n <= 141 fits one wave, which
+// needs no barrier. A batch is bound by throughput: one wave per member up to n = 1037, so that
+// members run independently and little is recomputed, and four beyond. E = 0: none fits (more
+// than 4207 elements; the lane layout then).
+struct StripLayout {
+  int E = 0, NW = 0, own = 0, HL = 0, HR = 0, K = 0;
+  int NT = 0, A = 0;  // lane layout: threads and active threads (0: strips)
+};
+StripLayout lane_layout(int n, int requested) {
+  StripLayout s;
+  s.E = choose_E(n, requested);
+  if (!s.E) return s;
+  s.A = n / s.E;
+  s.NT = (s.A + 63) / 64 * 64;
+  return s;
+}
+StripLayout strip_layout(int n, bool batch) {
+  static constexpr int single[][2] = {{2, 1}, {3, 1}, {2, 4}, {3, 4}, {5, 1},
+                                      {5, 4}, {5, 8}, {9, 8}};
+  static constexpr int many[][2] = {{3, 1}, {5, 1}, {9, 1}, {17, 1}, {9, 4}};
+  const int(*cand)[2] = batch ? many : single;
+  const int ncand = batch ? 5 : 8;
+  for (int kmin : {3, 1})
+    for (int c = 0; c < ncand; ++c) {
+      StripLayout s;
+      s.E = cand[c][0], s.NW = cand[c][1];
+      s.own = (n + s.NW - 1) / s.NW;
+      const int last = n - (s.NW - 1) * s.own;
+      for (s.K = 8; s.K >= kmin; --s.K) {
+        s.HL = std::max(8 * s.K, 4 * s.K + 7), s.HR = 8 * s.K + 3;
+        if (s.own + s.HL + s.HR <= 64 * s.E && (s.NW == 1 || last >= s.HL + s.HR + s.E)) return s;
+      }
+    }
+  return StripLayout{};
+}
+
 struct ObsPlan {
   int S = 0, U = 0;
-  std::vector<int> stepk, ustart, umask, u_optr, u_olist, u_of_o;
+  std::vector<int> stepk, wstart, upos, ustart, umask, u_optr, u_olist, u_of_o;
   std::vector<double> wgt;
 };
 
-bool build_obs(const riot_desc &d, int E, int NT, ObsPlan &p) {
+bool build_obs(const riot_desc &d, const StripLayout &sl, ObsPlan &p) {
   const int n = d.n, T = d.nsteps, no = d.nobs;
   std::vector<int> order(no);
   for (int o = 0; o < no; ++o) {
@@ -104,19 +142,26 @@ bool build_obs(const riot_desc &d, int E, int NT, ObsPlan &p) {
   p.u_optr.push_back(no);
   for (int u = 0; u < p.U; ++u)
     if (p.stepk[ustep[u]] < 0) p.stepk[ustep[u]] = p.S++;
-  p.ustart.assign((size_t)std::max(p.S, 1) * NT, 0);
-  p.umask.assign((size_t)std::max(p.S, 1) * NT, 0);
-  std::vector<char> seen((size_t)std::max(p.S, 1) * NT, 0);
-  for (int u = 0; u < p.U; ++u) {
-    const int k = p.stepk[ustep[u]];
-    const int l = uidx[u] / E, j = uidx[u] % E;
-    const size_t s = (size_t)k * NT + l;
-    if (!seen[s]) {
-      seen[s] = 1;
+  if (sl.NT) {
+    p.ustart.assign((size_t)std::max(p.S, 1) * sl.NT, 0);
+    p.umask.assign((size_t)std::max(p.S, 1) * sl.NT, 0);
+    for (int u = p.U - 1; u >= 0; --u) {
+      const size_t s = (size_t)p.stepk[ustep[u]] * sl.NT + uidx[u] / sl.E;
       p.ustart[s] = u;
+      p.umask[s] |= 1 << uidx[u] % sl.E;
     }
-    p.umask[s] |= 1 << j;
+    return true;
   }
+  // (unique observations are sorted by step and element, so by strip within a step)
+  p.wstart.assign((size_t)std::max(p.S, 1) * sl.NW + 1, p.U);
+  p.upos.assign(std::max(p.U, 1), 0);
+  for (int u = p.U - 1; u >= 0; --u) {
+    const int k = p.stepk[ustep[u]], w = uidx[u] / sl.own;
+    p.upos[u] = uidx[u] - w * sl.own + sl.HL;
+    p.wstart[(size_t)k * sl.NW + w] = u;
+  }
+  for (size_t i = p.wstart.size() - 1; i-- > 0;)  // strips without observations: empty ranges
+    p.wstart[i] = std::min(p.wstart[i], p.wstart[i + 1]);
   return true;
 }
 
@@ -125,14 +170,16 @@ bool build_obs(const riot_desc &d, int E, int NT, ObsPlan &p) {
 struct riot_handle {
   riot_desc d{};
   hipStream_t st = nullptr;
-  int E = 0, NT = 0, A = 0, S = 0, U = 0, w = 0;
+  StripLayout sl;
+  bool batch = false;  // laid out for a batch (throughput, not latency)
+  int S = 0, U = 0, w = 0;
   int cus = 256;  // compute units of the device the handle was created on
   bool fp32 = false;
   bool linearized = false;
   double base_diag = 0.0;
   // device regions
   double *taps = nullptr, *brow = nullptr;
-  int *stepk = nullptr, *ustart = nullptr, *umask = nullptr;
+  int *stepk = nullptr, *wstart = nullptr, *upos = nullptr, *ustart = nullptr, *umask = nullptr;
   double *wgt64 = nullptr;
   float *wgt32 = nullptr;
   int *obs_step = nullptr, *obs_idx = nullptr, *u_optr = nullptr, *u_olist = nullptr,
@@ -207,8 +254,13 @@ size_t carve(riot_handle &h, void *base) {
   h.taps = c.take<double>(h.w + 1);
   h.brow = c.take<double>(n);
   h.stepk = c.take<int>(T + 1);
-  h.ustart = c.take<int>((size_t)std::max(h.S, 1) * h.NT);
-  h.umask = c.take<int>((size_t)std::max(h.S, 1) * h.NT);
+  if (h.sl.NT) {
+    h.ustart = c.take<int>((size_t)std::max(h.S, 1) * h.sl.NT);
+    h.umask = c.take<int>((size_t)std::max(h.S, 1) * h.sl.NT);
+  } else {
+    h.wstart = c.take<int>((size_t)std::max(h.S, 1) * h.sl.NW + 1);
+    h.upos = c.take<int>(U1);
+  }
   h.wgt64 = c.take<double>(U1);
   h.wgt32 = h.fp32 ? c.take<float>(U1) : nullptr;
   h.obs_step = c.take<int>(std::max(d.nobs, 1));
@@ -220,7 +272,7 @@ size_t carve(riot_handle &h, void *base) {
   h.rinv = c.take<double>(std::max(d.nobs, 1));
   // the whole window's stage blocks, or one checkpoint segment's
   const int Tst = d.ckpt_stride > 0 ? d.ckpt_stride : T;
-  const size_t blk = (size_t)(Tst + 1) * 4 * stage_block_elems(h.E, h.NT);
+  const size_t blk = (size_t)(Tst + 1) * 4 * stage_block_elems(h.sl.E, h.sl.NW, h.sl.NT);
   h.xs64 = c.take<double>(blk);
   h.xs32 = h.fp32 ? c.take<float>(blk) : nullptr;
   h.fgrad = c.take<char>(U1 * Rs);
@@ -267,13 +319,13 @@ bool desc_valid(const riot_desc *d) {
 bool prepare(riot_handle &h, const riot_desc *d, ObsPlan *plan) {
   h.d = *d;
   h.fp32 = d->prec == RIOT_FP32_TLAD;
-  h.E = choose_E(d->n, d->elems_per_lane);
-  h.A = d->n / h.E;
-  h.NT = (h.A + 63) / 64 * 64;
+  if (!h.fp32) h.sl = strip_layout(d->n, h.batch);
+  if (!h.sl.E) h.sl = lane_layout(d->n, d->elems_per_lane);
+  if (!h.sl.E) return false;
   h.w = d->l_halfwidth;
   ObsPlan local;
   ObsPlan &p = plan ? *plan : local;
-  if (!build_obs(*d, h.E, h.NT, p)) return false;
+  if (!build_obs(*d, h.sl, p)) return false;
   h.S = p.S;
   h.U = p.U;
   return true;
@@ -283,17 +335,18 @@ void fill_view(riot_handle &h) {
   ModelView &mv = h.mv;
   mv.n = h.d.n;
   mv.T = h.d.nsteps;
-  mv.E = h.E;
-  mv.NT = h.NT;
-  mv.A = h.A;
+  mv.E = h.sl.E, mv.NW = h.sl.NW, mv.own = h.sl.own;
+  mv.HL = h.sl.HL, mv.HR = h.sl.HR, mv.K = h.sl.K;
+  mv.NT = h.sl.NT, mv.A = h.sl.A;
+  mv.cus = h.cus;
   mv.h = h.d.dt;
   mv.F = h.d.forcing;
   mv.S = h.S;
   mv.U = h.U;
   mv.xs = h.fp32 ? (const void *)h.xs32 : (const void *)h.xs64;
   mv.stepk = h.stepk;
-  mv.ustart = h.ustart;
-  mv.umask = h.umask;
+  mv.wstart = h.wstart, mv.upos = h.upos;
+  mv.ustart = h.ustart, mv.umask = h.umask;
   mv.wgt = h.fp32 ? (const void *)h.wgt32 : (const void *)h.wgt64;
 }
 
@@ -510,13 +563,19 @@ riot_status hess_apply_impl(riot_handle *h, int m, const double *W, double *Y, i
 
 }  // namespace
 
+// Workspace of one handle, laid out for single calls or for a batch.
+static size_t handle_bytes(const riot_desc *desc, bool batch) {
+  if (!desc_valid(desc)) return 0;
+  riot_handle h;
+  h.batch = batch;
+  if (!prepare(h, desc, nullptr)) return 0;
+  return carve(h, nullptr);
+}
+
 extern "C" {
 
 size_t riot_workspace_bytes(const riot_desc *desc) {
-  if (!desc_valid(desc)) return 0;
-  riot_handle h;
-  if (!prepare(h, desc, nullptr)) return 0;
-  return carve(h, nullptr);
+  return handle_bytes(desc, false);
 }
 
 // Set up a handle in `workspace` (shared by riot_init and the batch): carve, host tables,
@@ -563,6 +622,8 @@ static riot_status init_handle(riot_handle *h, const riot_desc *desc, void *work
   cp(h->taps, d.l_taps, (size_t)(w + 1) * sizeof(double));
   cp(h->brow, brow.data(), (size_t)n * sizeof(double));
   cp(h->stepk, plan.stepk.data(), plan.stepk.size() * sizeof(int));
+  cp(h->wstart, plan.wstart.data(), plan.wstart.size() * sizeof(int));
+  cp(h->upos, plan.upos.data(), plan.upos.size() * sizeof(int));
   cp(h->ustart, plan.ustart.data(), plan.ustart.size() * sizeof(int));
   cp(h->umask, plan.umask.data(), plan.umask.size() * sizeof(int));
   cp(h->wgt64, plan.wgt.data(), plan.wgt.size() * sizeof(double));
@@ -1319,7 +1380,7 @@ struct riot_batch {
   riot::IncJob *inc = nullptr;
   // layout chosen by riot_batch_autotune (or the defaults)
   int nwg = 0;
-  int wave_max_nt = 64;  // problems with NT <= this use member-per-wave tiles (0: none)
+  int wave_max_nt = 64;  // one-strip problems up to this use member-per-wave tiles (0: none)
   uint64_t seed = 0;
   hipGraphExec_t graph = nullptr;
   ~riot_batch() {
@@ -1410,7 +1471,9 @@ riot_status batch_build_tiles(riot_batch &b) {
   std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return cost(a) > cost(c); });
   std::vector<riot::TladTile> gw, gv, hw, hv;
   for (int j : order) {
-    const bool wave = b.hs[j]->NT <= b.wave_max_nt;
+    const StripLayout &sl = b.hs[j]->sl;
+    const bool wave = sl.NT ? sl.NT <= b.wave_max_nt
+                            : sl.NW == 1 && (b.wave_max_nt == 64 || (b.n[j] + 7) / 8 <= b.wave_max_nt);
     (wave ? gv : gw).push_back({j, 0});
     for (int i = 0; i < b.m[j]; ++i) (wave ? hv : hw).push_back({j, i});
   }
@@ -1559,7 +1622,7 @@ riot_status batch_pipeline(riot_batch &b) {
   hipStream_t st = b.st;
   riot_status rs;
   // a1-a2: trajectories, innovations, gradients g = -L G^T R^{-1} d (first outer loop)
-  RIOT_BHIP(riot::launch_trajectory_batched(b.nprob, b.traj, st));
+  RIOT_BHIP(riot::launch_trajectory_batched(b.nprob, b.traj, b.fp32, st));
   RIOT_BHIP(riot::launch_innovation_batched(b.nprob, b.maxU, b.innov, b.fp32, st));
   if ((rs = batch_hvp(b, 1)) != RIOT_OK) return rs;
   RIOT_BHIP(riot::launch_apply_L_batched(b.nprob, 1, b.maxext, b.aL_grad, st));
@@ -1601,7 +1664,7 @@ size_t riot_batch_workspace_bytes(int32_t nprob, const riot_desc *descs) {
     riot_desc d = descs[j];
     d.elems_per_lane = 8;
     if (!batch_desc_ok(d)) return 0;
-    const size_t w = riot_workspace_bytes(&d);
+    const size_t w = handle_bytes(&d, true);
     if (!w) return 0;
     tot += align256(w);
     tn += d.n;
@@ -1646,7 +1709,8 @@ riot_status riot_batch_init(int32_t nprob, const riot_desc *descs, void *workspa
       break;
     }
     b->hs.push_back(h);
-    const size_t w = riot_workspace_bytes(&d);
+    h->batch = true;
+    const size_t w = handle_bytes(&d, true);
     rs = init_handle(h, &d, base + off, w, b->st);
     off += align256(w);
     b->n.push_back(d.n);
@@ -1721,7 +1785,7 @@ riot_status riot_batch_autotune(riot_batch *b, int32_t *workgroups_out,
   if (b->graph) return RIOT_E_STATE;
   // inputs of the timed launches: the current trajectories and deterministic probes
   b->seed = 0x5eedULL;
-  RIOT_BHIP(riot::launch_trajectory_batched(b->nprob, b->traj, b->st));
+  RIOT_BHIP(riot::launch_trajectory_batched(b->nprob, b->traj, b->fp32, b->st));
   RIOT_BHIP(riot::launch_philox_batched(b->nprob, (long long)b->maxn * b->maxm, b->seed, b->philox,
                                         b->st));
   RIOT_BHIP(riot::launch_apply_L_batched(b->nprob, b->maxm, b->maxext, b->aL_in, b->st));

@@ -102,29 +102,39 @@ struct PhiloxJob {
 // ---------------------------------------------------------------------------
 // Lorenz-96 member layout.
 //
-// One probe ("member") of the batched TL/AD integration is owned by one
-// workgroup of NT threads. Active thread l (l < A = n / E) owns the E
-// contiguous state elements a = l*E .. a+E-1 and keeps them in registers.
-// The base trajectory is stored per (step, RK4 stage) as a block of (E + 4)
-// rows of NT values: row j < E holds x[l*E + j] in column l, rows E..E+3 hold
-// the four halo values x[a-2], x[a-1], x[a+E], x[a+E+1] of thread l. Every row
-// is read by a wave as one contiguous, coalesced segment.
+// The state is cut into NW strips of `own` elements, one wave each; a lane holds E consecutive
+// positions of its wave's window of 64 E elements, which starts HL elements before the strip
+// (see l96.hip). The base trajectory is stored per (step, RK4 stage) as NW blocks of E rows of
+// 64 values in pairs of rows, position i E + j of the wave's window in row j and column i, so
+// that a wave reads contiguous segments.
+//
+// A handle whose TL/AD integrations run in FP32, and any of more elements than the strips take
+// (4207), has the lane layout (l96_lanes.hip): one workgroup of NT threads per member, active thread l (l < A = n / E) owning the elements
+// l*E .. l*E+E-1. Its stage blocks are E + 4 rows of NT values: row j < E holds x[l*E + j] in
+// column l, rows E..E+3 the four halo values x[a-2], x[a-1], x[a+E], x[a+E+1] (a = l*E).
 // ---------------------------------------------------------------------------
 
 struct ModelView {
-  int n, T, E, NT, A;   // state size, window steps, elems/lane, threads, active threads
+  int n, T, E, NW;      // state size, window steps, positions per lane, strips (waves)
+  int own, HL, HR, K;   // elements per strip, halo elements, RK4 steps between halo refreshes
+  int NT, A;            // lane layout: threads, active threads (both 0: strips)
+  int cus;              // compute units of the device
   double h, F;          // RK4 step and forcing
   int S, U;             // observed steps, unique observed (step, variable) pairs
-  const void *xs;       // base stage blocks, (T+1)*4 blocks of (E+4)*NT Real
+  const void *xs;       // base stage blocks, (T+1)*4 of stage_block_elems values
   const int *stepk;     // [T+1] observed-step ordinal or -1
-  const int *ustart;    // [S*NT] first unique-obs index of thread l at observed step k
-  const int *umask;     // [S*NT] bit j set when element l*E+j is observed at step k
-  const void *wgt;      // [U] sum of R^{-1} over the observations of each unique pair (Real)
+  const int *wstart;    // [S*NW + 1] first unique-obs index of strip w at observed step k
+  const int *upos;      // [U] window position of each unique observation
+  const int *ustart;    // lane layout: [S*NT] first unique-obs index of thread l at observed step k
+  const int *umask;     // lane layout: [S*NT] bit j set when element l*E+j is observed then
+  const void *wgt;      // [U] sum of R^{-1} over the observations of each unique pair (float in FP32 handles)
 };
 
-inline size_t stage_block_elems(int E, int NT) { return (size_t)(E + 4) * NT; }
+inline size_t stage_block_elems(int E, int NW, int NT) {
+  return NT ? (size_t)(E + 4) * NT : (size_t)E * NW * 64;
+}
 
-// Batched model jobs (E = 8 for every problem of a batch).
+// Batched model jobs.
 struct TrajJob {
   ModelView mv;
   const double *x0;
@@ -164,9 +174,9 @@ struct ApplyLJobE {
 
 // Batched model launches. Persistent TL/AD: `nwg` workgroups of 256 threads first take
 // whole-workgroup tiles (one member per workgroup) from wg_tiles through counters[0],
-// then each wave takes wave tiles (one member per wave, problems with NT <= 64) from
+// then each wave takes wave tiles (one member per wave, problems of one strip) from
 // wave_tiles through counters[1]. Tiles are processed in list order (longest first).
-hipError_t launch_trajectory_batched(int nprob, const TrajJob *jobs, hipStream_t st);
+hipError_t launch_trajectory_batched(int nprob, const TrajJob *jobs, bool fp32, hipStream_t st);
 hipError_t launch_innovation_batched(int nprob, int maxU, const InnovJob *jobs, bool fp32,
                                      hipStream_t st);
 // clk (optional): per tile, start and end of its integration on the device's constant-rate
@@ -215,7 +225,7 @@ hipError_t launch_innovation(const ModelView &mv, const double *xs64, int nobs, 
 hipError_t launch_cost(int n, const double *v, int nobs, const double *d, const double *rinv,
                        double *out, hipStream_t st);
 
-// Flags or-ed into the TL/AD mode (see Member::run): skip step 0 of the window, start the
+// Flags or-ed into the TL/AD mode (see Strip::run): skip step 0 of the window, start the
 // AD from dx0, return the final tangent state of a TL-only sweep.
 constexpr int kTladSkip0 = 8, kTladInitLam = 16, kTladOutState = 32;
 
@@ -223,9 +233,33 @@ constexpr int kTladSkip0 = 8, kTladInitLam = 16, kTladOutState = 32;
 // pass (probe product), 1 = AD only with shared forcing `fsrc` (gradient), 2 = TL only
 // (raw observed values into f), 3 = AD only with each member's own forcing f.
 // dx0 [n x m] natural layout (already multiplied by L); lam0 [n x m] out.
-// f: per-member forcing scratch [m x U] (Real). fp32 selects the Real type.
+// f: per-member forcing scratch [m x U] (float or double: fp32).
 hipError_t launch_tlad(const ModelView &mv, int m, int mode, const double *dx0, double *lam0,
                        void *f, const void *fsrc, bool fp32, hipStream_t st);
+
+// The same launches on the lane layout (l96_lanes.hip), for the launchers of l96.hip.
+hipError_t lanes_trajectory(const ModelView &mv, int nsteps, const double *x0, double *xout,
+                            double *xs64, float *xs32, hipStream_t st);
+hipError_t lanes_window_obs(const ModelView &mv, int nstates, const double *x0, double *xu,
+                            hipStream_t st);
+hipError_t lanes_innovation(const ModelView &mv, const double *xs64, const int *obs_step,
+                            const int *obs_idx, const double *y, const double *rinv,
+                            const int *u_optr, const int *u_olist, double *d, void *fgrad,
+                            bool fp32, hipStream_t st);
+hipError_t lanes_tlad(const ModelView &mv, int m, int mode, const double *dx0, double *lam0,
+                      void *f, const void *fsrc, bool fp32, hipStream_t st);
+hipError_t lanes_obs_value(const ModelView &mv, const double *xs64, int nobs, const int *obs_step,
+                           const int *obs_idx, int lo, bool include_lo, double *out,
+                           hipStream_t st);
+hipError_t lanes_cg(const ModelView &mv, int w, const double *taps, const double *g, int iters,
+                    double rtol, double *x, double *iterates, double *vec_scratch, void *f,
+                    int *used, bool fp32, hipStream_t st);
+hipError_t lanes_trajectory_batched(int nprob, const TrajJob *jobs, hipStream_t st);
+hipError_t lanes_innovation_batched(int nprob, int maxU, const InnovJob *jobs, hipStream_t st);
+hipError_t lanes_tlad_persistent(int nwg, int mode, const TladProb *probs, const TladTile *wg_tiles,
+                                 int n_wg, const TladTile *wave_tiles, int n_wave, int *counters,
+                                 hipStream_t st, long long *clk);
+int lanes_persistent_resident_per_cu();
 
 // Observed values x_t[i] of a stored segment whose step 0 is window step lo (see kernel).
 hipError_t launch_obs_value(const ModelView &mv, const double *xs64, int nobs, const int *obs_step,

@@ -1,0 +1,48 @@
+"""Strips of the Lorenz-96 integrations at the sizes where their layout changes (one, four and
+eight waves, halos longer than the state, a short last strip; beyond 4207 elements the lane
+layout), windows longer and shorter than the steps between two halo refreshes, strips with no,
+few and all positions observed, and the kernel of two members per workgroup with an odd block,
+against the oracle."""
+
+import numpy as np
+import pytest
+
+from oracle import bcov, fourdvar, l96
+from tests._problems import rel, riot_for, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(n, T, seed):
+    """Steps 0 and T, one dense step, one step observed in the first 130 elements only, scattered
+    single observations and duplicates."""
+    rng = np.random.default_rng(seed)
+    x = 8.0 + rng.standard_normal(n)
+    t = [np.full(n, max(T - 1, 0)), np.full(min(n, 130), T // 2), [0, 0, T, T, T]]
+    i = [np.arange(n), np.arange(min(n, 130)), [0, n - 1, n // 2, n // 2, n // 3]]
+    k = rng.integers(5, 40)
+    t.append(rng.integers(0, T + 1, size=k))
+    i.append(rng.integers(0, n, size=k))
+    t, i = np.concatenate(t), np.concatenate(i)
+    y = 8.0 + rng.standard_normal(t.size)
+    return fourdvar.Problem(n, T, 0.01, 8.0, t, i, y, rng.uniform(0.5, 2.0, t.size), x,
+                            bcov.gaussian_taps(2.0, 1.0))
+
+
+@pytest.mark.parametrize("n,T,m", [
+    (4, 3, 2), (5, 20, 3), (61, 9, 2), (62, 9, 2), (77, 17, 1), (78, 17, 1), (93, 6, 2),
+    (94, 6, 2), (141, 7, 2), (142, 17, 2), (211, 9, 2), (212, 4, 2), (213, 13, 1), (308, 7, 2),
+    (309, 9, 3), (564, 5, 2), (565, 9, 2), (1001, 9, 3), (1076, 18, 2), (1080, 15, 2),
+    (2152, 8, 2), (2160, 9, 257), (4096, 17, 2), (4192, 4, 2), (4208, 9, 3), (8192, 9, 2),
+])
+def test_strips_match_oracle(n, T, m):
+    p = _problem(n, T, 10 * n + T)
+    lin = fourdvar.linearize(p, p.xb)
+    r = riot_for(p, m_max=m)
+    # each value is a sum of products of at most 20 steps' rounding errors (T e^(T dt 2) eps)
+    assert rel(to_np(r.forecast(p.xb, T)), l96.forecast(p.xb, T, p.h, p.F)) < 1e-13
+    d, g, J = r.linearize(p.xb)
+    assert rel(to_np(d), lin.d) < 1e-12
+    assert rel(to_np(g), lin.g) < 1e-11
+    W = np.random.default_rng(n).standard_normal((n, m))
+    assert rel(to_np(r.hess_apply(W)), fourdvar.hvp(p, lin, W)) < 1e-11
