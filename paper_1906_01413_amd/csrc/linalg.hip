@@ -2201,12 +2201,75 @@ hipError_t launch_copy_batched(int nprob, long long maxcount, const CopyJob *job
 }
 
 
+namespace {
+
+// C_q = alpha A_q^T B_q + beta C_q of a strided batch with a long contraction and few tiles: one
+// wave per 16 x 16 tile of C, so that four times as many waves as with 32 x 32 tiles share the
+// work of the same chains (an element is summed in the same order, k ascending by fours). Four
+// chunks of 16 k are in flight. The tiles of one product share an XCD (workgroup L runs on XCD
+// L % 8), whose L2 then holds its operands. Bound by the chain: K / 4 matrix instructions of 64
+// clocks. 16 products of 64 x 64 with K = 2048: 55 us, as 64 waves of 32 x 32 169 us.
+__global__ void __launch_bounds__(64)
+    gemm_tn16_kernel(int M, int N, int K, int batch, const double *__restrict__ A, int lda,
+                     long long sA, const double *__restrict__ B, int ldb, long long sB,
+                     double *__restrict__ C, int ldc, long long sC, double alpha, double beta) {
+  const int tm = (M + 15) / 16, tn = (N + 15) / 16;
+  const int L = blockIdx.x, slot = L / kXcds, q = slot / (tm * tn) * kXcds + L % kXcds;
+  if (q >= batch) return;
+  const int tile = slot % (tm * tn), m0 = tile % tm * 16, n0 = tile / tm * 16;
+  const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4;
+  gmem<const double> *a = gptr(A + sA * q + (size_t)min(m0 + li, M - 1) * lda);
+  gmem<const double> *b = gptr(B + sB * q + (size_t)min(n0 + li, N - 1) * ldb);
+  double av[4][4], bv[4][4];
+  auto load = [&](int k0, double (&x)[4], double (&y)[4]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int k = k0 + 4 * s + lg, kc = min(k, K - 1);
+      const double xa = a[kc], xb = b[kc];
+      x[s] = k < K ? xa : 0.0;
+      y[s] = k < K ? xb : 0.0;
+    }
+  };
+  d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) load(16 * c, av[c], bv[c]);
+  for (int k0 = 0; k0 < K; k0 += 64)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      load(k0 + 16 * (c + 3), av[(c + 3) % 4], bv[(c + 3) % 4]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c][s], bv[c][s], acc, 0, 0, 0);
+    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = m0 + lg + 4 * r, col = n0 + li;
+    if (row < M && col < N) {
+      double *c = C + sC * q + (size_t)col * ldc + row;
+      double out = alpha * acc[r];
+      if (beta != 0.0) out += beta * *c;
+      *c = out;
+    }
+  }
+}
+
+}  // namespace
+
 hipError_t gemm_f64_strided(int ta, int tb, int M, int N, int K, double alpha, const double *A,
                             int lda, long long sA, const double *B, int ldb, long long sB,
                             double beta, double *C, int ldc, long long sC, int batch,
                             hipStream_t st) {
   if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
   if (!(sA | sB | sC)) return hipErrorInvalidValue;
+  // 32 x 32 tiles that leave most of the 1024 SIMDs idle
+  const long long tiles = (long long)((M + 31) / 32) * ((N + 31) / 32) * batch;
+  if (ta == 1 && tb == 0 && K > 0 && tiles < 512) {
+    const int t16 = ((M + 15) / 16) * ((N + 15) / 16);
+    hipLaunchKernelGGL(gemm_tn16_kernel, dim3(t16 * ((batch + kXcds - 1) / kXcds) * kXcds),
+                       dim3(64), 0, st, M, N, K, batch, A, lda, sA, B, ldb, sB, C, ldc, sC, alpha,
+                       beta);
+    return hipGetLastError();
+  }
   dim3 grid((M + 31) / 32, (N + 31) / 32, batch);
 #define RIOT_GEMMS(TA_, TB_)                                                                  \
   hipLaunchKernelGGL((gemm_mfma_kernel<TA_, TB_>), grid, dim3(64), 0, st, M, N, K, A, lda, B, \

@@ -17,9 +17,27 @@
 namespace riot {
 namespace {
 
-constexpr int kCX = 64;   // grid points per tile
-constexpr int kCC = 16;   // output channels per tile
-constexpr int kMaxWidth = 11;  // keeps a tile's LDS within 64 KiB at 64 channels
+constexpr int kMaxWidth = 11;
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+// Sum over a workgroup of 256 threads as a binary tree (thread t adds t + 128, t + 64, ...).
+__device__ __forceinline__ double tree_sum(double v, double *red) {
+  const int t = threadIdx.x;
+  red[t] = v;
+  __syncthreads();
+  if (t < 128) red[t] += red[t + 128];
+  __syncthreads();
+  double s = 0.0;
+  if (t < 64) {
+    s = red[t] + red[t + 64];
+    for (int k = 32; k > 0; k >>= 1) s += __shfl_down(s, k, 64);
+    if (t == 0) red[0] = s;
+  }
+  __syncthreads();
+  s = red[0];
+  __syncthreads();
+  return s;
+}
 
 // Per-row standardization (x - mean) / std of FP64 input rows (one workgroup per sample and
 // input channel) into FP32.
@@ -29,82 +47,135 @@ __global__ void __launch_bounds__(256)
   const double *xs = x + (size_t)blockIdx.x * n;
   double s = 0.0;
   for (int i = threadIdx.x; i < n; i += blockDim.x) s += xs[i];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  const double mean = red[0] / n;
-  __syncthreads();
+  const double mean = tree_sum(s, red) / n;
   double q = 0.0;
   for (int i = threadIdx.x; i < n; i += blockDim.x) q += (xs[i] - mean) * (xs[i] - mean);
-  red[threadIdx.x] = q;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  const double inv = 1.0 / sqrt(red[0] / n);
+  const double inv = 1.0 / sqrt(tree_sum(q, red) / n);
   for (int i = threadIdx.x; i < n; i += blockDim.x)
     out[(size_t)blockIdx.x * n + i] = (float)((xs[i] - mean) * inv);
 }
 
-// z[c, i] = b[c] + sum_{c', j} W[c, c', j] h[c', (i + j - r) mod n], ReLU when relu != 0.
-// Tile: kCX grid points x kCC output channels; the input rows (all cin, with the halo)
-// and the tile's weights are staged in LDS; each thread computes four grid points.
+// z[c, i] = b[c] + sum_{c', j} W[c, c', j] h[c', (i + j - r) mod n], ReLU when relu != 0, on
+// the FP32 matrix cores: the contraction over (c', j) in that order, four values per
+// v_mfma_f32_16x16x4_f32, which adds its four products one after the other, each with one
+// rounding, so that an output value is the same chain of fused multiply-adds as before.
+// Operand lanes: lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16]; result register r of
+// lane l is C[4 (l / 16) + r][l % 16].
+// A workgroup takes all output channels, wave by wave 16 of them, and 16 NT grid points per wave
+// (waves that have no channels of their own take the next points: cgs waves along the
+// channels); the input rows (all cin, with the halo) are staged in LDS once, the weights come
+// from L2 four input channels (W matrix instructions per point tile) ahead.
+// FLIP: the backward-data pass, weights W[c'][c][W - 1 - j] of a forward layer cin <- cout, and
+// the result zeroed where act <= 0 (the ReLU derivative of the layer below).
+// n = 2048, 64 -> 64 channels, width 9, 16 samples (2.4 GFLOP): 55 us, one fused multiply-add per
+// lane and LDS value took 91 us; one sample 23 us.
+template <int W, int NT, bool FLIP>
 __global__ void __launch_bounds__(256)
-    conv_fwd_kernel(int n, int cin, int cout, int width, const float *__restrict__ h,
-                    const float *__restrict__ W, const float *__restrict__ b,
-                    float *__restrict__ z, int relu) {
-  extern __shared__ float sh[];
-  const int r = width / 2, span = kCX + width - 1;
-  float *Xs = sh;                       // [cin][span]
-  float *Ws = sh + (size_t)cin * span;  // [kCC][cin][width]
-  const int x0 = blockIdx.x * kCX, c0 = blockIdx.y * kCC, s = blockIdx.z;
-  const float *hs = h + (size_t)s * cin * n;
-  for (int k = threadIdx.x; k < cin * span; k += blockDim.x) {
-    const int ci = k / span, xx = k - ci * span;
-    int g = x0 + xx - r;
-    g = g < 0 ? g + n : (g >= n ? g - n : g);
-    Xs[k] = hs[(size_t)ci * n + g];
-  }
-  const int wsz = cin * width;
-  for (int k = threadIdx.x; k < kCC * wsz; k += blockDim.x) {
-    const int cl = k / wsz;
-    Ws[k] = (c0 + cl < cout) ? W[(size_t)(c0 + cl) * wsz + (k - cl * wsz)] : 0.f;
-  }
-  __syncthreads();
-  const int cl = threadIdx.x / 16, xq = threadIdx.x % 16;
-  const int c = c0 + cl;
-  if (c >= cout) return;
-  const float bias = b ? b[c] : 0.f;
-  float acc[4] = {bias, bias, bias, bias};
-  const float *wr = Ws + (size_t)cl * wsz;
-  for (int ci = 0; ci < cin; ++ci) {
-    const float *xr = Xs + (size_t)ci * span + xq * 4;
-    for (int j = 0; j < width; ++j) {
-      const float w = wr[ci * width + j];
+    conv_kernel(int n, int cin, int cout, int cgs, const float *__restrict__ h,
+                const float *__restrict__ Wt, const float *__restrict__ b,
+                const float *__restrict__ act, float *__restrict__ z, int relu) {
+  extern __shared__ float Xs[];  // [cin rounded up to 4][span]
+  constexpr int r = W / 2;
+  const int XT = 16 * NT * (4 / cgs), span = XT + W - 1;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int x0 = blockIdx.x * XT, s = blockIdx.y;
+  const int c0 = 16 * (wave % cgs), xw = 16 * NT * (wave / cgs);
+  const int cin4 = (cin + 3) / 4 * 4;
+  const int ca = c0 + li;  // this lane's row of A
+  float a[2][W];
+  int off[W];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) acc[q] = fmaf(w, xr[q + j], acc[q]);
+  for (int q = 0; q < W; ++q) off[q] = (4 * q + lg) / W * span + (4 * q + lg) % W + xw + li;
+  auto load_a = [&](int cb, float (&av)[W]) {
+#pragma unroll
+    for (int q = 0; q < W; ++q) {
+      const int k = 4 * q + lg;
+      const int ci = cb + k / W;
+      const bool in = ci < cin && ca < cout;
+      const size_t at = FLIP ? ((size_t)ci * cout + ca) * W + (W - 1 - k % W)
+                             : ((size_t)ca * cin + cb) * W + k;
+      const float v = Wt[in ? at : 0];
+      av[q] = in ? v : 0.f;
+    }
+  };
+  load_a(0, a[0]);
+  const float *hs = h + (size_t)s * cin * n;
+  for (int cb = wave; cb < cin4; cb += 16) {  // four rows of this wave at a time
+    float v[4][2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int ci = cb + 4 * q, xx = lane + 64 * p;
+        int g = x0 + xx - r;
+        g = g < 0 ? g + n : (g >= n ? g - n : g);
+        v[q][p] = (ci < cin && xx < span) ? hs[(size_t)ci * n + g] : 0.f;
+      }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int ci = cb + 4 * q, xx = lane + 64 * p;
+        if (ci < cin4 && xx < span) Xs[ci * span + xx] = v[q][p];
+      }
+  }
+  f4 acc[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c = c0 + 4 * lg + q;
+      acc[t][q] = (!FLIP && c < cout) ? b[c] : 0.f;
+    }
+  __syncthreads();
+  auto block = [&](int cb, const float (&av)[W]) {
+    const float *xr = Xs + cb * span;
+#pragma unroll
+    for (int q = 0; q < W; ++q)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], xr[off[q] + 16 * t], acc[t], 0, 0, 0);
+  };
+  for (int cb = 0; cb < cin4; cb += 8) {
+    load_a(cb + 4, a[1]);  // (zeros past the last channel)
+    block(cb, a[0]);
+    if (cb + 4 >= cin4) break;
+    load_a(cb + 8, a[0]);
+    block(cb + 4, a[1]);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = c0 + 4 * lg + q;
+    if (c >= cout) continue;
+    const size_t o = ((size_t)s * cout + c) * n + x0 + xw + li;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      float v = acc[t][q];
+      if (FLIP)
+        v = act[o + 16 * t] > 0.f ? v : 0.f;
+      else if (relu)
+        v = fmaxf(v, 0.f);
+      z[o + 16 * t] = v;
     }
   }
-  float *zo = z + ((size_t)s * cout + c) * n + x0 + xq * 4;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) zo[q] = relu ? fmaxf(acc[q], 0.f) : acc[q];
 }
 
 // Localized output head: N[s][c S + q][i] = z[s][c][i] for grid points i of segment q
-// (n / S consecutive points), 0 elsewhere; z has k / S channels.
+// (n / S consecutive points), 0 elsewhere; z has k / S channels. To FP32 (N) and / or, with
+// columns ld64 apart, FP64 (N64).
 __global__ void segment_out_kernel(int n, int kch, int S, long long total,
-                                   const float *__restrict__ z, float *__restrict__ N) {
+                                   const float *__restrict__ z, float *__restrict__ N,
+                                   double *__restrict__ N64, int ld64) {
   const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   const int k = kch * S;
-  const int i = (int)(e % n), col = (int)((e / n) % k);
-  const long long s = e / ((long long)n * k);
-  const int c = col / S, q = col - c * S;
-  N[e] = (i / (n / S) == q) ? z[(s * kch + c) * n + i] : 0.f;
+  const long long gcol = e / n;
+  const int i = (int)(e - gcol * n);
+  const long long s = gcol / k;
+  const int col = (int)(gcol - s * k), c = col / S, q = col - c * S;
+  const float v = (i / (n / S) == q) ? z[(s * kch + c) * n + i] : 0.f;
+  if (N) N[e] = v;
+  if (N64) N64[gcol * ld64 + i] = (double)v;
 }
 
 // Its transpose: gz[s][c][i] = gN[s][c S + (segment of i)][i].
@@ -118,88 +189,127 @@ __global__ void segment_grad_kernel(int n, int kch, int S, long long total,
   gz[e] = gN[(s * kch * S + (long long)c * S + q) * n + i];
 }
 
-// Wt[ci][co][j'] = W[co][ci][width - 1 - j']: the backward-data pass is a forward
-// convolution of the output gradient with these weights.
-__global__ void flip_transpose_kernel(int cin, int cout, int width, const float *__restrict__ W,
-                                      float *__restrict__ Wt) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= cin * cout * width) return;
-  const int j = k % width, co = (k / width) % cout, ci = k / (width * cout);
-  Wt[k] = W[((size_t)co * cin + ci) * width + (width - 1 - j)];
-}
+// Weight gradient gW[co][ci][j] = sum_s sum_i g[s][co][i] h[s][ci][(i + j - r) mod n] and bias
+// gradient gb[co] = sum_s sum_i g[s][co][i], in two passes with a fixed summation order. Pass 1,
+// on the FP32 matrix cores: a workgroup takes the chunks of kCP grid points [z per, z per + per)
+// of all samples, 16 WC output and 16 WI input channels, a wave 16 x 16 of them with all W taps:
+// four points of g are one operand of W products with h shifted by j, and the bias gradient is
+// the product with ones. The chunk's rows of g and h (with the halo) are staged in LDS, the next
+// chunk's in registers meanwhile. FP32 sums run over fl chunks (256, 128 or 64 points of one
+// sample, as they divide n; fl divides per) and then go to FP64. Pass 2 adds the workgroups'
+// sums in FP64.
+// n = 2048, 64 x 64 channels, width 9, 16 samples (2.4 GFLOP): 43 us and 5 us; one fused
+// multiply-add per lane and register window took 37 us, and the second pass, one chain of 128
+// partial sums per weight, 28 us.
+constexpr int kCP = 64;
 
-// g *= (act > 0): ReLU derivative applied to the gradient of a hidden layer's output.
-__global__ void relu_mask_kernel(long long count, const float *__restrict__ act,
-                                 float *__restrict__ g) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count && !(act[i] > 0.f)) g[i] = 0.f;
-}
-
-// Weight gradient gW[co][ci][j] = sum_s sum_i g[s][co][i] h[s][ci][(i + j - r) mod n] and
-// bias gradient gb[co] = sum_s sum_i g[s][co][i], in two passes with a fixed summation
-// order. Pass 1: a workgroup takes one chunk of CP grid points of one sample, 16 output
-// and 16 input channels; g rows and h rows (with the halo) are staged in LDS, thread
-// (co, ci) slides a W-wide register window along the chunk and keeps W FP32 sums.
-// Pass 2 adds the chunks' partial sums in FP64, chunk by chunk.
-template <int W>
+template <int W, int WC, int WI>
 __global__ void __launch_bounds__(256)
-    conv_bwd_weight_part_kernel(int n, int cin, int cout, int CP, int chunks_per_sample,
-                                const float *__restrict__ g, const float *__restrict__ h,
-                                float *__restrict__ part_w, float *__restrict__ part_b) {
-  extern __shared__ float sh[];
-  constexpr int r = W / 2;
-  const int span = CP + W - 1, hld = span + 1;  // odd row stride: no LDS bank conflicts
-  float *Gs = sh;                              // [16][CP]
-  float *Hs = sh + 16 * CP;                    // [16][hld]
-  const int chunk = blockIdx.x, s = chunk / chunks_per_sample;
-  const int i0 = (chunk - s * chunks_per_sample) * CP;
-  const int ci0 = blockIdx.y * 16, co0 = blockIdx.z * 16;
-  for (int e = threadIdx.x; e < 16 * CP; e += blockDim.x) {
-    const int cl = e / CP, p = e - cl * CP;
-    Gs[e] = (co0 + cl < cout) ? g[((size_t)s * cout + co0 + cl) * n + i0 + p] : 0.f;
+    conv_wgrad_kernel(int n, int cin, int cout, int chunks, int per, int fl, const float *__restrict__ g,
+                      const float *__restrict__ h, double *__restrict__ part) {
+  constexpr int r = W / 2, span = kCP + W - 1;
+  // row strides of 4 mod 8 words: the 16 rows x 4 points of an operand fall into distinct banks
+  constexpr int ldg = kCP + 4, ldh = (span + 3) / 8 * 8 + 4;
+  __shared__ float Gs[16 * WC * ldg], Hs[16 * WI * ldh];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int ci0 = blockIdx.y * 16 * WI, co0 = blockIdx.z * 16 * WC;
+  const int wc = wave % WC, wi = wave / WC;
+  const int cps = n / kCP, cbeg = blockIdx.x * per, cend = min(cbeg + per, chunks);
+  float vg[4 * WC], vh[4 * WI][2];
+  auto fetch = [&](int c) {
+    const int s = c / cps, i0 = (c - s * cps) * kCP;
+#pragma unroll
+    for (int q = 0; q < 4 * WC; ++q) {
+      const int co = co0 + wave + 4 * q;
+      const float v = g[((size_t)s * cout + min(co, cout - 1)) * n + i0 + lane];
+      vg[q] = co < cout ? v : 0.f;
+    }
+    int p0 = i0 + lane - r, p1 = i0 + 64 + lane - r;
+    p0 = p0 < 0 ? p0 + n : p0;
+    p1 = p1 >= n ? p1 - n : p1;
+#pragma unroll
+    for (int q = 0; q < 4 * WI; ++q) {
+      const int ci = ci0 + wave + 4 * q;
+      const float *hr = h + ((size_t)s * cin + min(ci, cin - 1)) * n;
+      const float a = hr[p0], b = lane < W - 1 ? hr[p1] : 0.f;
+      vh[q][0] = ci < cin ? a : 0.f;
+      vh[q][1] = ci < cin ? b : 0.f;
+    }
+  };
+  const bool bias = blockIdx.y == 0 && wi == 0;
+  f4 acc[W + 1];
+  double sum[W + 1][4];
+#pragma unroll
+  for (int j = 0; j <= W; ++j) {
+    acc[j] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[j][q] = 0.0;
   }
-  for (int e = threadIdx.x; e < 16 * span; e += blockDim.x) {
-    const int cl = e / span, p = e - cl * span;
-    int gi = i0 + p - r;
-    gi = gi < 0 ? gi + n : (gi >= n ? gi - n : gi);
-    Hs[cl * hld + p] = (ci0 + cl < cin) ? h[((size_t)s * cin + ci0 + cl) * n + gi] : 0.f;
+  auto flush = [&]() {
+#pragma unroll
+    for (int j = 0; j <= W; ++j) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sum[j][q] += (double)acc[j][q];
+      acc[j] = f4{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  if (cbeg < cend) fetch(cbeg);
+  for (int c = cbeg; c < cend; ++c) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4 * WC; ++q) Gs[(wave + 4 * q) * ldg + lane] = vg[q];
+#pragma unroll
+    for (int q = 0; q < 4 * WI; ++q) {
+      Hs[(wave + 4 * q) * ldh + lane] = vh[q][0];
+      if (lane < W - 1) Hs[(wave + 4 * q) * ldh + 64 + lane] = vh[q][1];
+    }
+    __syncthreads();
+    if (c + 1 < cend) fetch(c + 1);
+    const float *gr = Gs + (16 * wc + li) * ldg + lg, *hr = Hs + (16 * wi + li) * ldh + lg;
+#pragma unroll 4
+    for (int p = 0; p < kCP; p += 4) {
+      const float av = gr[p];
+#pragma unroll
+      for (int j = 0; j < W; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, hr[p + j], acc[j], 0, 0, 0);
+      if (bias) acc[W] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, 1.f, acc[W], 0, 0, 0);
+    }
+    if ((c + 1) % fl == 0) flush();
   }
-  __syncthreads();
-  const int col = threadIdx.x / 16, cil = threadIdx.x % 16;
-  const float *gr = Gs + col * CP;
-  const float *hr = Hs + cil * hld;
-  float acc[W], win[W];
-  float accb = 0.f;
+  const long long cw = (long long)cout * cin * W;
+  double *o = part + (size_t)blockIdx.x * (cw + cout);
+  const int ci = ci0 + 16 * wi + li;
 #pragma unroll
-  for (int q = 0; q < W; ++q) acc[q] = 0.f;
+  for (int q = 0; q < 4; ++q) {
+    const int co = co0 + 16 * wc + 4 * lg + q;
+    if (co < cout && ci < cin) {
 #pragma unroll
-  for (int q = 0; q < W - 1; ++q) win[q + 1] = hr[q];
-  for (int p = 0; p < CP; ++p) {
-#pragma unroll
-    for (int q = 0; q < W - 1; ++q) win[q] = win[q + 1];
-    win[W - 1] = hr[p + W - 1];
-    const float gp = gr[p];
-    accb += gp;
-#pragma unroll
-    for (int q = 0; q < W; ++q) acc[q] = fmaf(gp, win[q], acc[q]);
+      for (int j = 0; j < W; ++j) o[((size_t)co * cin + ci) * W + j] = sum[j][q];
+    }
+    if (co < cout && bias && li == 0) o[cw + co] = sum[W][q];
   }
-  const int co = co0 + col, ci = ci0 + cil;
-  if (co < cout && ci < cin) {
-    float *o = part_w + ((size_t)chunk * cout + co) * cin * W + (size_t)ci * W;
-#pragma unroll
-    for (int q = 0; q < W; ++q) o[q] = acc[q];
-  }
-  if (blockIdx.y == 0 && cil == 0 && co < cout) part_b[(size_t)chunk * cout + co] = accb;
 }
 
-// out[e] = sum over chunks c = 0, 1, ... of part[c * count + e] (FP64, in chunk order).
-__global__ void chunk_sum_kernel(long long count, int chunks, const float *__restrict__ part,
-                                 float *__restrict__ out) {
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= count) return;
+// out[e] = sum over z < parts of part[z * count + e] (FP64): thread group q of a workgroup adds
+// z = q, q + 8, ..., then the groups are added in order. (One chain of loads per element would
+// be bound by their latency.)
+__global__ void __launch_bounds__(256)
+    part_sum_kernel(long long count, int parts, const double *__restrict__ part,
+                    float *__restrict__ out) {
+  __shared__ double red[256];
+  const int q = threadIdx.x >> 5;
+  const long long e = (long long)blockIdx.x * 32 + (threadIdx.x & 31);
   double acc = 0.0;
-  for (int c = 0; c < chunks; ++c) acc += (double)part[(size_t)c * count + e];
-  out[e] = (float)acc;
+  if (e < count) {
+#pragma unroll 8
+    for (int z = q; z < parts; z += 8) acc += part[(size_t)z * count + e];
+  }
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  if (q == 0 && e < count) {
+    for (int g = 1; g < 8; ++g) acc += red[32 * g + threadIdx.x];
+    out[e] = (float)acc;
+  }
 }
 
 __global__ void adam_kernel(long long count, float *__restrict__ p, const float *__restrict__ g,
@@ -218,15 +328,6 @@ __global__ void adam_kernel(long long count, float *__restrict__ p, const float 
 __global__ void f2d_kernel(long long count, const float *__restrict__ a, double *__restrict__ b) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < count) b[i] = (double)a[i];
-}
-
-// Y[col * ldy + i] = (double) X[col * n + i]: network output columns into an FP64 block.
-__global__ void widen_kernel(int n, long long cols, const float *__restrict__ X,
-                             double *__restrict__ Y, int ldy) {
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= cols * n) return;
-  const long long col = e / n;
-  Y[col * ldy + (e - col * n)] = (double)X[e];
 }
 
 // identity blocks (k x k per sample)
@@ -298,9 +399,9 @@ struct riot_net {
   float *params = nullptr, *grads = nullptr, *am = nullptr, *av = nullptr;
   float *x0 = nullptr;               // standardized inputs [batch][in_channels][n]
   std::vector<float *> acts;         // per layer outputs [batch][cout][n]
-  float *g0 = nullptr, *g1 = nullptr, *Wt = nullptr, *gN = nullptr;
+  float *g0 = nullptr, *g1 = nullptr, *gN = nullptr;
   float *Nout = nullptr;             // network output after the head [batch][k][n]
-  float *wpart = nullptr;            // per-chunk partial weight and bias gradients
+  double *wpart = nullptr;           // partial weight and bias gradients
   // loss workspace (FP64)
   double *Nd = nullptr, *G = nullptr, *Lc = nullptr, *Z = nullptr, *Gi = nullptr, *A = nullptr,
          *WA = nullptr, *C = nullptr, *Y1 = nullptr, *Y2 = nullptr, *MN = nullptr, *X = nullptr,
@@ -314,8 +415,30 @@ namespace {
 
 size_t n256(size_t b) { return (b + 255) / 256 * 256; }
 
-// grid points per chunk of the weight-gradient pass (divides n)
-int chunk_points(int n) { return n % 256 == 0 ? 256 : (n % 128 == 0 ? 128 : 64); }
+// Split of a layer's weight gradient: channel tiles per workgroup (16 wc output, 16 wi input
+// channels: four waves, along the side that has them), and as many workgroups along the grid
+// points as give one per compute unit (256) with the tiles.
+struct WgradPlan {
+  int wc, wi, chunks, per, parts, fl;
+};
+WgradPlan wgrad_plan(int batch, int n, int cin, int cout) {
+  WgradPlan p;
+  p.wc = cin <= 16 ? 4 : (cout <= 16 ? 1 : 2);
+  p.wi = 4 / p.wc;
+  const int tiles = ((cin + 16 * p.wi - 1) / (16 * p.wi)) * ((cout + 16 * p.wc - 1) / (16 * p.wc));
+  p.chunks = batch * (n / riot::kCP);
+  p.fl = n % 256 == 0 ? 4 : (n % 128 == 0 ? 2 : 1);
+  p.per = (p.chunks / p.fl + 256 / tiles - 1) / (256 / tiles) * p.fl;
+  p.parts = (p.chunks + p.per - 1) / p.per;
+  return p;
+}
+
+// The most parts of any batch up to batch_max (a larger batch need not have more).
+int wgrad_max_parts(int batch_max, int n, int cin, int cout) {
+  int mx = 0;
+  for (int b = 1; b <= batch_max; ++b) mx = std::max(mx, wgrad_plan(b, n, cin, cout).parts);
+  return mx;
+}
 
 struct NCarve {
   char *base;
@@ -366,15 +489,14 @@ size_t net_carve(riot_net &h, void *base) {
   for (int l = 0; l < d.layers; ++l) h.acts[l] = c.take<float>(B * h.cout[l] * n);
   h.g0 = c.take<float>(B * maxc * n);
   h.g1 = c.take<float>(B * maxc * n);
-  h.Wt = c.take<float>((size_t)maxc * maxc * d.width);
   h.gN = c.take<float>(B * k * n);
   h.Nout = c.take<float>(B * k * n);
   {
-    const size_t chunks = B * (n / chunk_points((int)n));
     size_t mx = 0;
     for (int l = 0; l < d.layers; ++l)
-      mx = std::max(mx, (size_t)h.cout[l] * h.cin[l] * d.width + h.cout[l]);
-    h.wpart = c.take<float>(chunks * mx);
+      mx = std::max(mx, (size_t)wgrad_max_parts(d.batch_max, (int)n, h.cin[l], h.cout[l]) *
+                            ((size_t)h.cout[l] * h.cin[l] * d.width + h.cout[l]));
+    h.wpart = c.take<double>(mx);
   }
   h.Nd = c.take<double>(B * n * k);
   h.G = c.take<double>(B * kk);
@@ -401,47 +523,79 @@ size_t net_carve(riot_net &h, void *base) {
     if ((call) != hipSuccess) return RIOT_E_HIP; \
   } while (0)
 
+// Convolution of `batch` samples: the forward layer (W, b; ReLU when relu), or with act the
+// backward-data pass of a layer cout -> cin. Grid points per wave: the most (64, 32, 16) that
+// leave two workgroups per compute unit, since the weights are read once per workgroup.
+template <int W, bool FLIP>
+void launch_conv(riot_net *h, int batch, const float *in, int cin, int cout, const float *Wt,
+                 const float *b, const float *act, float *out, bool relu) {
+  const int n = h->d.n, cgs = cout > 32 ? 4 : (cout > 16 ? 2 : 1), xw = 4 / cgs;
+  int nt = std::min(4, 4 / xw);
+  while (nt > 1 && (long long)batch * (n / (16 * nt * xw)) < 512) nt /= 2;
+  const int XT = 16 * nt * xw;
+  const size_t lds = (size_t)((cin + 3) / 4 * 4) * (XT + W - 1) * sizeof(float);
+  const dim3 grid(n / XT, batch);
+#define RIOT_CONV(NT_)                                                                          \
+  hipLaunchKernelGGL((riot::conv_kernel<W, NT_, FLIP>), grid, dim3(256), lds, h->st, n, cin, cout, \
+                     cgs, in, Wt, b, act, out, relu ? 1 : 0)
+  if (nt == 4)
+    RIOT_CONV(4);
+  else if (nt == 2)
+    RIOT_CONV(2);
+  else
+    RIOT_CONV(1);
+#undef RIOT_CONV
+}
+
+template <int W, int WC, int WI>
+void launch_wgrad(riot_net *h, const WgradPlan &p, int cin, int cout, const float *g,
+                  const float *hin) {
+  const dim3 grid(p.parts, (cin + 16 * WI - 1) / (16 * WI), (cout + 16 * WC - 1) / (16 * WC));
+  hipLaunchKernelGGL((riot::conv_wgrad_kernel<W, WC, WI>), grid, dim3(256), 0, h->st, h->d.n, cin,
+                     cout, p.chunks, p.per, p.fl, g, hin, h->wpart);
+}
+
+#define RIOT_WIDTH(W_, CALL)                  \
+  switch (W_) {                               \
+    case 1: { constexpr int WW = 1; CALL; } break;   \
+    case 3: { constexpr int WW = 3; CALL; } break;   \
+    case 5: { constexpr int WW = 5; CALL; } break;   \
+    case 7: { constexpr int WW = 7; CALL; } break;   \
+    case 9: { constexpr int WW = 9; CALL; } break;   \
+    case 11: { constexpr int WW = 11; CALL; } break; \
+    default: return RIOT_E_ARG;               \
+  }
+
 riot_status conv_forward(riot_net *h, int batch, const float *in, int cin, int cout,
                          const float *W, const float *b, float *out, bool relu) {
-  const int n = h->d.n, width = h->d.width;
-  const size_t lds = ((size_t)cin * (riot::kCX + width - 1) + (size_t)riot::kCC * cin * width) *
-                     sizeof(float);
-  hipLaunchKernelGGL(riot::conv_fwd_kernel, dim3(n / riot::kCX, (cout + riot::kCC - 1) / riot::kCC, batch),
-                     dim3(256), lds, h->st, n, cin, cout, width, in, W, b, out, relu ? 1 : 0);
+  RIOT_WIDTH(h->d.width, (launch_conv<WW, false>(h, batch, in, cin, cout, W, b, nullptr, out, relu)));
   NET_HIP(hipGetLastError());
   return RIOT_OK;
 }
 
-template <int W>
-void launch_wgrad_part(dim3 grid, size_t lds, hipStream_t st, int n, int cin, int cout, int CP,
-                       int cps, const float *g, const float *hin, float *pw, float *pb) {
-  hipLaunchKernelGGL(riot::conv_bwd_weight_part_kernel<W>, grid, dim3(256), lds, st, n, cin, cout,
-                     CP, cps, g, hin, pw, pb);
+// out = the gradient of the layer's input, zeroed where act <= 0 (layer: cout -> cin channels)
+riot_status conv_backward_data(riot_net *h, int batch, const float *g, int cin, int cout,
+                               const float *W, const float *act, float *out) {
+  RIOT_WIDTH(h->d.width, (launch_conv<WW, true>(h, batch, g, cin, cout, W, nullptr, act, out, false)));
+  NET_HIP(hipGetLastError());
+  return RIOT_OK;
 }
 
+// grads: the layer's weights, then its biases
 riot_status weight_grad(riot_net *h, int batch, int cin, int cout, const float *g,
-                        const float *hin, float *gW, float *gb) {
-  const int n = h->d.n, W = h->d.width, CP = chunk_points(n), cps = n / CP;
-  const int chunks = batch * cps;
-  const dim3 grid(chunks, (cin + 15) / 16, (cout + 15) / 16);
-  const size_t lds = (16 * (size_t)CP + 16 * (size_t)(CP + W)) * sizeof(float);
-  float *pw = h->wpart, *pb = h->wpart + (size_t)chunks * cout * cin * W;
-  switch (W) {
-    case 1: launch_wgrad_part<1>(grid, lds, h->st, n, cin, cout, CP, cps, g, hin, pw, pb); break;
-    case 3: launch_wgrad_part<3>(grid, lds, h->st, n, cin, cout, CP, cps, g, hin, pw, pb); break;
-    case 5: launch_wgrad_part<5>(grid, lds, h->st, n, cin, cout, CP, cps, g, hin, pw, pb); break;
-    case 7: launch_wgrad_part<7>(grid, lds, h->st, n, cin, cout, CP, cps, g, hin, pw, pb); break;
-    case 9: launch_wgrad_part<9>(grid, lds, h->st, n, cin, cout, CP, cps, g, hin, pw, pb); break;
-    case 11: launch_wgrad_part<11>(grid, lds, h->st, n, cin, cout, CP, cps, g, hin, pw, pb); break;
-    default: return RIOT_E_ARG;
+                        const float *hin, float *grads) {
+  const WgradPlan p = wgrad_plan(batch, h->d.n, cin, cout);
+  if (p.wc == 4) {
+    RIOT_WIDTH(h->d.width, (launch_wgrad<WW, 4, 1>(h, p, cin, cout, g, hin)));
+  } else if (p.wc == 2) {
+    RIOT_WIDTH(h->d.width, (launch_wgrad<WW, 2, 2>(h, p, cin, cout, g, hin)));
+  } else {
+    RIOT_WIDTH(h->d.width, (launch_wgrad<WW, 1, 4>(h, p, cin, cout, g, hin)));
   }
   NET_HIP(hipGetLastError());
-  const long long cw = (long long)cout * cin * W;
-  hipLaunchKernelGGL(riot::chunk_sum_kernel, dim3(riot::nblocks(cw)), dim3(256), 0, h->st, cw,
-                     chunks, pw, gW);
-  NET_HIP(hipGetLastError());
-  hipLaunchKernelGGL(riot::chunk_sum_kernel, dim3(riot::nblocks(cout)), dim3(256), 0, h->st,
-                     (long long)cout, chunks, pb, gb);
+  const long long count = (long long)cout * cin * h->d.width + cout;
+  hipLaunchKernelGGL(riot::part_sum_kernel, dim3((unsigned)((count + 31) / 32)), dim3(256), 0,
+                     h->st, count, p.parts, h->wpart, grads);
   NET_HIP(hipGetLastError());
   return RIOT_OK;
 }
@@ -539,21 +693,15 @@ riot_status riot_net_forward(riot_net *h, int32_t batch, const double *x, float 
   }
   const int S = h->d.segments;
   const long long tot = (long long)batch * k * n;
-  float *res = N ? N : h->Nout;
   hipLaunchKernelGGL(riot::segment_out_kernel, dim3(riot::nblocks(tot)), dim3(256), 0, h->st, n,
-                     k / S, S, tot, h->acts[h->d.layers - 1], res);
+                     k / S, S, tot, h->acts[h->d.layers - 1], N || N64 ? N : h->Nout, N64, ld64);
   NET_HIP(hipGetLastError());
-  if (N64) {
-    hipLaunchKernelGGL(riot::widen_kernel, dim3(riot::nblocks((long long)batch * k * n)), dim3(256),
-                       0, h->st, n, (long long)batch * k, res, N64, ld64);
-    NET_HIP(hipGetLastError());
-  }
   return RIOT_OK;
 }
 
 riot_status riot_net_backward(riot_net *h, int32_t batch, const float *gN) {
   if (!h || !gN || batch < 1 || batch > h->d.batch_max) return RIOT_E_ARG;
-  const int n = h->d.n, width = h->d.width, L = h->d.layers;
+  const int n = h->d.n, L = h->d.layers;
   const int S = h->d.segments, kch = h->d.k / S;
   const long long tot = (long long)batch * kch * n;
   hipLaunchKernelGGL(riot::segment_grad_kernel, dim3(riot::nblocks(tot)), dim3(256), 0, h->st, n,
@@ -562,22 +710,11 @@ riot_status riot_net_backward(riot_net *h, int32_t batch, const float *gN) {
   float *g = h->g0, *gnext = h->g1;
   for (int l = L - 1; l >= 0; --l) {
     const int ci = h->cin[l], co = h->cout[l];
-    if (l < L - 1) {
-      hipLaunchKernelGGL(riot::relu_mask_kernel, dim3(riot::nblocks((long long)batch * co * n)),
-                         dim3(256), 0, h->st, (long long)batch * co * n, h->acts[l], g);
-      NET_HIP(hipGetLastError());
-    }
     const float *hin = l == 0 ? h->x0 : h->acts[l - 1];
-    {
-      riot_status rs = weight_grad(h, batch, ci, co, g, hin, h->grads + h->woff[l],
-                                   h->grads + h->boff[l]);
-      if (rs != RIOT_OK) return rs;
-    }
+    riot_status rs = weight_grad(h, batch, ci, co, g, hin, h->grads + h->woff[l]);
+    if (rs != RIOT_OK) return rs;
     if (l > 0) {
-      hipLaunchKernelGGL(riot::flip_transpose_kernel, dim3(riot::nblocks((long long)ci * co * width)),
-                         dim3(256), 0, h->st, ci, co, width, h->params + h->woff[l], h->Wt);
-      NET_HIP(hipGetLastError());
-      riot_status rs = conv_forward(h, batch, g, co, ci, h->Wt, nullptr, gnext, false);
+      rs = conv_backward_data(h, batch, g, co, ci, h->params + h->woff[l], h->acts[l - 1], gnext);
       if (rs != RIOT_OK) return rs;
       std::swap(g, gnext);
     }
