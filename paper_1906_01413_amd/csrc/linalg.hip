@@ -2205,10 +2205,10 @@ namespace {
 
 // C_q = alpha A_q^T B_q + beta C_q of a strided batch with a long contraction and few tiles: one
 // wave per 16 x 16 tile of C, so that four times as many waves as with 32 x 32 tiles share the
-// work of the same chains (an element is summed in the same order, k ascending by fours). Four
-// chunks of 16 k are in flight. The tiles of one product share an XCD (workgroup L runs on XCD
+// work of the same chains (an element is summed in the same order, k ascending by fours).
+// Seven chunks of 16 k are in flight (with three, 58 us). The tiles of one product share an XCD (workgroup L runs on XCD
 // L % 8), whose L2 then holds its operands. Bound by the chain: K / 4 matrix instructions of 64
-// clocks. 16 products of 64 x 64 with K = 2048: 55 us, as 64 waves of 32 x 32 169 us.
+// clocks. 16 products of 64 x 64 with K = 2048: 46 us, as 64 waves of 32 x 32 169 us.
 __global__ void __launch_bounds__(64)
     gemm_tn16_kernel(int M, int N, int K, int batch, const double *__restrict__ A, int lda,
                      long long sA, const double *__restrict__ B, int ldb, long long sB,
@@ -2220,7 +2220,8 @@ __global__ void __launch_bounds__(64)
   const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4;
   gmem<const double> *a = gptr(A + sA * q + (size_t)min(m0 + li, M - 1) * lda);
   gmem<const double> *b = gptr(B + sB * q + (size_t)min(n0 + li, N - 1) * ldb);
-  double av[4][4], bv[4][4];
+  constexpr int R = 8;
+  double av[R][4], bv[R][4];
   auto load = [&](int k0, double (&x)[4], double (&y)[4]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -2232,11 +2233,11 @@ __global__ void __launch_bounds__(64)
   };
   d4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int c = 0; c < 3; ++c) load(16 * c, av[c], bv[c]);
-  for (int k0 = 0; k0 < K; k0 += 64)
+  for (int c = 0; c < R - 1; ++c) load(16 * c, av[c], bv[c]);
+  for (int k0 = 0; k0 < K; k0 += 16 * R)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      load(k0 + 16 * (c + 3), av[(c + 3) % 4], bv[(c + 3) % 4]);
+    for (int c = 0; c < R; ++c) {
+      load(k0 + 16 * (c + R - 1), av[(c + R - 1) % R], bv[(c + R - 1) % R]);
 #pragma unroll
       for (int s = 0; s < 4; ++s)
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c][s], bv[c][s], acc, 0, 0, 0);

@@ -55,6 +55,45 @@ __global__ void __launch_bounds__(256)
     out[(size_t)blockIdx.x * n + i] = (float)((xs[i] - mean) * inv);
 }
 
+// Weights in operand order. The contraction index of a convolution is k = c' W + j; step k / 4
+// takes lanes l / 16 = k % 4; groups of four steps are stored lane by lane, so element k of
+// output channel c is float (step % 4) of lane 16 (k % 4) + c % 16 of group step / 4 of the 16
+// channels c / 16. Zeros fill up to whole groups and 16 channels. fwd: the layer's own weights;
+// bwd: those of its backward-data pass (none for the first layer).
+struct Frag {
+  int layers, width;
+  int cin[16], cout[16];
+  long long woff[16], fwd[16], bwd[16];  // offsets of the layer's weights in the three arrays
+};
+__host__ __device__ __forceinline__ int frag_groups(int cin, int width) {
+  return ((cin + 3) / 4 * width + 3) / 4;
+}
+__host__ __device__ __forceinline__ long long frag_floats(int cin, int cout, int width) {
+  return (long long)((cout + 15) / 16) * frag_groups(cin, width) * 256;
+}
+__device__ __forceinline__ long long frag_at(int cin, int width, int c, int k) {
+  const int step = k / 4;
+  return (((long long)(c / 16) * frag_groups(cin, width) + step / 4) * 64 + 16 * (k % 4) + c % 16) *
+             4 + step % 4;
+}
+// parameter i (of the flat parameters) is v
+__device__ __forceinline__ void frag_put(const Frag &f, long long i, float v,
+                                         float *__restrict__ frag) {
+  int l = f.layers - 1;
+  while (l > 0 && i < f.woff[l]) --l;
+  const int e = (int)(i - f.woff[l]), cin = f.cin[l], cout = f.cout[l], W = f.width;
+  if (e >= cout * cin * W) return;  // a bias
+  const int co = e / (cin * W), k = e - co * cin * W, ci = k / W, j = k - ci * W;
+  frag[f.fwd[l] + frag_at(cin, W, co, k)] = v;
+  if (l > 0) frag[f.bwd[l] + frag_at(cout, W, ci, co * W + W - 1 - j)] = v;
+}
+
+__global__ void frag_kernel(long long count, Frag f, const float *__restrict__ p,
+                            float *__restrict__ frag) {
+  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < count) frag_put(f, i, p[i], frag);
+}
+
 // z[c, i] = b[c] + sum_{c', j} W[c, c', j] h[c', (i + j - r) mod n], ReLU when relu != 0, on
 // the FP32 matrix cores: the contraction over (c', j) in that order, four values per
 // v_mfma_f32_16x16x4_f32, which adds its four products one after the other, each with one
@@ -63,16 +102,19 @@ __global__ void __launch_bounds__(256)
 // lane l is C[4 (l / 16) + r][l % 16].
 // A workgroup takes all output channels, wave by wave 16 of them, and 16 NT grid points per wave
 // (waves that have no channels of their own take the next points: cgs waves along the
-// channels); the input rows (all cin, with the halo) are staged in LDS once, the weights come
-// from L2 four input channels (W matrix instructions per point tile) ahead.
+// channels); the input rows (all cin, with the halo) are staged in LDS once. The weights come
+// in the order of the operands (Frag), 16 bytes per lane for four matrix instructions, 16 input
+// channels ahead.
 // FLIP: the backward-data pass, weights W[c'][c][W - 1 - j] of a forward layer cin <- cout, and
 // the result zeroed where act <= 0 (the ReLU derivative of the layer below).
-// n = 2048, 64 -> 64 channels, width 9, 16 samples (2.4 GFLOP): 55 us, one fused multiply-add per
-// lane and LDS value took 91 us; one sample 23 us.
+// n = 2048, 64 -> 64 channels, width 9: 16 samples (2.4 GFLOP) 31 us (16 us at the rate of a
+// large FP32 product), one sample 12 us, bound by staging and the chain of 144 matrix
+// instructions. One fused multiply-add per lane and LDS value took 91 and 23 us; weights in
+// parameter order, 16 rows of 16 bytes per load, 55 and 23 us.
 template <int W, int NT, bool FLIP>
 __global__ void __launch_bounds__(256)
     conv_kernel(int n, int cin, int cout, int cgs, const float *__restrict__ h,
-                const float *__restrict__ Wt, const float *__restrict__ b,
+                const float *__restrict__ wf, const float *__restrict__ b,
                 const float *__restrict__ act, float *__restrict__ z, int relu) {
   extern __shared__ float Xs[];  // [cin rounded up to 4][span]
   constexpr int r = W / 2;
@@ -80,25 +122,16 @@ __global__ void __launch_bounds__(256)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int x0 = blockIdx.x * XT, s = blockIdx.y;
   const int c0 = 16 * (wave % cgs), xw = 16 * NT * (wave / cgs);
-  const int cin4 = (cin + 3) / 4 * 4;
-  const int ca = c0 + li;  // this lane's row of A
-  float a[2][W];
-  int off[W];
+  const int cin4 = (cin + 3) / 4 * 4, groups = frag_groups(cin, W);
+  // (a wave without channels of its own repeats the last ones')
+  const f4 *wl = reinterpret_cast<const f4 *>(wf) +
+                 (size_t)min(c0 / 16, (cout - 1) / 16) * groups * 64 + lane;
+  f4 a[W], an[W];
+  auto load_a = [&](int cb, f4 (&av)[W]) {  // W groups: 16 input channels from cb
 #pragma unroll
-  for (int q = 0; q < W; ++q) off[q] = (4 * q + lg) / W * span + (4 * q + lg) % W + xw + li;
-  auto load_a = [&](int cb, float (&av)[W]) {
-#pragma unroll
-    for (int q = 0; q < W; ++q) {
-      const int k = 4 * q + lg;
-      const int ci = cb + k / W;
-      const bool in = ci < cin && ca < cout;
-      const size_t at = FLIP ? ((size_t)ci * cout + ca) * W + (W - 1 - k % W)
-                             : ((size_t)ca * cin + cb) * W + k;
-      const float v = Wt[in ? at : 0];
-      av[q] = in ? v : 0.f;
-    }
+    for (int q = 0; q < W; ++q) av[q] = wl[(size_t)min(cb / 16 * W + q, groups - 1) * 64];
   };
-  load_a(0, a[0]);
+  load_a(0, a);
   const float *hs = h + (size_t)s * cin * n;
   for (int cb = wave; cb < cin4; cb += 16) {  // four rows of this wave at a time
     float v[4][2];
@@ -127,21 +160,25 @@ __global__ void __launch_bounds__(256)
       const int c = c0 + 4 * lg + q;
       acc[t][q] = (!FLIP && c < cout) ? b[c] : 0.f;
     }
+  int off[W];
+#pragma unroll
+  for (int q = 0; q < W; ++q) off[q] = (4 * q + lg) / W * span + (4 * q + lg) % W + xw + li;
   __syncthreads();
-  auto block = [&](int cb, const float (&av)[W]) {
-    const float *xr = Xs + cb * span;
+  for (int cb = 0; cb < cin4; cb += 16) {
+    load_a(cb + 16, an);
 #pragma unroll
-    for (int q = 0; q < W; ++q)
+    for (int u = 0; u < 4; ++u) {
+      if (cb + 4 * u >= cin4) break;
+      const float *xr = Xs + (cb + 4 * u) * span;
 #pragma unroll
-      for (int t = 0; t < NT; ++t)
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q], xr[off[q] + 16 * t], acc[t], 0, 0, 0);
-  };
-  for (int cb = 0; cb < cin4; cb += 8) {
-    load_a(cb + 4, a[1]);  // (zeros past the last channel)
-    block(cb, a[0]);
-    if (cb + 4 >= cin4) break;
-    load_a(cb + 8, a[0]);
-    block(cb + 4, a[1]);
+      for (int q = 0; q < W; ++q)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+          acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[(u * W + q) / 4][(u * W + q) % 4],
+                                                        xr[off[q] + 16 * t], acc[t], 0, 0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < W; ++q) a[q] = an[q];
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -314,7 +351,8 @@ __global__ void __launch_bounds__(256)
 
 __global__ void adam_kernel(long long count, float *__restrict__ p, const float *__restrict__ g,
                             float *__restrict__ m, float *__restrict__ v, float lr, float b1,
-                            float b2, float eps, float c1, float c2) {
+                            float b2, float eps, float c1, float c2, Frag fm,
+                            float *__restrict__ frag) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
   const float gi = g[i];
@@ -322,7 +360,9 @@ __global__ void adam_kernel(long long count, float *__restrict__ p, const float 
   const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
   m[i] = mi;
   v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  p[i] = pi;
+  frag_put(fm, i, pi, frag);
 }
 
 __global__ void f2d_kernel(long long count, const float *__restrict__ a, double *__restrict__ b) {
@@ -396,6 +436,9 @@ struct riot_net {
   long long nparams = 0;
   std::vector<long long> woff, boff;  // per layer offsets into the flat parameters
   std::vector<int> cin, cout;
+  riot::Frag fm{};                    // the weights in operand order: follow params
+  float *frag = nullptr;
+  size_t nfrag = 0;
   float *params = nullptr, *grads = nullptr, *am = nullptr, *av = nullptr;
   float *x0 = nullptr;               // standardized inputs [batch][in_channels][n]
   std::vector<float *> acts;         // per layer outputs [batch][cout][n]
@@ -482,6 +525,17 @@ size_t net_carve(riot_net &h, void *base) {
   const size_t B = d.batch_max, n = d.n, k = d.k, kk = (size_t)k * k;
   h.params = c.take<float>(np);
   h.grads = c.take<float>(np);
+  h.fm.layers = d.layers, h.fm.width = d.width;
+  long long nf = 0;
+  for (int l = 0; l < d.layers; ++l) {
+    h.fm.cin[l] = h.cin[l], h.fm.cout[l] = h.cout[l], h.fm.woff[l] = h.woff[l];
+    h.fm.fwd[l] = nf;
+    nf += riot::frag_floats(h.cin[l], h.cout[l], d.width);
+    h.fm.bwd[l] = nf;
+    if (l > 0) nf += riot::frag_floats(h.cout[l], h.cin[l], d.width);
+  }
+  h.nfrag = nf;
+  h.frag = c.take<float>(nf);
   h.am = c.take<float>(np);
   h.av = c.take<float>(np);
   h.x0 = c.take<float>(B * d.in_channels * n);
@@ -523,11 +577,11 @@ size_t net_carve(riot_net &h, void *base) {
     if ((call) != hipSuccess) return RIOT_E_HIP; \
   } while (0)
 
-// Convolution of `batch` samples: the forward layer (W, b; ReLU when relu), or with act the
+// Convolution of `batch` samples: the forward layer (weights in operand order, b; ReLU when relu), or with act the
 // backward-data pass of a layer cout -> cin. Grid points per wave: the most (64, 32, 16) that
 // leave two workgroups per compute unit, since the weights are read once per workgroup.
 template <int W, bool FLIP>
-void launch_conv(riot_net *h, int batch, const float *in, int cin, int cout, const float *Wt,
+void launch_conv(riot_net *h, int batch, const float *in, int cin, int cout, const float *wf,
                  const float *b, const float *act, float *out, bool relu) {
   const int n = h->d.n, cgs = cout > 32 ? 4 : (cout > 16 ? 2 : 1), xw = 4 / cgs;
   int nt = std::min(4, 4 / xw);
@@ -537,7 +591,7 @@ void launch_conv(riot_net *h, int batch, const float *in, int cin, int cout, con
   const dim3 grid(n / XT, batch);
 #define RIOT_CONV(NT_)                                                                          \
   hipLaunchKernelGGL((riot::conv_kernel<W, NT_, FLIP>), grid, dim3(256), lds, h->st, n, cin, cout, \
-                     cgs, in, Wt, b, act, out, relu ? 1 : 0)
+                     cgs, in, wf, b, act, out, relu ? 1 : 0)
   if (nt == 4)
     RIOT_CONV(4);
   else if (nt == 2)
@@ -638,6 +692,7 @@ riot_status riot_net_init(const riot_net_desc *desc, void *workspace, size_t byt
                      h->st) != hipSuccess ||
       hipMemcpyAsync(h->trsm_jobs, tj.data(), B * sizeof(riot::TrsmJob), hipMemcpyHostToDevice,
                      h->st) != hipSuccess ||
+      hipMemsetAsync(h->frag, 0, h->nfrag * sizeof(float), h->st) != hipSuccess ||
       hipStreamSynchronize(h->st) != hipSuccess)
     rs = RIOT_E_HIP;
   if (rs != RIOT_OK) {
@@ -654,9 +709,13 @@ int64_t riot_net_param_count(const riot_net *h) { return h ? h->nparams : 0; }
 
 riot_status riot_net_set_params(riot_net *h, const float *params, const float *grads) {
   if (!h) return RIOT_E_ARG;
-  if (params)
+  if (params) {
     NET_HIP(hipMemcpyAsync(h->params, params, h->nparams * sizeof(float),
                            hipMemcpyDeviceToDevice, h->st));
+    hipLaunchKernelGGL(riot::frag_kernel, dim3(riot::nblocks(h->nparams)), dim3(256), 0, h->st,
+                       (long long)h->nparams, h->fm, h->params, h->frag);
+    NET_HIP(hipGetLastError());
+  }
   if (grads)
     NET_HIP(hipMemcpyAsync(h->grads, grads, h->nparams * sizeof(float), hipMemcpyDeviceToDevice,
                            h->st));
@@ -686,7 +745,7 @@ riot_status riot_net_forward(riot_net *h, int32_t batch, const double *x, float 
   for (int l = 0; l < h->d.layers; ++l) {
     const bool last = l == h->d.layers - 1;
     float *out = h->acts[l];
-    riot_status rs = conv_forward(h, batch, in, h->cin[l], h->cout[l], h->params + h->woff[l],
+    riot_status rs = conv_forward(h, batch, in, h->cin[l], h->cout[l], h->frag + h->fm.fwd[l],
                                   h->params + h->boff[l], out, !last);
     if (rs != RIOT_OK) return rs;
     in = out;
@@ -714,7 +773,7 @@ riot_status riot_net_backward(riot_net *h, int32_t batch, const float *gN) {
     riot_status rs = weight_grad(h, batch, ci, co, g, hin, h->grads + h->woff[l]);
     if (rs != RIOT_OK) return rs;
     if (l > 0) {
-      rs = conv_backward_data(h, batch, g, co, ci, h->params + h->woff[l], h->acts[l - 1], gnext);
+      rs = conv_backward_data(h, batch, g, co, ci, h->frag + h->fm.bwd[l], h->acts[l - 1], gnext);
       if (rs != RIOT_OK) return rs;
       std::swap(g, gnext);
     }
@@ -731,7 +790,7 @@ riot_status riot_net_adam(riot_net *h, float lr, float beta1, float beta2, float
   }
   hipLaunchKernelGGL(riot::adam_kernel, dim3(riot::nblocks(h->nparams)), dim3(256), 0, h->st,
                      (long long)h->nparams, h->params, h->grads, h->am, h->av, lr, beta1, beta2,
-                     eps, c1, c2);
+                     eps, c1, c2, h->fm, h->frag);
   NET_HIP(hipGetLastError());
   return RIOT_OK;
 }
