@@ -1,7 +1,7 @@
 // Symmetric eigen-solver for the m x m matrix K of the randomized eigendecomposition
 // (Alg. 3: K = Z Lambda Z^T), FP64, for gfx950.
 //
-//  1. Householder tridiagonalisation Q^T K Q = T (one workgroup; reflectors kept).
+//  1. Householder tridiagonalisation Q^T K Q = T (reflectors kept).
 //  2. Root representation: T - sigma I = L D L^T positive definite, sigma just below
 //     the smallest eigenvalue (found by bisection with Sturm counts).
 //  3. Eigenvalues of L D L^T to high relative accuracy: one wave per eigenvalue,
@@ -61,273 +61,12 @@ struct EigLayout {
   }
 };
 
-constexpr int kTriThreads = 512;
 constexpr int kEigMaxM = 1088;  // largest m of the eigen-solver
 
 // ---------------------------------------------------------------------------
-// 1. Householder tridiagonalisation (full storage, one workgroup).
+// 1. Householder tridiagonalisation.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kTriThreads)
-    tridiag_kernel(int m, const double *__restrict__ K, double *__restrict__ work,
-                   const EigJob *__restrict__ jobs) {
-  if (jobs) m = jobs[blockIdx.y].m, K = jobs[blockIdx.y].K, work = jobs[blockIdx.y].work;
-  extern __shared__ double sh[];
-  EigLayout Lw(m);
-  double *Aw = work + Lw.Aw, *Hv = work + Lw.Hv, *dg = work + Lw.d, *eg = work + Lw.e;
-  double *vs = sh, *ps = sh + m, *part = sh + 2 * m;
-  __shared__ double red[16];
-  const int tid = threadIdx.x, nt = blockDim.x;
-  for (size_t idx = tid; idx < (size_t)m * m; idx += nt) {
-    Aw[idx] = K[idx];
-    Hv[idx] = 0.0;
-  }
-  __syncthreads();
-  for (int k = 0; k + 2 < m; ++k) {
-    const int R = m - k - 1;
-    double part_s = 0.0;
-    for (int i = tid; i < R; i += nt) {
-      const double x = Aw[(size_t)k * m + k + 1 + i];
-      vs[i] = x;
-      part_s += x * x;
-    }
-    const double sig2 = wsum(part_s, red);
-    const double sig = sqrt(sig2);
-    const double x0 = vs[0];
-    __syncthreads();
-    if (sig == 0.0) {
-      if (tid == 0) {
-        dg[k] = Aw[(size_t)k * m + k];
-        eg[k] = 0.0;
-      }
-      __syncthreads();
-      continue;
-    }
-    const double alpha = (x0 >= 0.0) ? -sig : sig;
-    const double vn = sqrt(2.0 * (sig2 - alpha * x0));
-    if (tid == 0) vs[0] = x0 - alpha;
-    __syncthreads();
-    for (int i = tid; i < R; i += nt) {
-      const double v = vs[i] / vn;
-      vs[i] = v;
-      Hv[(size_t)k * m + k + 1 + i] = v;
-    }
-    __syncthreads();
-    // p = S v: thread groups split the column range of each row
-    const int groups = max(1, nt / R);
-    if (R <= nt) {
-      const int i = tid % R, g = tid / R;
-      double acc = 0.0;
-      if (g < groups)
-        for (int j = g; j < R; j += groups)
-          acc += Aw[(size_t)(k + 1 + j) * m + (k + 1 + i)] * vs[j];
-      if (tid < R * groups) part[tid] = acc;
-      __syncthreads();
-      for (int ii = tid; ii < R; ii += nt) {
-        double s = 0.0;
-        for (int gg = 0; gg < groups; ++gg) s += part[gg * R + ii];
-        ps[ii] = s;
-      }
-    } else {
-      for (int i = tid; i < R; i += nt) {
-        double s = 0.0;
-        for (int j = 0; j < R; ++j) s += Aw[(size_t)(k + 1 + j) * m + (k + 1 + i)] * vs[j];
-        ps[i] = s;
-      }
-    }
-    __syncthreads();
-    double kp = 0.0;
-    for (int i = tid; i < R; i += nt) kp += vs[i] * ps[i];
-    const double Kv = wsum(kp, red);
-    for (int i = tid; i < R; i += nt) ps[i] = ps[i] - Kv * vs[i];
-    __syncthreads();
-    const size_t tot = (size_t)R * R;
-    for (size_t idx = tid; idx < tot; idx += nt) {
-      const int i = (int)(idx % R), j = (int)(idx / R);
-      Aw[(size_t)(k + 1 + j) * m + (k + 1 + i)] -= 2.0 * (vs[i] * ps[j] + ps[i] * vs[j]);
-    }
-    if (tid == 0) {
-      dg[k] = Aw[(size_t)k * m + k];
-      eg[k] = alpha;
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    if (m >= 2) {
-      dg[m - 2] = Aw[(size_t)(m - 2) * m + m - 2];
-      dg[m - 1] = Aw[(size_t)(m - 1) * m + m - 1];
-      eg[m - 2] = Aw[(size_t)(m - 2) * m + m - 1];
-    } else {
-      dg[0] = Aw[0];
-    }
-    eg[m - 1] = 0.0;
-  }
-}
 
-// Grid variant, for m beyond the register tiles: a persistent grid of kTriGridWG workgroups
-// and two grid-wide barriers per step. Workgroup g owns a contiguous block of columns of
-// the symmetric working matrix (full storage in Aw) for the rank-2 updates and a contiguous
-// block of the trailing rows for the product p = S v. Step k:
-//   every workgroup forms the reflector v of column k itself (the same data and the same
-//   reduction order everywhere, so all hold the same v); workgroup 0 stores it;
-//   p = S v by row blocks (reads of S coalesced along its columns) and the block's share
-//   of v^T p into a per-workgroup slot;                                   -- barrier
-//   w = p - (v^T p) v with v^T p summed over the slots in order, and the rank-2 update
-//   S -= 2 (v w^T + w v^T) of the owned columns;                          -- barrier
-// A barrier is a release fence and an arrival on a counter (cleared before the launch), then
-// acquire polls until every workgroup of this barrier has arrived; the polls are bounded, and
-// a workgroup that gives up raises an abort word the others see and the eigen-solver's flag.
-constexpr int kTriGridWG = 64;
-constexpr int kTriGridThreads = 256;
-constexpr int kTriGridMaxPolls = 1 << 22;
-
-__device__ bool grid_barrier(int *ctr, int *abort_w, int target, int *ok_lds) {
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __hip_atomic_fetch_add(ctr, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    int polls = 0, ok = 1;
-    while (__hip_atomic_load(ctr, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < target) {
-      if (__hip_atomic_load(abort_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ||
-          ++polls > kTriGridMaxPolls) {
-        __hip_atomic_store(abort_w, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ok = 0;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-    *ok_lds = ok;
-  }
-  __syncthreads();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  return *ok_lds != 0;
-}
-
-__global__ void __launch_bounds__(kTriGridThreads)
-    tridiag_grid_kernel(int m, const double *__restrict__ K, double *__restrict__ work,
-                        int *__restrict__ gsync, int *__restrict__ flag) {
-  EigLayout Lw(m);
-  double *Aw = work + Lw.Aw, *Hv = work + Lw.Hv, *dg = work + Lw.d, *eg = work + Lw.e;
-  double *pg = work + Lw.scr, *partg = pg + m;  // p, and the per-workgroup shares of v^T p
-  int *const ctr = gsync, *const abort_w = gsync + 1;
-  __shared__ double vs[kEigMaxM];
-  __shared__ double red[16];
-  __shared__ double psum[kTriGridThreads];
-  __shared__ int ok;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int G = gridDim.x, g = blockIdx.x;
-  const int cper = (m + G - 1) / G, clo = min(m, g * cper), chi = min(m, clo + cper);
-  int nbar = 0;
-  // copy of K (owned columns) and cleared reflector columns
-  for (int j = clo; j < chi; ++j)
-    for (int i = tid; i < m; i += nt) {
-      Aw[(size_t)j * m + i] = K[(size_t)j * m + i];
-      Hv[(size_t)j * m + i] = 0.0;
-    }
-  if (!grid_barrier(ctr, abort_w, ++nbar * G, &ok)) {
-    if (tid == 0) flag[0] = 1;
-    return;
-  }
-  for (int k = 0; k + 2 < m; ++k) {
-    const int R = m - k - 1, r0 = k + 1;
-    // reflector of column k, in every workgroup
-    double part = 0.0;
-    for (int i = tid; i < R; i += nt) {
-      const double x = Aw[(size_t)k * m + r0 + i];
-      vs[i] = x;
-      part += x * x;
-    }
-    const double sig2 = wsum(part, red);
-    const double sig = sqrt(sig2);
-    const double x0 = vs[0];
-    __syncthreads();
-    if (sig == 0.0) {  // column already reduced: no reflector, S unchanged
-      if (g == 0 && tid == 0) {
-        dg[k] = Aw[(size_t)k * m + k];
-        eg[k] = 0.0;
-      }
-      continue;
-    }
-    const double alpha = (x0 >= 0.0) ? -sig : sig;
-    const double vn = sqrt(2.0 * (sig2 - alpha * x0));
-    if (tid == 0) vs[0] = x0 - alpha;
-    __syncthreads();
-    for (int i = tid; i < R; i += nt) {
-      const double v = vs[i] / vn;
-      vs[i] = v;
-      if (g == 0) Hv[(size_t)k * m + r0 + i] = v;
-    }
-    if (g == 0 && tid == 0) {
-      dg[k] = Aw[(size_t)k * m + k];
-      eg[k] = alpha;
-    }
-    __syncthreads();
-    // p = S v for this workgroup's rows: thread (row, column group), groups summed in order
-    const int rper = (R + G - 1) / G, rlo = min(R, g * rper), nr = min(R, rlo + rper) - rlo;
-    double vp = 0.0;
-    if (nr > 0) {
-      const int ngrp = max(1, nt / nr), ri = tid % nr, cg = tid / nr;
-      double acc = 0.0;
-      if (cg < ngrp)
-        for (int j = cg; j < R; j += ngrp) acc += Aw[(size_t)(r0 + j) * m + r0 + rlo + ri] * vs[j];
-      psum[tid] = (cg < ngrp) ? acc : 0.0;
-      __syncthreads();
-      if (tid < nr) {
-        double sacc = 0.0;
-        for (int c = 0; c < ngrp; ++c) sacc += psum[c * nr + tid];
-        pg[r0 + rlo + tid] = sacc;
-        vp = sacc * vs[rlo + tid];
-      }
-    }
-    const double vps = wsum(vp, red);
-    if (tid == 0) partg[g] = vps;
-    if (!grid_barrier(ctr, abort_w, ++nbar * G, &ok)) break;
-    // w = p - (v^T p) v, and the rank-2 update of the owned columns within the trailing block
-    double Kv = 0.0;
-    for (int q = 0; q < G; ++q) Kv += partg[q];
-    const int jlo = max(clo, r0);
-    for (int j = jlo; j < chi; ++j) {
-      const double vj = vs[j - r0];
-      const double wj = pg[j] - Kv * vj;
-      for (int i = tid; i < R; i += nt) {
-        const double vi = vs[i];
-        const double wi = pg[r0 + i] - Kv * vi;
-        Aw[(size_t)j * m + r0 + i] -= 2.0 * (vi * wj + wi * vj);
-      }
-    }
-    if (!grid_barrier(ctr, abort_w, ++nbar * G, &ok)) break;
-  }
-  if (__hip_atomic_load(abort_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-    if (tid == 0) flag[0] = 1;
-    return;
-  }
-  if (g == 0 && tid == 0) {
-    if (m >= 2) {
-      dg[m - 2] = Aw[(size_t)(m - 2) * m + m - 2];
-      dg[m - 1] = Aw[(size_t)(m - 1) * m + m - 1];
-      eg[m - 2] = Aw[(size_t)(m - 2) * m + m - 1];
-    } else {
-      dg[0] = Aw[0];
-    }
-    eg[m - 1] = 0.0;
-  }
-}
-
-// Register-tile variant. The lower triangle of K is cut into 9 x 9 tiles (R, C), R >= C, one
-// tile per lane (81 FP64 registers); diagonal tiles hold the full symmetric block. Lanes are
-// ordered by tile column, then tile row, so whole waves fall idle as the reduction moves
-// right. Every sum is taken in a fixed order (no atomics), so the result
-// is the same bit for bit on every run. Step k of the reduction is three phases and three
-// barriers:
-//   phase 1  apply the pending rank-2 update of step k-1, with w = p - (v^T p) v formed per lane
-//            from v and p of step k-1, and gather column k and the partial |x|^2; the block
-//            stores reflector k-1 to global memory;
-//   phase 2  every lane forms the Householder scalars from |x|^2 (the column-block tiles' parts,
-//            one slot per tile row, summed in order) and x_{k+1} and its own slices of v (rows
-//            and columns of its tile), and writes its tile's share of p = A v (row sums and, off
-//            the diagonal, column sums) into the slot of its partner block; each wave reduces
-//            its lanes' shares of v^T A v by a fixed shuffle tree; the diagonal lanes store v;
-//   phase 3  p[i] = the sum of its slots over the active partner blocks, in a fixed order.
-// v, p and v^T p are double-buffered by step parity.
 // Sum over the wave, returned to every lane (the same value, bit for bit, in every wave for the
 // same inputs): DPP adds within each row of 16 lanes (quad_perm [1,0,3,2] and [2,3,0,1],
 // half-row mirror, row mirror), then row_bcast:15 and row_bcast:31 carry the row sums up to
@@ -351,8 +90,334 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+// Row variant: one exchange per step. The matrix S is held in registers by rows (full storage),
+// RPW rows per wave, lane l of a wave holding columns l, l + 64, .... Step k needs column k of
+// S_k = S_{k-1} - 2 (v w^T + w v^T), w = p - (v^T p) v, from the reflector v and the product
+// p = S v of step k - 1; what the rows' owners publish at the end of step k - 1 is therefore
+// p_i and the next column's S_{k-1}[i][k], and every wave then forms v^T p, w, column k of S_k
+// and the new reflector by itself, in the same order everywhere (so all hold the same bits),
+// updates its rows and takes their products with the new reflector.
+//
+// LOCAL (GRID = false): one workgroup, exchange in LDS, one barrier per step.
+// GRID: a workgroup per 4 RPW rows, exchange through global memory. Each published value has a
+// place of its own (step k's 2 (m - 1 - k) values from k (2 m - 1 - k) on, m (m - 1) in all),
+// which holds kUnset until the value is there: the readers poll the values themselves, so there
+// is neither a flag nor a fence nor a barrier, and nothing of S leaves the registers. A
+// workgroup whose rows are done leaves; the last one has no rows and writes the reflectors and
+// the tridiagonal, off the others' path. The polls are bounded; a wave that gives up raises an
+// abort word the others see and the eigen-solver's flag.
+// Bound by the latency of the exchange and the chain of two wave sums, a square root and its
+// reciprocal: 1.5 us a step within one workgroup (m <= 64), 1.8 us (m = 65 .. 128), 2.5 us
+// (m = 272) and 2.9 us (m = 512) over a grid. Before, a grid with S in memory and two barriers
+// per step took 24 us a step (m = 512: 12.5 ms, now 1.46 ms), and one workgroup with S in
+// register tiles and three barriers 4 us (m = 272: 1.07 ms, now 0.69 ms; m = 30: 104 us, now
+// 46 us). Within one workgroup every wave repeats the vector work, which fills the SIMDs from
+// m = 65 on (3 us a step).
+constexpr unsigned long long kUnset = 0x7ff4dead5eedbeefull;  // a signalling NaN: no result is
+constexpr int kTriMaxPolls = 1 << 22;
+constexpr int kRowsLocalMaxM = 64;
 
+__global__ void fill_unset_kernel(long long count, unsigned long long *__restrict__ p) {
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count;
+       i += (long long)gridDim.x * blockDim.x)
+    p[i] = kUnset;
+}
+
+// x[q] of q known only at run time (uniform)
+template <int NC>
+__device__ __forceinline__ double pick(const double (&x)[NC], int q) {
+  double r = x[0];
+#pragma unroll
+  for (int i = 1; i < NC; ++i) {
+    double v = x[i];
+    asm("" : "+v"(v));  // a selected value, not a selected address (which puts x in memory)
+    r = (q == i) ? v : r;
+  }
+  return r;
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// a value that is the same in every lane, kept in scalar registers
+__device__ __forceinline__ double uniform(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
+// The wave's sums of N values per lane (N = 2, 4 or 8): the result of value j in the lanes with
+// lane % N = j. Each halving sends the half of the values that other lanes collect (N + 3 adds
+// and moves fewer than N separate sums of six steps each).
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) { return dpp_add_src<CTRL, 0xf>(v); }
+template <int N, int CTRL, int BIT>
+__device__ __forceinline__ void fold_half(double *v, int lane) {
+  const bool up = lane >> BIT & 1;
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) {
+    const double lo = v[i], hi = v[i + N / 2];
+    v[i] = (up ? hi : lo) + dpp_move<CTRL>(up ? lo : hi);
+  }
+}
+template <int N>
+__device__ __forceinline__ double wave_fold(double (&v)[N], int lane) {
+  if (N >= 8) fold_half<8, 0x141, 2>(v, lane);                   // row_half_mirror
+  if (N >= 4) fold_half<4, 0x4E, 1>(v, lane);                    // quad_perm [2, 3, 0, 1]
+  fold_half<2, 0xB1, 0>(v, lane);                                // quad_perm [1, 0, 3, 2]
+  double s = v[0];
+  if (N <= 2) s += dpp_move<0x122>(s);                           // row_ror:2
+  if (N <= 4) s += dpp_move<0x124>(s);                           // row_ror:4
+  s += dpp_move<0x128>(s);                                       // row_ror:8
+  const unsigned lo = __double2loint(s), hi = __double2hiint(s);
+  u32x2_t a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  u32x2_t b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  s = __hiloint2double(b.x, a.x) + __hiloint2double(b.y, a.y);
+  const unsigned lo2 = __double2loint(s), hi2 = __double2hiint(s);
+  a = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
+  b = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
+  return __hiloint2double(b.x, a.x) + __hiloint2double(b.y, a.y);
+}
+
+template <int NC, int RPW, int NW, bool GRID>
+__global__ void __launch_bounds__(64 * NW)
+    tridiag_rows_kernel(int m, const double *__restrict__ K, double *__restrict__ work,
+                        int *__restrict__ abort_w, int *__restrict__ flag,
+                        const EigJob *__restrict__ jobs) {
+  if (jobs) m = jobs[blockIdx.y].m, K = jobs[blockIdx.y].K, work = jobs[blockIdx.y].work;
+  EigLayout Lw(m);
+  double *Hv = work + Lw.Hv, *dg = work + Lw.d, *eg = work + Lw.e;
+  unsigned long long *xg = reinterpret_cast<unsigned long long *>(work + Lw.Aw);
+  constexpr int kX = 2 * 64 * NC, kPoll = kX / (64 * NW) + 1;
+  __shared__ double buf[2][kX];
+  __shared__ int ok;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // rows: dealt in turn to the waves of one workgroup, in blocks over a grid
+  auto row = [&](int j) {
+    return GRID ? ((int)blockIdx.x * NW + wave) * RPW + j : wave + NW * j;
+  };
+  const bool recorder = GRID ? (blockIdx.x == gridDim.x - 1 && wave == 0) : wave == NW - 1;
+  // the last step of this workgroup: after it none of its rows is left
+  int last = m - 1;
+  if (GRID && blockIdx.x != gridDim.x - 1) {
+    const int hi = (int)(blockIdx.x + 1) * NW * RPW - 1;
+    if (hi < m - 1) last = hi - 1;
+  }
+  double S[RPW][NC], vr[RPW], vc[NC], x[NC];
+#pragma unroll
+  for (int j = 0; j < RPW; ++j) {
+    const int r = row(j);
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const int c = lane + 64 * q;
+      // the lower triangle of K
+      S[j][q] = (r < m && c < m) ? K[(size_t)min(r, c) * m + max(r, c)] : 0.0;
+    }
+    vr[j] = r < m ? K[r] : 0.0;  // column 0 (x of step 0)
+  }
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    const int c = lane + 64 * q;
+    x[q] = c < m ? K[c] : 0.0;
+    vc[q] = 0.0;
+  }
+  if (tid == 0) ok = 1;
+  double vhead = 0.0;
+  for (int k = 0; k <= last; ++k) {
+    if (k > 0) {
+      // p and column k of S_{k-1}, entries k .. m - 1 each
+      const int R = m - k;
+      double *b = buf[k & 1];
+      if (GRID) {
+        const unsigned long long *src = xg + (size_t)(k - 1) * (2 * m - k);
+        unsigned long long v[kPoll];
+#pragma unroll
+        for (int e = 0; e < kPoll; ++e) {
+          const int i = tid + 64 * NW * e;
+          v[e] = i < 2 * R ? __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                           : 0ull;
+        }
+        int polls = 0;
+        for (;;) {
+          bool wait = false;
+#pragma unroll
+          for (int e = 0; e < kPoll; ++e) wait |= v[e] == kUnset;
+          if (!wait) break;
+          if (++polls > kTriMaxPolls ||
+              ((polls & 255) == 0 &&
+               __hip_atomic_load(abort_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+            __hip_atomic_store(abort_w, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            ok = 0;
+            break;
+          }
+#pragma unroll
+          for (int e = 0; e < kPoll; ++e)
+            if (v[e] == kUnset)
+              v[e] = __hip_atomic_load(src + tid + 64 * NW * e, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int e = 0; e < kPoll; ++e) {
+          const int i = tid + 64 * NW * e;
+          if (i < 2 * R) b[i] = __longlong_as_double((long long)v[e]);
+        }
+      }
+      __syncthreads();
+      if (GRID && !ok) break;
+      const double *pl = b - k, *cl = b + R - k;  // by row index
+      double pc[NC], kp = 0.0;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int c = lane + 64 * q;
+        const bool in = c >= k && c < m;
+        pc[q] = in ? pl[in ? c : k] : 0.0;
+        x[q] = in ? cl[in ? c : k] : 0.0;
+        kp = fma(vc[q], pc[q], kp);
+      }
+      const double Kv = wave_sum_dpp(kp);
+      const double wk = 2.0 * (pl[k] - Kv * vhead), vk = vhead;
+      // w is doubled from here on
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        pc[q] = 2.0 * (pc[q] - Kv * vc[q]);
+        x[q] = fma(-vk, pc[q], fma(-wk, vc[q], x[q]));
+      }
+#pragma unroll
+      for (int j = 0; j < RPW; ++j) {
+        // (a grid's workgroup leaves soon after its first row is done, and what its finished rows
+        // hold is not used: no branch there)
+        const int r = GRID ? min(max(row(j), k), m - 1) : row(j);
+        if (!GRID && (r < k || r >= m)) continue;
+        const double wr = 2.0 * (pl[r] - Kv * vr[j]);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) S[j][q] = fma(-vr[j], pc[q], fma(-wr, vc[q], S[j][q]));
+        vr[j] = uniform(fma(-vk, wr, fma(-wk, vr[j], cl[r])));  // x_r
+      }
+    }
+    const double dk = lane_value(pick(x, k >> 6), k & 63);
+    const double x0 = lane_value(pick(x, (k + 1) >> 6), (k + 1) & 63);
+    if (k >= m - 2) {  // the last columns: no reflector
+      if (recorder) {
+        if (k == m - 2) {
+          if (lane == 0) dg[k] = dk, eg[k] = x0;
+        } else if (m == 1 && lane == 0) {
+          dg[0] = dk;
+        }
+        if (lane == 0) eg[m - 1] = 0.0;
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+          const int c = lane + 64 * q;
+          if (c < m) Hv[(size_t)k * m + c] = 0.0, Hv[(size_t)(m - 1) * m + c] = 0.0;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < RPW; ++j) {
+        const double dl = pick(S[j], (m - 1) >> 6);
+        if (m >= 2 && row(j) == m - 1 && lane == ((m - 1) & 63)) dg[m - 1] = dl;
+      }
+      break;
+    }
+    // reflector of column k
+    double s2 = 0.0;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const double y = lane + 64 * q > k ? x[q] : 0.0;
+      s2 = fma(y, y, s2);
+    }
+    const double sig2 = wave_sum_dpp(s2);
+    const double sig = sqrt(sig2), alpha = x0 >= 0.0 ? -sig : sig;
+    // (a column already reduced: no reflector, v = 0)
+    const double inv = sig == 0.0 ? 0.0 : rsqrt(2.0 * (sig2 - alpha * x0));
+    vhead = (x0 - alpha) * inv;
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const int c = lane + 64 * q;
+      vc[q] = c > k + 1 ? x[q] * inv : (c == k + 1 ? vhead : 0.0);
+    }
+    // the rows' products and column k + 1, published
+    const int R = m - 1 - k, q1 = (k + 1) >> 6, l1 = (k + 1) & 63;
+    double *b = buf[(k + 1) & 1];
+    unsigned long long *dst = xg + (size_t)k * (2 * m - 1 - k);
+    double p[RPW];
+#pragma unroll
+    for (int j = 0; j < RPW; ++j) {
+      const int r = row(j);
+      vr[j] = uniform(r > k + 1 ? vr[j] * inv : (r == k + 1 ? vhead : 0.0));
+      p[j] = 0.0;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) p[j] = fma(S[j][q], vc[q], p[j]);
+      const double cv = pick(S[j], q1);
+      if (lane == l1 && r > k && r < m) {
+        if (GRID)
+          __hip_atomic_store(dst + R + r - k - 1, (unsigned long long)__double_as_longlong(cv),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          b[R + r - k - 1] = cv;
+      }
+    }
+    const double ps = wave_fold(p, lane);
+    const int r = row(lane % RPW);
+    if (lane < RPW && r > k && r < m) {
+      if (GRID)
+        __hip_atomic_store(dst + r - k - 1, (unsigned long long)__double_as_longlong(ps),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        b[r - k - 1] = ps;
+    }
+    if (recorder) {
+      if (lane == 0) dg[k] = dk, eg[k] = sig == 0.0 ? 0.0 : alpha;
+#pragma unroll
+      for (int q = 0; q < NC; ++q) {
+        const int c = lane + 64 * q;
+        if (c < m) Hv[(size_t)k * m + c] = vc[q];
+      }
+    }
+  }
+  if (GRID) {
+    __syncthreads();
+    if (!ok && tid == 0) flag[0] = 1;
+  }
+}
+
+// One workgroup per problem of at most maxm <= kRowsLocalMaxM.
+void launch_tridiag_local(int nprob, int maxm, int m, const double *K, double *work,
+                          const EigJob *jobs, hipStream_t st) {
+#define RIOT_TRI_LOCAL(NC_, RPW_, NW_)                                                          \
+  hipLaunchKernelGGL((tridiag_rows_kernel<NC_, RPW_, NW_, false>), dim3(1, nprob), dim3(64 * NW_), \
+                     0, st, m, K, work, nullptr, nullptr, jobs)
+  if (maxm <= 32)
+    RIOT_TRI_LOCAL(1, 8, 4);
+  else
+    RIOT_TRI_LOCAL(1, 8, 8);
+#undef RIOT_TRI_LOCAL
+}
+
+// On a grid, m up to kEigMaxM: 8 rows per workgroup and one workgroup that records.
+template <int NC>
+void launch_tridiag_grid(int m, const double *K, double *work, int *abort_w, int *flag,
+                         hipStream_t st) {
+  hipLaunchKernelGGL((tridiag_rows_kernel<NC, 2, 4, true>), dim3((m + 7) / 8 + 1), dim3(256), 0, st,
+                     m, K, work, abort_w, flag, nullptr);
+}
+
+// Register-tile variant. The lower triangle of K is cut into 9 x 9 tiles (R, C), R >= C, one
+// tile per lane (81 FP64 registers); diagonal tiles hold the full symmetric block. Lanes are
+// ordered by tile column, then tile row, so whole waves fall idle as the reduction moves
+// right. Every sum is taken in a fixed order (no atomics), so the result
+// is the same bit for bit on every run. Step k of the reduction is three phases and three
+// barriers:
+//   phase 1  apply the pending rank-2 update of step k-1, with w = p - (v^T p) v formed per lane
+//            from v and p of step k-1, and gather column k and the partial |x|^2; the block
+//            stores reflector k-1 to global memory;
+//   phase 2  every lane forms the Householder scalars from |x|^2 (the column-block tiles' parts,
+//            one slot per tile row, summed in order) and x_{k+1} and its own slices of v (rows
+//            and columns of its tile), and writes its tile's share of p = A v (row sums and, off
+//            the diagonal, column sums) into the slot of its partner block; each wave reduces
+//            its lanes' shares of v^T A v by a fixed shuffle tree; the diagonal lanes store v;
+//   phase 3  p[i] = the sum of its slots over the active partner blocks, in a fixed order.
+// v, p and v^T p are double-buffered by step parity.
 constexpr int kTB = 9;
 constexpr int kTileMaxNb = 31;  // m <= 279
 constexpr int kTileMaxThreads = 512;
@@ -1677,16 +1742,26 @@ size_t eig_work_doubles(int m) { return EigLayout(m).total; }
 hipError_t launch_eig(int m, const double *K, double *lam, double *Z, double *work, int *flag,
                       hipStream_t st) {
   if (m < 1 || m > kEigMaxM) return hipErrorInvalidValue;
-  if (tile_fits(m))
-    hipLaunchKernelGGL(tridiag_tile_kernel, dim3(1), dim3(tile_threads(m)), 0, st, m, K, work,
-                       nullptr);
-  else {
-    // barrier counter and abort word after p and the workgroups' shares, cleared first
-    int *gsync = reinterpret_cast<int *>(work + EigLayout(m).scr + m + kTriGridWG);
-    hipError_t e0 = launch_zero_ints(gsync, 2, st);
+  if (m <= kRowsLocalMaxM) {
+    launch_tridiag_local(1, m, m, K, work, nullptr, st);
+  } else {
+    int *abort_w = reinterpret_cast<int *>(work + EigLayout(m).scr);
+    hipError_t e0 = launch_zero_ints(abort_w, 1, st);
     if (e0 != hipSuccess) return e0;
-    hipLaunchKernelGGL(tridiag_grid_kernel, dim3(kTriGridWG), dim3(kTriGridThreads), 0, st, m, K,
-                       work, gsync, flag);
+    hipLaunchKernelGGL(fill_unset_kernel, dim3(256), dim3(256), 0, st, (long long)m * (m - 1),
+                       reinterpret_cast<unsigned long long *>(work));
+    if (m <= 2 * 64)
+      launch_tridiag_grid<2>(m, K, work, abort_w, flag, st);
+    else if (m <= 3 * 64)
+      launch_tridiag_grid<3>(m, K, work, abort_w, flag, st);
+    else if (m <= 5 * 64)
+      launch_tridiag_grid<5>(m, K, work, abort_w, flag, st);
+    else if (m <= 8 * 64)
+      launch_tridiag_grid<8>(m, K, work, abort_w, flag, st);
+    else if (m <= 12 * 64)
+      launch_tridiag_grid<12>(m, K, work, abort_w, flag, st);
+    else
+      launch_tridiag_grid<17>(m, K, work, abort_w, flag, st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1711,8 +1786,12 @@ hipError_t launch_eig(int m, const double *K, double *lam, double *Z, double *wo
 hipError_t launch_eig_batched(int nprob, int maxm, const EigJob *jobs, hipStream_t st) {
   if (nprob <= 0) return hipSuccess;
   if (maxm < 1 || !tile_fits(maxm)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(tridiag_tile_kernel, dim3(1, nprob), dim3(tile_threads(maxm)), 0, st, 0,
-                     nullptr, nullptr, jobs);
+  // (the workgroups of many grids need not all be resident: one workgroup per problem)
+  if (maxm <= kRowsLocalMaxM)
+    launch_tridiag_local(nprob, maxm, 0, nullptr, nullptr, jobs, st);
+  else
+    hipLaunchKernelGGL(tridiag_tile_kernel, dim3(1, nprob), dim3(tile_threads(maxm)), 0, st, 0,
+                       nullptr, nullptr, jobs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(root_kernel, dim3(1, nprob), dim3(256), (size_t)4 * maxm * sizeof(double), st,
