@@ -685,7 +685,7 @@ riot_status riot_net_init(const riot_net_desc *desc, void *workspace, size_t byt
   for (int s = 0; s < B; ++s) {
     cj[s] = {k, h->G + s * kk, h->Lc + s * kk, 0.0, h->flags + 2 * s, h->flags + 2 * s + 1,
              nullptr, nullptr};
-    tj[s] = {k, k, h->Z + s * kk, k, h->Lc + s * kk, nullptr};
+    tj[s] = {k, k, h->Z + s * kk, k, h->Lc + s * kk, nullptr, nullptr};
   }
   riot_status rs = RIOT_OK;
   if (hipMemcpyAsync(h->chol_jobs, cj.data(), B * sizeof(riot::CholJob), hipMemcpyHostToDevice,

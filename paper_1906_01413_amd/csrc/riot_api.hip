@@ -1537,9 +1537,9 @@ riot_status batch_tables(riot_batch &b) {
     const double srelZ = 11.0 * ((double)m * m + (double)m * (m + 1)) * u;
     hQ[j] = {m, h.G, h.R, srelY, h.flags + 0, h.flags + 4, cq1, cq1 + 2};
     hZ[j] = {m, h.G, h.R, srelZ, h.flags + 1, h.flags + 4, cq2, cq2 + 2};
-    tQ[j] = {n, m, h.Q, n, h.R, cq1};
-    tZ[j] = {m, m, h.Zs, m, h.R, cq2};
-    t1[j] = {m, m, h.B1, m, h.R, cq2};
+    tQ[j] = {n, m, h.Q, n, h.R, cq1, h.partial};
+    tZ[j] = {m, m, h.Zs, m, h.R, cq2, h.partial};
+    t1[j] = {m, m, h.B1, m, h.R, cq2, h.partial};
     sy[j] = {m, h.K};
     eg[j] = {m, h.K, lam, h.Zs, h.sywork, h.flags + 2};
     ic[j] = {n, m, lam, V, h.cvec, g, b.Dz + b.off_n[j], h.scal + 4};
@@ -1609,10 +1609,12 @@ riot_status batch_cholqr(riot_batch &b, const riot::CqJob *cq, const riot::GemmJ
   RIOT_BHIP(riot::launch_cholqr_reset_batched(b.nprob, cq, st));
   for (int pass = 0; pass < 8; ++pass) {
     const bool sh = shifted && pass == 0;
-    RIOT_BHIP(riot::launch_gemm_batched(1, 0, b.nprob, b.maxm, b.maxm, 1.0, 0.0, gram, st));
+    RIOT_BHIP(riot::launch_gemm_batched(1, 0, b.nprob, b.maxm, b.maxm, 1.0, 0.0, gram, st, true));
     RIOT_BHIP(riot::launch_chol_batched(b.nprob, sh ? 1 : 2, ch, st));
-    RIOT_BHIP(riot::launch_trsm_batched(b.nprob, maxrows, tr, st));
-    if (comp) RIOT_BHIP(riot::launch_trsm_batched(b.nprob, b.maxm, comp, st));
+    // (X and its companion are solved with the same factor)
+    RIOT_BHIP(riot::launch_trsm_diag_inv_batched(b.nprob, b.maxm, tr, st));
+    RIOT_BHIP(riot::launch_trsm_rlt_inv_batched(b.nprob, maxrows, b.maxm, tr, st));
+    if (comp) RIOT_BHIP(riot::launch_trsm_rlt_inv_batched(b.nprob, b.maxm, b.maxm, comp, st));
     RIOT_BHIP(riot::launch_cholqr_ctrl_batched(b.nprob, sh ? 1 : 0, cq, st));
   }
   return RIOT_OK;

@@ -52,6 +52,7 @@ struct TrsmJob {
   int ldx;
   const double *L;
   const int *run;
+  double *dinv;  // inverses of L's diagonal blocks (the solves through them), or unused
 };
 struct CqJob {
   int *cq;
@@ -339,9 +340,14 @@ hipError_t gemm_f64_strided(int ta, int tb, int M, int N, int K, double alpha, c
 // Batched forms of the launches above (jobs: device array of nprob entries; max*: largest
 // size over the batch, which sets the grid).
 hipError_t launch_gemm_batched(int ta, int tb, int nprob, int maxM, int maxN, double alpha,
-                               double beta, const GemmJob *jobs, hipStream_t st);
+                               double beta, const GemmJob *jobs, hipStream_t st,
+                               bool lower = false);
 hipError_t launch_chol_batched(int nprob, int mode, const CholJob *jobs, hipStream_t st);
 hipError_t launch_trsm_batched(int nprob, int maxrows, const TrsmJob *jobs, hipStream_t st);
+// The same through the inverses of L's diagonal blocks, which the first fills (m <= 288).
+hipError_t launch_trsm_diag_inv_batched(int nprob, int maxm, const TrsmJob *jobs, hipStream_t st);
+hipError_t launch_trsm_rlt_inv_batched(int nprob, int maxrows, int maxm, const TrsmJob *jobs,
+                                       hipStream_t st);
 hipError_t launch_cholqr_reset_batched(int nprob, const CqJob *jobs, hipStream_t st);
 hipError_t launch_cholqr_ctrl_batched(int nprob, int pass_was_shifted, const CqJob *jobs,
                                       hipStream_t st);
