@@ -260,6 +260,105 @@ __global__ void __launch_bounds__(256)
       }
 }
 
+// A^T B over a long contraction (K), 64 x 64 of C per wave: 16 matrix-instruction tiles share
+// each operand, so that the wave needs neither LDS nor barriers: four columns' worth of loads a
+// chunk of 16 k, read along k as 16-byte pairs (within eight k, lanes l / 16 = g take k = 2 g and
+// 2 g + 1 for two instructions), R - 1 chunks ahead. One wave per SIMD fills the matrix pipes:
+// tiles times splits of K near 1024 waves. All tiles of a split run on one XCD (workgroup L on
+// XCD L % 8), whose L2 then serves the split's slices of A and B to all of them.
+// K = 65536, 512 columns: lower half 0.42 ms (46 TFLOP/s; the 64 x 64 LDS kernel 0.99 ms), both
+// projections 1.2 ms (57 TFLOP/s; 2.33 ms).
+template <bool LOWER, bool PAIR>
+__global__ void __launch_bounds__(64)
+    gemm_tn_wave64_kernel(int M, int N, int K, const double *__restrict__ A, int lda,
+                          const double *__restrict__ B, int ldb, int kchunk, int splits,
+                          double *__restrict__ partial, const int *__restrict__ run,
+                          const double *__restrict__ B2, int N1) {
+  typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
+  if (run && run[0] == 0) return;
+  const int tm = (M + 63) / 64, tn = (N + 63) / 64;
+  const int tiles = LOWER ? tm * (tm + 1) / 2 : tm * tn;
+  const int slot = blockIdx.x / kXcds;
+  int tt = slot % tiles;
+  const int kz = slot / tiles * kXcds + blockIdx.x % kXcds;
+  if (kz >= splits) return;
+  int bx, by;
+  if (LOWER) {
+    bx = 0;
+    while (tt > bx) tt -= ++bx;
+    by = tt;
+  } else {
+    bx = tt % tm, by = tt / tm;
+  }
+  const int m0 = bx * 64, n0 = by * 64;
+  const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4;
+  const int kbeg = kz * kchunk, kend = min(K, kbeg + kchunk);
+  // (columns past the last repeat it; their results are not stored)
+  gmem<const double> *a[4], *b[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    a[t] = gptr(A + (size_t)min(m0 + 16 * t + li, M - 1) * lda);
+    const int c = min(n0 + 16 * t + li, N - 1);
+    b[t] = gptr(PAIR && c >= N1 ? B2 + (size_t)(c - N1) * ldb : B + (size_t)c * ldb);
+  }
+  constexpr int R = 3;
+  pair_t av[R][4][2], bv[R][4][2];
+  auto load = [&](int k0, pair_t (&x)[4][2], pair_t (&y)[4][2]) {
+    if (k0 + 16 <= kend) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          x[t][s] = *reinterpret_cast<gmem<const pair_t> *>(a[t] + k0 + 8 * s + 2 * lg);
+          y[t][s] = *reinterpret_cast<gmem<const pair_t> *>(b[t] + k0 + 8 * s + 2 * lg);
+        }
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int k = k0 + 8 * s + 2 * lg + e;
+            x[t][s][e] = k < kend ? a[t][k] : 0.0;
+            y[t][s][e] = k < kend ? b[t][k] : 0.0;
+          }
+    }
+  };
+  d4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int c = 0; c < R - 1; ++c) load(kbeg + 16 * c, av[c], bv[c]);
+  for (int k0 = kbeg; k0 < kend; k0 += 16 * R)
+#pragma unroll
+    for (int c = 0; c < R; ++c) {
+      if (k0 + 16 * c >= kend) break;
+      load(k0 + 16 * (c + R - 1), av[(c + R - 1) % R], bv[(c + R - 1) % R]);
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c][i][s][e], bv[c][j][s][e],
+                                                               acc[i][j], 0, 0, 0);
+    }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = m0 + 16 * i + lg + 4 * r, col = n0 + 16 * j + li;
+        if (row < M && col < N) gptr(partial)[(size_t)kz * M * N + (size_t)col * M + row] = acc[i][j][r];
+      }
+}
+
 // ints after the Gram's partial sums of squares used by the multi-workgroup Cholesky: one
 // "panel published" flag per 32-column block, then the breakdown and modified words
 constexpr int kCholMaxBlocks = 48;  // 1088 / 32 = 34 blocks at the largest sketch
@@ -1437,6 +1536,148 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// The same solve for many rows, one wave per 32 rows, 64 columns at a time and without LDS. Both
+// the contraction and the product with a diagonal inverse are formed transposed (columns of X
+// along the rows of the result): result register s of lane l is then column 4 s + l / 16 and
+// row l % 16, which is just what the lane supplies as an operand of the next product, so solved
+// blocks go from registers into the following block's product and every lane reads back only
+// what it wrote itself. -X is the accumulators' start; operands come two chunks of 16 columns
+// ahead. n = 65536, m = 512: 0.41 ms, four waves per 32 rows with the partial sums in LDS 1.1 ms;
+// it needs a wave per SIMD (rows >= kWaveRows), below which those end sooner.
+constexpr int kWaveRows = 16384;
+
+__global__ void __launch_bounds__(64, 2)
+    trsm_rlt_inv_wave_kernel(int rows, int m, double *X, int ldx, const double *__restrict__ L,
+                             const double *__restrict__ dinv, const int *__restrict__ run,
+                             int rows2, double *X2, int ldx2) {
+  if (run && run[0] == 0) return;
+  const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4;
+  int r0 = blockIdx.x * 32;
+  const int nblk1 = (rows + 31) / 32;
+  if ((int)blockIdx.x >= nblk1) {  // a block of the second matrix
+    r0 = ((int)blockIdx.x - nblk1) * 32, rows = rows2, X = X2, ldx = ldx2;
+  }
+  if (r0 >= rows) return;
+  // lane offsets from a uniform column: this lane's rows (clamped; a clamped row's results are
+  // not stored)
+  unsigned xo[2];
+#pragma unroll
+  for (int rt = 0; rt < 2; ++rt)
+    xo[rt] = (unsigned)lg * ldx + min(r0 + 16 * rt + li, rows - 1);
+  auto xcol = [&](int c) { return gptr(X) + (size_t)c * ldx; };
+  auto lcol = [&](int k) { return gptr(L) + (size_t)k * m; };
+  const bool in0 = r0 + li < rows, in1 = r0 + 16 + li < rows;
+  constexpr int R = 2;
+  for (int c0 = 0; c0 < m; c0 += 64) {
+    const int nct = min(4, (m - c0 + 15) / 16);  // column tiles
+    d4 acc[4][2];
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int c = c0 + 16 * ct + 4 * s + lg;
+          double v = 0.0;
+          if (c < m) v = xcol(c0 + 16 * ct + 4 * s)[xo[rt]];
+          acc[ct][rt][s] = -v;
+        }
+    unsigned lo_[4];  // this lane's row of L per column tile
+#pragma unroll
+    for (int ct = 0; ct < 4; ++ct) lo_[ct] = (unsigned)lg * m + min(c0 + 16 * ct + li, m - 1);
+    double av[R][4][4], bv[R][2][4];
+    auto load = [&](int k0, double (&a)[4][4], double (&b)[2][4]) {
+      const int kc = min(k0, c0 - 16);  // (past the end: loaded, not used)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+#pragma unroll
+        for (int ct = 0; ct < 4; ++ct) a[ct][s] = lcol(kc + 4 * s)[lo_[ct]];
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) b[rt][s] = xcol(kc + 4 * s)[xo[rt]];
+      }
+    };
+    if (c0 > 0) {
+#pragma unroll
+      for (int c = 0; c < R - 1; ++c) load(16 * c, av[c], bv[c]);
+      for (int k0 = 0; k0 < c0; k0 += 16 * R)
+#pragma unroll
+        for (int c = 0; c < R; ++c) {
+          if (k0 + 16 * c >= c0) break;
+          load(k0 + 16 * (c + R - 1), av[(c + R - 1) % R], bv[(c + R - 1) % R]);
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+              for (int rt = 0; rt < 2; ++rt)
+                acc[ct][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[c][ct][s], bv[c][rt][s],
+                                                                   acc[ct][rt], 0, 0, 0);
+        }
+    }
+    // the block's own 32 x 32 operands: both diagonal inverses and what lies below the first
+    // (rows and columns beyond m: zero in dinv)
+    const int jb = c0 / 32;
+    double d0[2][2][4], d1[2][2][4], lo[2][2][4];
+    const bool two = c0 + 32 < m;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int c = 16 * j + 4 * s + lg;
+          const size_t at = (size_t)c * 32 + 16 * i + li;
+          d0[i][j][s] = gptr(dinv)[(size_t)jb * 1024 + at];
+          d1[i][j][s] = gptr(dinv)[(size_t)(two ? jb + 1 : jb) * 1024 + at];
+          lo[i][j][s] = two ? lcol(c0 + 16 * j + 4 * s)[lo_[2 + i]] : 0.0;
+        }
+    auto solve = [&](const double (&d)[2][2][4], const d4 (&b)[2][2], d4 (&q)[2][2]) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+          q[i][rt] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+          for (int j = 0; j <= i; ++j)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+              q[i][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(d[i][j][s], -b[j][rt][s], q[i][rt],
+                                                              0, 0, 0);
+        }
+    };
+    auto store = [&](int ct0, const d4 (&q)[2][2]) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int c = c0 + 16 * (ct0 + i) + 4 * s + lg;
+          if (c < m) {
+            if (in0) xcol(c0 + 16 * (ct0 + i) + 4 * s)[xo[0]] = q[i][0][s];
+            if (in1) xcol(c0 + 16 * (ct0 + i) + 4 * s)[xo[1]] = q[i][1][s];
+          }
+        }
+    };
+    d4 b0[2][2] = {{acc[0][0], acc[0][1]}, {acc[1][0], acc[1][1]}}, q0[2][2];
+    solve(d0, b0, q0);
+    store(0, q0);
+    if (nct > 2) {
+      d4 b1[2][2] = {{acc[2][0], acc[2][1]}, {acc[3][0], acc[3][1]}}, q1[2][2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+              b1[i][rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(lo[i][j][s], q0[j][rt][s], b1[i][rt],
+                                                               0, 0, 0);
+      solve(d1, b1, q1);
+      store(2, q1);
+    }
+  }
+}
+
 // The same solve with the workgroup's 16-row strip of X held in LDS for m <= kStripM: the
 // strip is read once and written once, and the solved column blocks that every later
 // block's contraction needs are LDS operands instead of global re-reads. Four waves: wave
@@ -1859,6 +2100,7 @@ hipError_t gemm_f64(int ta, int tb, int M, int N, int K, double alpha, const dou
   if (gram_sq && (!lower || !partial || K <= 0 || beta != 0.0)) return hipErrorInvalidValue;
   if (K <= 0) splitk = 1;
   if (splitk < 1 || !partial) splitk = 1;
+  const int max_splits = splitk;
   // 64 x 64 tiles through LDS when both sides span a tile, else one wave per 32 x 32 tile
   const bool big = M >= kGT && N >= kGT;
   const int kround = big ? kGK : 4;
@@ -1871,10 +2113,29 @@ hipError_t gemm_f64(int ta, int tb, int M, int N, int K, double alpha, const dou
   int kchunk = (K + splitk - 1) / splitk;
   kchunk = (kchunk + kround - 1) / kround * kround;
   if (kchunk <= 0) kchunk = kround;
-  const int splits = K > 0 ? (K + kchunk - 1) / kchunk : 1;
+  int splits = K > 0 ? (K + kchunk - 1) / kchunk : 1;
   // the Gram-with-squares form always goes through the reduction, which writes them
   double *part = (splits > 1 || gram_sq || sym) ? partial : nullptr;
-  if (big) {
+  // a wave per 64 x 64 tile and split where these give most of the 1024 SIMDs a wave with 1024
+  // or more of K each (below, the LDS kernel's smaller share per wave ends sooner)
+  const int wsplits = std::min(max_splits, 1024 / tiles / kXcds * kXcds);
+  if (ta == 1 && tb == 0 && big && wsplits >= kXcds && tiles * wsplits >= 512 &&
+      K / wsplits >= 1024 && partial) {
+    const int kc = ((K + wsplits - 1) / wsplits + 15) / 16 * 16;
+    splits = (K + kc - 1) / kc;
+    part = partial;
+    const dim3 grid(tiles * ((splits + kXcds - 1) / kXcds) * kXcds);
+#define RIOT_GEMM_W64(LO_, PA_)                                                                   \
+  hipLaunchKernelGGL((gemm_tn_wave64_kernel<LO_, PA_>), grid, dim3(64), 0, st, M, N, K, A, lda, B, \
+                     ldb, kc, splits, partial, run, B2, N1)
+    if (pair)
+      RIOT_GEMM_W64(false, true);
+    else if (lower)
+      RIOT_GEMM_W64(true, false);
+    else
+      RIOT_GEMM_W64(false, false);
+#undef RIOT_GEMM_W64
+  } else if (big) {
     dim3 grid(tm, tn, splits);
     int xs = 0;
     if (splits % kXcds == 0) {
@@ -1980,6 +2241,9 @@ hipError_t launch_trsm_rlt_inv(int rows, int m, double *X, int ldx, const double
     hipLaunchKernelGGL(trsm_rlt_inv_strip_kernel,
                        dim3((rows + kSR - 1) / kSR + (rows2 + kSR - 1) / kSR), dim3(256), 0, st,
                        rows, m, X, ldx, L, dinv, run, rows2, X2, ldx2, Xsrc, nullptr);
+  else if (rows + rows2 >= kWaveRows)
+    hipLaunchKernelGGL(trsm_rlt_inv_wave_kernel, dim3((rows + 31) / 32 + (rows2 + 31) / 32),
+                       dim3(64), 0, st, rows, m, X, ldx, L, dinv, run, rows2, X2, ldx2);
   else
     hipLaunchKernelGGL(trsm_rlt_inv_kernel, dim3((rows + 31) / 32 + (rows2 + 31) / 32), dim3(256),
                        0, st, rows, m, X, ldx, L, dinv, run, rows2, X2, ldx2);

@@ -19,7 +19,7 @@ using namespace riot;
 
 namespace {
 
-constexpr int kSplitK = 16;
+constexpr int kSplitK = 24;
 
 // Scratch of the linear algebra: the split-K partial products of an m x m Gram matrix,
 // later reused for the inverses of the Cholesky factor's 32 x 32 diagonal blocks.
