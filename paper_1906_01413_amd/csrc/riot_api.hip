@@ -19,17 +19,21 @@ using namespace riot;
 
 namespace {
 
-constexpr int kSplitK = 24;
+// Splits of a contraction over n that the scratch holds for an n x m problem: 16, and 24 where a
+// block of the problem is 32 MiB or more (65536 x 512: 36 tiles of the Gram product times 24
+// splits are 864 of 1024 waves; sketch 12.2 ms, with 16 splits 12.7). Smaller problems keep the
+// scratch small: riot_sketch_eig_noalloc takes those that fit 32 MiB in all.
+inline int split_k(size_t n, size_t m) { return n * m >= (size_t)1 << 22 ? 24 : 16; }
 
 // Scratch of the linear algebra: the split-K partial products of an m x m Gram matrix,
 // later reused for the inverses of the Cholesky factor's 32 x 32 diagonal blocks.
 // The Gram's partial sums of squares for the in-place Cholesky follow both uses, then 32
 // doubles of flags for its workgroups, then the partial sums of its squared distance from I.
-inline size_t gram_sq_offset(size_t m) {
-  return std::max((size_t)kSplitK * std::max(m * m, m), (m + 31) / 32 * 1024);
+inline size_t gram_sq_offset(int splitk, size_t m) {
+  return std::max((size_t)splitk * std::max(m * m, m), (m + 31) / 32 * 1024);
 }
-inline size_t partial_doubles(size_t m) {
-  return gram_sq_offset(m) + 2 * ((m * m + 255) / 256) + 32;
+inline size_t partial_doubles(int splitk, size_t m) {
+  return gram_sq_offset(splitk, m) + 2 * ((m * m + 255) / 256) + 32;
 }
 
 // Bump allocator over the caller's workspace (base == nullptr: size only).
@@ -174,6 +178,7 @@ struct riot_handle {
   bool batch = false;  // laid out for a batch (throughput, not latency)
   int S = 0, U = 0, w = 0;
   int cus = 256;  // compute units of the device the handle was created on
+  int splitk = 16;  // splits of a contraction that `partial` holds
   bool fp32 = false;
   bool linearized = false;
   double base_diag = 0.0;
@@ -229,6 +234,7 @@ struct LaSpace {
   double *Q, *G, *R, *B1, *B2, *K, *Zs, *sywork, *partial, *scal, *cvec;
   int *flags;
   int *cq;  // CholeskyQR pass control (kMaxCholQRPasses + 1 ints), after the 16 flags
+  int splitk = 16;  // splits of a contraction that `partial` holds
   // host-read pass control (see cholqr): the host-mapped word (host and device addresses)
   // and the handle's sequence counter; nullptr: every pass is launched, predicated
   int *hflag = nullptr, *hflag_dev = nullptr;
@@ -238,6 +244,7 @@ struct LaSpace {
 inline LaSpace la_of(riot_handle *h) {
   LaSpace la{h->st, h->Q, h->G, h->R, h->B1, h->B2, h->K, h->Zs, h->sywork, h->partial, h->scal,
              h->cvec, h->flags, h->flags + 16};
+  la.splitk = h->splitk;
   if (h->pass_sync && h->hflag) la.hflag = h->hflag, la.hflag_dev = h->hflag_dev, la.seq = &h->pass_seq;
   return la;
 }
@@ -293,7 +300,8 @@ size_t carve(riot_handle &h, void *base) {
   h.K = c.take<double>(m2);
   h.Zs = c.take<double>(m2);
   h.sywork = c.take<double>(eig_work_doubles(mm));
-  h.partial = c.take<double>(partial_doubles(mm));
+  h.splitk = split_k(n, mm);
+  h.partial = c.take<double>(partial_doubles(h.splitk, mm));
   h.cvec = c.take<double>(mm);
   h.scal = c.take<double>(16);
   h.cgv = c.take<double>((size_t)5 * n);
@@ -436,9 +444,9 @@ riot_status cholqr(const LaSpace &h, int rows, int m, const double *Xin, double 
     // its squared Frobenius norm and distance from I, and is factored there in place; the
     // Cholesky also writes its diagonal blocks' inverses into the Gram's split-K buffer,
     // free by then, and decides whether the next pass runs
-    double *gsq = h.partial + gram_sq_offset(m);
+    double *gsq = h.partial + gram_sq_offset(h.splitk, m);
     RIOT_HIP(gemm_f64(1, 0, m, m, rows, 1.0, src, rows, src, rows, 0.0, h.R, m, h.partial,
-                      kSplitK, st, run, true, gsq));
+                      h.splitk, st, run, true, gsq));
     CholQrCtl ctl;
     ctl.cq = cq, ctl.pass = pass, ctl.npass = kMaxCholQRPasses, ctl.count = count;
     const bool wait = host_ctl && pass + 1 >= always && pass + 1 < kMaxCholQRPasses;
@@ -471,27 +479,27 @@ riot_status sketch_eig(const LaSpace &la, int n, int m, const double *Y, const d
   riot_status rs = cholqr(la, n, m, Y, la.Q, true, 0, nullptr, 0, la.flags + 5);
   if (rs != RIOT_OK) return rs;
   // B1 and B2 in one launch (half the K splits: the partial buffer holds both products)
-  RIOT_HIP(gemm_f64(1, 0, m, m, n, 1.0, la.Q, n, Y, n, 0.0, la.B1, m, la.partial, kSplitK / 2,
+  RIOT_HIP(gemm_f64(1, 0, m, m, n, 1.0, la.Q, n, Y, n, 0.0, la.B1, m, la.partial, la.splitk / 2,
                     st, nullptr, false, nullptr, Om_eff, la.B2));
   rs = cholqr(la, m, m, la.B2, la.Zs, false, 1, la.B1, m);
   if (rs != RIOT_OK) return rs;
   if (info) {  // ||K - K^T|| / ||K|| (reported) needs K before symmetrisation
-    RIOT_HIP(gemm_f64(0, 1, m, m, m, 1.0, la.B1, m, la.Zs, m, 0.0, la.K, m, la.partial, kSplitK,
+    RIOT_HIP(gemm_f64(0, 1, m, m, m, 1.0, la.B1, m, la.Zs, m, 0.0, la.K, m, la.partial, la.splitk,
                       st));
     RIOT_HIP(launch_symmetrize(m, la.K, la.scal + 1, la.partial, st));
   } else {  // K <- (K + K^T) / 2 as the product's split-K reduction forms it
-    RIOT_HIP(gemm_f64(0, 1, m, m, m, 1.0, la.B1, m, la.Zs, m, 0.0, la.K, m, la.partial, kSplitK,
+    RIOT_HIP(gemm_f64(0, 1, m, m, m, 1.0, la.B1, m, la.Zs, m, 0.0, la.K, m, la.partial, la.splitk,
                       st, nullptr, false, nullptr, nullptr, nullptr, true));
   }
   RIOT_HIP(launch_eig(m, la.K, lambda, la.Zs, la.sywork, la.flags + 2, st));
   RIOT_HIP(gemm_f64(0, 0, n, m, m, 1.0, la.Q, n, la.Zs, m, 0.0, V, n, nullptr, 1, st));
   RIOT_HIP(launch_check_finite(m, lambda, la.flags + 3, st, (long long)n * m, V));
   if (info) {
-    RIOT_HIP(gemm_f64(1, 0, m, m, n, 1.0, la.Q, n, la.Q, n, 0.0, la.G, m, la.partial, kSplitK, st));
+    RIOT_HIP(gemm_f64(1, 0, m, m, n, 1.0, la.Q, n, la.Q, n, 0.0, la.G, m, la.partial, la.splitk, st));
     RIOT_HIP(launch_orth_err(m, la.G, la.scal + 2, st));
     // residual of the defining equation with the symmetrised K: ||K B2 - B1|| / ||B1||
     // (B1 = Q^T Y formed again: the solve above overwrote it; B2 and K are intact)
-    RIOT_HIP(gemm_f64(1, 0, m, m, n, 1.0, la.Q, n, Y, n, 0.0, la.R, m, la.partial, kSplitK, st));
+    RIOT_HIP(gemm_f64(1, 0, m, m, n, 1.0, la.Q, n, Y, n, 0.0, la.R, m, la.partial, la.splitk, st));
     RIOT_HIP(gemm_f64(0, 0, m, m, m, 1.0, la.K, m, la.B2, m, 0.0, la.G, m, nullptr, 1, st));
     RIOT_HIP(launch_axpby((long long)m * m, 1.0, la.G, -1.0, la.R, st));
     RIOT_HIP(launch_fro_ratio((long long)m * m, la.G, la.R, la.scal + 7, st));
@@ -521,7 +529,7 @@ riot_status sketch_increment(const LaSpace &la, int n, int k, const double *lamb
                              const double *V, const double *grad, riot_update mode, double *dz,
                              double *dofs_host, int32_t *mode_used) {
   hipStream_t st = la.st;
-  RIOT_HIP(gemm_f64(1, 0, k, 1, n, 1.0, V, n, grad, n, 0.0, la.cvec, k, la.partial, kSplitK, st));
+  RIOT_HIP(gemm_f64(1, 0, k, 1, n, 1.0, V, n, grad, n, 0.0, la.cvec, k, la.partial, la.splitk, st));
   const int ml = mode == RIOT_LRA ? 0 : (mode == RIOT_LRU ? 1 : 2);
   RIOT_HIP(launch_increment_combine(n, k, lambda, V, la.cvec, grad, ml, dz, la.scal + 4, st));
   if (mode_used) RIOT_HIP(launch_choose_mode(k, lambda, la.flags + 8, st));
@@ -542,7 +550,7 @@ riot_status sketch_increment(const LaSpace &la, int n, int k, const double *lamb
 riot_status proj_residual(const LaSpace &la, int n, int m, const double *Q, const double *AQ,
                           double *rho_host) {
   hipStream_t st = la.st;
-  RIOT_HIP(gemm_f64(1, 0, m, m, n, 1.0, Q, n, AQ, n, 0.0, la.K, m, la.partial, kSplitK, st));
+  RIOT_HIP(gemm_f64(1, 0, m, m, n, 1.0, Q, n, AQ, n, 0.0, la.K, m, la.partial, la.splitk, st));
   RIOT_HIP(hipMemcpyAsync(la.Q, AQ, (size_t)n * m * sizeof(double), hipMemcpyDeviceToDevice, st));
   RIOT_HIP(gemm_f64(0, 0, n, m, m, -1.0, Q, n, la.K, m, 1.0, la.Q, n, la.partial, 1, st));
   RIOT_HIP(launch_fro_ratio((long long)n * m, la.Q, AQ, la.scal + 6, st));
@@ -866,7 +874,7 @@ riot_status riot_increment_select(riot_handle *h, int32_t k, const double *lambd
   hipStream_t st = h->st;
   double *dzc = h->sel, *dxc = dzc + 2 * (size_t)n, *xc = dxc + 2 * (size_t)n;
   double *vc = xc + 2 * (size_t)n, *xu = vc + 2 * (size_t)n, *J = xu + 2 * U1;
-  RIOT_HIP(gemm_f64(1, 0, k, 1, n, 1.0, V, n, grad, n, 0.0, h->cvec, k, h->partial, kSplitK, st));
+  RIOT_HIP(gemm_f64(1, 0, k, 1, n, 1.0, V, n, grad, n, 0.0, h->cvec, k, h->partial, h->splitk, st));
   RIOT_HIP(launch_increment_combine(n, k, lambda, V, h->cvec, grad, 0, dzc, h->scal + 4, st));
   RIOT_HIP(launch_increment_combine(n, k, lambda, V, h->cvec, grad, 1, dzc + n, h->scal + 4, st));
   RIOT_HIP(launch_apply_L(n, h->w, h->taps, 2, dzc, dxc, nullptr, 0, st));
@@ -964,7 +972,7 @@ static riot_status precond_apply_impl(riot_handle *h, int nlev, const double *co
   for (int q = 0; q < nlev; ++q) {
     const int j = op == 0 ? nlev - 1 - q : q;  // P applies the last factor first
     const int k = mj[j];
-    RIOT_HIP(gemm_f64(1, 0, k, m, n, 1.0, V[j], n, X, n, 0.0, h->B1, k, h->partial, kSplitK, st));
+    RIOT_HIP(gemm_f64(1, 0, k, m, n, 1.0, V[j], n, X, n, 0.0, h->B1, k, h->partial, h->splitk, st));
     RIOT_HIP(launch_precond_scale(k, m, lam[j], power, h->B1, st));
     RIOT_HIP(gemm_f64(0, 0, n, m, k, 1.0, V[j], n, h->B1, k, 1.0, X, n, nullptr, 1, st));
   }
@@ -1025,7 +1033,7 @@ riot_status riot_project_out(riot_handle *h, int32_t r, const double *U, int32_t
   const int n = h->d.n;
   hipStream_t st = h->st;
   for (int pass = 0; pass < 2; ++pass) {  // twice: classical Gram-Schmidt to rounding level
-    RIOT_HIP(gemm_f64(1, 0, r, m, n, 1.0, U, n, X, n, 0.0, h->B2, r, h->partial, kSplitK, st));
+    RIOT_HIP(gemm_f64(1, 0, r, m, n, 1.0, U, n, X, n, 0.0, h->B2, r, h->partial, h->splitk, st));
     RIOT_HIP(gemm_f64(0, 0, n, m, r, -1.0, U, n, h->B2, r, 1.0, X, n, nullptr, 1, st));
   }
   return RIOT_OK;
@@ -1099,7 +1107,7 @@ riot_status riot_block_lanczos(riot_handle *h, int32_t l, int32_t iters, const d
     rs = hess_apply_impl(h, l, Qi, Y, 0);
     if (rs != RIOT_OK) return rs;
     // M_i = Q_i^T Y_i
-    RIOT_HIP(gemm_f64(1, 0, l, l, n, 1.0, Qi, n, Y, n, 0.0, blk(i, i), ml, h->partial, kSplitK, st));
+    RIOT_HIP(gemm_f64(1, 0, l, l, n, 1.0, Qi, n, Y, n, 0.0, blk(i, i), ml, h->partial, h->splitk, st));
     if (i == iters - 1) break;
     // R = Y_i - Q_i M_i - Q_{i-1} W_{i-1}^T, orthogonalised against every block so far
     RIOT_HIP(gemm_f64(0, 0, n, l, l, -1.0, Qi, n, blk(i, i), ml, 1.0, Y, n, nullptr, 1, st));
@@ -1108,7 +1116,7 @@ riot_status riot_block_lanczos(riot_handle *h, int32_t l, int32_t iters, const d
                         nullptr, 1, st));
     const int done = (i + 1) * l;
     for (int pass = 0; pass < 2; ++pass) {
-      RIOT_HIP(gemm_f64(1, 0, done, l, n, 1.0, Q, n, Y, n, 0.0, h->B2, done, h->partial, kSplitK,
+      RIOT_HIP(gemm_f64(1, 0, done, l, n, 1.0, Q, n, Y, n, 0.0, h->B2, done, h->partial, h->splitk,
                         st));
       RIOT_HIP(gemm_f64(0, 0, n, l, done, -1.0, Q, n, h->B2, done, 1.0, Y, n, nullptr, 1, st));
     }
@@ -1116,9 +1124,9 @@ riot_status riot_block_lanczos(riot_handle *h, int32_t l, int32_t iters, const d
     double *Qn = Qi + (size_t)l * n;
     rs = cholqr(la, n, l, Y, Qn, true, 0);
     if (rs != RIOT_OK) return rs;
-    RIOT_HIP(gemm_f64(1, 0, l, l, n, 1.0, Qn, n, Y, n, 0.0, blk(i + 1, i), ml, h->partial, kSplitK,
+    RIOT_HIP(gemm_f64(1, 0, l, l, n, 1.0, Qn, n, Y, n, 0.0, blk(i + 1, i), ml, h->partial, h->splitk,
                       st));
-    RIOT_HIP(gemm_f64(1, 0, l, l, n, 1.0, Y, n, Qn, n, 0.0, blk(i, i + 1), ml, h->partial, kSplitK,
+    RIOT_HIP(gemm_f64(1, 0, l, l, n, 1.0, Y, n, Qn, n, 0.0, blk(i, i + 1), ml, h->partial, h->splitk,
                       st));
   }
   // blocks outside the band are zero
@@ -1127,7 +1135,7 @@ riot_status riot_block_lanczos(riot_handle *h, int32_t l, int32_t iters, const d
   RIOT_HIP(launch_eig(ml, T, lambda, la.Zs, la.sywork, la.flags + 2, st));
   RIOT_HIP(gemm_f64(0, 0, n, ml, ml, 1.0, Q, n, la.Zs, ml, 0.0, U, n, nullptr, 1, st));
   // dz = -sum (1 + l_i)^{-1} u_i u_i^T g (LRA), dx = L dz
-  RIOT_HIP(gemm_f64(1, 0, ml, 1, n, 1.0, U, n, grad, n, 0.0, la.cvec, ml, la.partial, kSplitK, st));
+  RIOT_HIP(gemm_f64(1, 0, ml, 1, n, 1.0, U, n, grad, n, 0.0, la.cvec, ml, la.partial, la.splitk, st));
   RIOT_HIP(launch_increment_combine(n, ml, lambda, U, la.cvec, grad, 0, dz, la.scal + 4, st));
   RIOT_HIP(launch_apply_L(n, h->w, h->taps, 1, dz, dx, nullptr, 0, st));
   return RIOT_OK;
@@ -1188,7 +1196,7 @@ riot_status riot_psas_increment(riot_handle *h, int32_t k, const double *lambda,
   hipStream_t st = h->st;
   double *t = h->pso + no;
   // c = U^T rhs; t = -(LRA or LRU combination of rhs); dw = -R^{-1/2} t
-  RIOT_HIP(gemm_f64(1, 0, k, 1, no, 1.0, U, no, rhs, no, 0.0, h->cvec, k, h->partial, kSplitK, st));
+  RIOT_HIP(gemm_f64(1, 0, k, 1, no, 1.0, U, no, rhs, no, 0.0, h->cvec, k, h->partial, h->splitk, st));
   const int ml = mode == RIOT_LRA ? 0 : (mode == RIOT_LRU ? 1 : 2);
   RIOT_HIP(launch_increment_combine(no, k, lambda, U, h->cvec, rhs, ml, t, h->scal + 4, st));
   RIOT_HIP(launch_psas_scale(no, h->rinv, t, dw, st));
@@ -1974,7 +1982,8 @@ size_t sketch_carve(riot_sketch &s, void *base) {
   la.K = c.take<double>(m2);
   la.Zs = c.take<double>(m2);
   la.sywork = c.take<double>(eig_work_doubles((int)m));
-  la.partial = c.take<double>(partial_doubles(m));
+  la.splitk = split_k(n, m);
+  la.partial = c.take<double>(partial_doubles(la.splitk, m));
   la.cvec = c.take<double>(m);
   la.scal = c.take<double>(16);
   la.flags = c.take<int>(32);  // 16 flags, then the CholeskyQR pass control
