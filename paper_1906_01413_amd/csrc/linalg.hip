@@ -958,11 +958,12 @@ __global__ void __launch_bounds__(kCholThreads)
       const int nsq = (int)(((size_t)m * m + 255) / 256);
       for (int q = tid; q < nsq; q += nt) part += gram_sq[q];
     } else {
-      // from the lower triangle (the upper one need not be formed): diagonal + 2 x strict lower
+      // from the lower triangle: diagonal + 2 x strict lower. The upper one need not be formed,
+      // so its values are dropped, not weighted by zero (they may be Inf or NaN)
       for (size_t idx = tid; idx < (size_t)m * m; idx += nt) {
         const int i = (int)(idx % m), j = (int)(idx / m);
-        const double w = (i > j) ? 2.0 : ((i == j) ? 1.0 : 0.0);
-        part += w * G[idx] * G[idx];
+        const double g = (i >= j) ? G[idx] : 0.0;
+        part += ((i > j) ? 2.0 : 1.0) * g * g;
       }
     }
     fro = sqrt(wg_sum(part, red));
