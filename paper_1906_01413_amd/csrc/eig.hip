@@ -104,8 +104,12 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 // which holds kUnset until the value is there: the readers poll the values themselves, so there
 // is neither a flag nor a fence nor a barrier, and nothing of S leaves the registers. A
 // workgroup whose rows are done leaves; the last one has no rows and writes the reflectors and
-// the tridiagonal, off the others' path. The polls are bounded; a wave that gives up raises an
-// abort word the others see and the eigen-solver's flag.
+// the tridiagonal, off the others' path. The workgroups of a grid must all become resident for the
+// steps to go on, so the polls are bounded (some seconds of them); a wave that gives up raises an
+// abort word the others see. One workgroup, which waits for nobody, then does the reduction: the
+// tile kernel (m <= 279) or, slowly, the one on memory. (Solves on several streams behind other
+// work can each get a part of the chip.) The grids are kept to two waves per SIMD, 512 workgroups on
+// the chip, so that three of m = 1088 (137 each) fit; with one wave (288 registers) two did not.
 // Bound by the latency of the exchange and the chain of two wave sums, a square root and its
 // reciprocal: 1.5 us a step within one workgroup (m <= 64), 1.8 us (m = 65 .. 128), 2.5 us
 // (m = 272) and 2.9 us (m = 512) over a grid. Before, a grid with S in memory and two barriers
@@ -114,7 +118,6 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 // 46 us). Within one workgroup every wave repeats the vector work, which fills the SIMDs from
 // m = 65 on (3 us a step).
 constexpr unsigned long long kUnset = 0x7ff4dead5eedbeefull;  // a signalling NaN: no result is
-constexpr int kTriMaxPolls = 1 << 22;
 constexpr int kRowsLocalMaxM = 64;
 
 __global__ void fill_unset_kernel(long long count, unsigned long long *__restrict__ p) {
@@ -181,10 +184,9 @@ __device__ __forceinline__ double wave_fold(double (&v)[N], int lane) {
 }
 
 template <int NC, int RPW, int NW, bool GRID>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW, GRID ? 2 : 1)
     tridiag_rows_kernel(int m, const double *__restrict__ K, double *__restrict__ work,
-                        int *__restrict__ abort_w, int *__restrict__ flag,
-                        const EigJob *__restrict__ jobs) {
+                        int *__restrict__ abort_w, int max_polls, const EigJob *__restrict__ jobs) {
   if (jobs) m = jobs[blockIdx.y].m, K = jobs[blockIdx.y].K, work = jobs[blockIdx.y].work;
   EigLayout Lw(m);
   double *Hv = work + Lw.Hv, *dg = work + Lw.d, *eg = work + Lw.e;
@@ -245,7 +247,7 @@ __global__ void __launch_bounds__(64 * NW)
 #pragma unroll
           for (int e = 0; e < kPoll; ++e) wait |= v[e] == kUnset;
           if (!wait) break;
-          if (++polls > kTriMaxPolls ||
+          if (++polls > max_polls ||
               ((polls & 255) == 0 &&
                __hip_atomic_load(abort_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
             __hip_atomic_store(abort_w, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -375,10 +377,6 @@ __global__ void __launch_bounds__(64 * NW)
       }
     }
   }
-  if (GRID) {
-    __syncthreads();
-    if (!ok && tid == 0) flag[0] = 1;
-  }
 }
 
 // One workgroup per problem of at most maxm <= kRowsLocalMaxM.
@@ -386,7 +384,7 @@ void launch_tridiag_local(int nprob, int maxm, int m, const double *K, double *w
                           const EigJob *jobs, hipStream_t st) {
 #define RIOT_TRI_LOCAL(NC_, RPW_, NW_)                                                          \
   hipLaunchKernelGGL((tridiag_rows_kernel<NC_, RPW_, NW_, false>), dim3(1, nprob), dim3(64 * NW_), \
-                     0, st, m, K, work, nullptr, nullptr, jobs)
+                     0, st, m, K, work, nullptr, 0, jobs)
   if (maxm <= 32)
     RIOT_TRI_LOCAL(1, 8, 4);
   else
@@ -396,10 +394,79 @@ void launch_tridiag_local(int nprob, int maxm, int m, const double *K, double *w
 
 // On a grid, m up to kEigMaxM: 8 rows per workgroup and one workgroup that records.
 template <int NC>
-void launch_tridiag_grid(int m, const double *K, double *work, int *abort_w, int *flag,
+void launch_tridiag_grid(int m, const double *K, double *work, int *abort_w, int max_polls,
                          hipStream_t st) {
   hipLaunchKernelGGL((tridiag_rows_kernel<NC, 2, 4, true>), dim3((m + 7) / 8 + 1), dim3(256), 0, st,
-                     m, K, work, abort_w, flag, nullptr);
+                     m, K, work, abort_w, max_polls, nullptr);
+}
+
+// One workgroup on the matrix in memory (full storage in Aw, a copy of K), for the sizes beyond the
+// register tiles where a grid gave up: run[0] is 0 otherwise. Bound by one compute unit's share of
+// the caches' bandwidth: 9 ms at m = 280, 0.48 s at m = 1088 (the grid 0.7 and 4 ms).
+constexpr int kAloneThreads = 512;
+
+__global__ void __launch_bounds__(kAloneThreads)
+    tridiag_alone_kernel(int m, const double *__restrict__ K, double *__restrict__ work,
+                         const int *__restrict__ run) {
+  if (run[0] == 0) return;
+  constexpr int nt = kAloneThreads;
+  EigLayout Lw(m);
+  double *S = work + Lw.Aw, *Hv = work + Lw.Hv, *dg = work + Lw.d, *eg = work + Lw.e;
+  __shared__ double vs[kEigMaxM], ps[kEigMaxM], red[16];
+  const int tid = threadIdx.x;
+  for (size_t e = tid; e < (size_t)m * m; e += nt) {
+    const int i = (int)(e % m), j = (int)(e / m);
+    S[e] = K[(size_t)min(i, j) * m + max(i, j)];
+    Hv[e] = 0.0;
+  }
+  __syncthreads();
+  for (int k = 0; k + 2 < m; ++k) {
+    const int R = m - k - 1, r0 = k + 1;
+    double part = 0.0;
+    for (int i = tid; i < R; i += nt) {
+      const double x = S[(size_t)k * m + r0 + i];
+      vs[i] = x;
+      part = fma(x, x, part);
+    }
+    const double sig2 = wsum(part, red), sig = sqrt(sig2), x0 = vs[0];
+    const double alpha = x0 >= 0.0 ? -sig : sig;
+    const double inv = sig == 0.0 ? 0.0 : rsqrt(2.0 * (sig2 - alpha * x0));
+    __syncthreads();
+    for (int i = tid; i < R; i += nt) {
+      const double v = (i == 0 ? x0 - alpha : vs[i]) * inv;
+      vs[i] = v;
+      Hv[(size_t)k * m + r0 + i] = v;
+    }
+    if (tid == 0) dg[k] = S[(size_t)k * m + k], eg[k] = sig == 0.0 ? 0.0 : alpha;
+    __syncthreads();
+    // p = S v, a row per thread (columns read along the rows, which are contiguous)
+    double kp = 0.0;
+    for (int i = tid; i < R; i += nt) {
+      double acc = 0.0;
+#pragma unroll 8
+      for (int j = 0; j < R; ++j) acc = fma(S[(size_t)(r0 + j) * m + r0 + i], vs[j], acc);
+      ps[i] = acc;
+      kp = fma(vs[i], acc, kp);
+    }
+    const double Kv = wsum(kp, red);
+    for (int i = tid; i < R; i += nt) ps[i] = 2.0 * (ps[i] - Kv * vs[i]);  // 2 w
+    __syncthreads();
+    for (int i = tid; i < R; i += nt) {
+      const double v = vs[i], w = ps[i];
+#pragma unroll 8
+      for (int j = 0; j < R; ++j) {
+        double *s = S + (size_t)(r0 + j) * m + r0 + i;
+        *s = fma(-v, ps[j], fma(-w, vs[j], *s));
+      }
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    dg[m - 2] = S[(size_t)(m - 2) * m + m - 2];
+    dg[m - 1] = S[(size_t)(m - 1) * m + m - 1];
+    eg[m - 2] = S[(size_t)(m - 2) * m + m - 1];
+    eg[m - 1] = 0.0;
+  }
 }
 
 // Register-tile variant. The lower triangle of K is cut into 9 x 9 tiles (R, C), R >= C, one
@@ -417,7 +484,8 @@ void launch_tridiag_grid(int m, const double *K, double *work, int *abort_w, int
 //            the diagonal, column sums) into the slot of its partner block; each wave reduces
 //            its lanes' shares of v^T A v by a fixed shuffle tree; the diagonal lanes store v;
 //   phase 3  p[i] = the sum of its slots over the active partner blocks, in a fixed order.
-// v, p and v^T p are double-buffered by step parity.
+// v, p and v^T p are double-buffered by step parity. run (optional): the kernel does nothing where
+// run[0] is 0.
 constexpr int kTB = 9;
 constexpr int kTileMaxNb = 31;  // m <= 279
 constexpr int kTileMaxThreads = 512;
@@ -502,7 +570,8 @@ constexpr int kPslotLd = kTB * kTileMaxNb + 2;
 
 __global__ void __launch_bounds__(kTileMaxThreads)
     tridiag_tile_kernel(int m, const double *__restrict__ K, double *__restrict__ work,
-                        const EigJob *__restrict__ jobs) {
+                        const int *__restrict__ run, const EigJob *__restrict__ jobs) {
+  if (run && run[0] == 0) return;
   if (jobs) m = jobs[blockIdx.y].m, K = jobs[blockIdx.y].K, work = jobs[blockIdx.y].work;
   __shared__ double vb[2][kTB * kTileMaxNb], pb[2][kTB * kTileMaxNb];
   __shared__ double xs[kTB * kTileMaxNb];
@@ -1740,7 +1809,7 @@ void launch_backtransform(dim3 grid, int mmax, int m, const double *work, double
 size_t eig_work_doubles(int m) { return EigLayout(m).total; }
 
 hipError_t launch_eig(int m, const double *K, double *lam, double *Z, double *work, int *flag,
-                      hipStream_t st) {
+                      hipStream_t st, int max_polls) {
   if (m < 1 || m > kEigMaxM) return hipErrorInvalidValue;
   if (m <= kRowsLocalMaxM) {
     launch_tridiag_local(1, m, m, K, work, nullptr, st);
@@ -1751,17 +1820,24 @@ hipError_t launch_eig(int m, const double *K, double *lam, double *Z, double *wo
     hipLaunchKernelGGL(fill_unset_kernel, dim3(256), dim3(256), 0, st, (long long)m * (m - 1),
                        reinterpret_cast<unsigned long long *>(work));
     if (m <= 2 * 64)
-      launch_tridiag_grid<2>(m, K, work, abort_w, flag, st);
+      launch_tridiag_grid<2>(m, K, work, abort_w, max_polls, st);
     else if (m <= 3 * 64)
-      launch_tridiag_grid<3>(m, K, work, abort_w, flag, st);
+      launch_tridiag_grid<3>(m, K, work, abort_w, max_polls, st);
     else if (m <= 5 * 64)
-      launch_tridiag_grid<5>(m, K, work, abort_w, flag, st);
+      launch_tridiag_grid<5>(m, K, work, abort_w, max_polls, st);
     else if (m <= 8 * 64)
-      launch_tridiag_grid<8>(m, K, work, abort_w, flag, st);
+      launch_tridiag_grid<8>(m, K, work, abort_w, max_polls, st);
     else if (m <= 12 * 64)
-      launch_tridiag_grid<12>(m, K, work, abort_w, flag, st);
+      launch_tridiag_grid<12>(m, K, work, abort_w, max_polls, st);
     else
-      launch_tridiag_grid<17>(m, K, work, abort_w, flag, st);
+      launch_tridiag_grid<17>(m, K, work, abort_w, max_polls, st);
+    // where the grid gave up
+    if (tile_fits(m))
+      hipLaunchKernelGGL(tridiag_tile_kernel, dim3(1), dim3(tile_threads(m)), 0, st, m, K, work,
+                         abort_w, nullptr);
+    else
+      hipLaunchKernelGGL(tridiag_alone_kernel, dim3(1), dim3(kAloneThreads), 0, st, m, K, work,
+                         abort_w);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1791,7 +1867,7 @@ hipError_t launch_eig_batched(int nprob, int maxm, const EigJob *jobs, hipStream
     launch_tridiag_local(nprob, maxm, 0, nullptr, nullptr, jobs, st);
   else
     hipLaunchKernelGGL(tridiag_tile_kernel, dim3(1, nprob), dim3(tile_threads(maxm)), 0, st, 0,
-                       nullptr, nullptr, jobs);
+                       nullptr, nullptr, nullptr, jobs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(root_kernel, dim3(1, nprob), dim3(256), (size_t)4 * maxm * sizeof(double), st,

@@ -389,9 +389,11 @@ hipError_t launch_orth_err(int m, const double *G, double *out, hipStream_t st);
 // Symmetric eigendecomposition (eig.hip): tridiagonalisation, relatively robust
 // representation, multisection bisection, twisted-factorisation vectors, cluster
 // Rayleigh-Ritz, back-transformation. Eigenvalues descending. flag[0] = 1 on failure.
+// max_polls bounds the waits of the tridiagonalisation's workgroups for each other (m > 64).
+constexpr int kTriMaxPolls = 1 << 22;
 size_t eig_work_doubles(int m);
 hipError_t launch_eig(int m, const double *K, double *lam, double *Z, double *work, int *flag,
-                      hipStream_t st);
+                      hipStream_t st, int max_polls = kTriMaxPolls);
 
 // Increment helpers: c = V^T g handled by gemm_f64; these combine.
 // dz = -(V (c .* a)) [lra] or dz = -(g - V (c .* a)) [lru], a = coefficient per pair.
