@@ -44,7 +44,9 @@ struct TracerView {
 // All steps of a launch lie in one time block, so the emission term of a cell is the same at
 // every level: it is formed once per row and kept for the S - 1 rows until the last level
 // has used it. Likewise the adjoint adds the levels' lam of a cell first and multiplies by
-// dt W once.
+// dt W once. TWO: time blocks of one step each; a launch takes the steps of two blocks, with the
+// weights, controls and gradients of both. (512 x 512, 24 blocks, 64 members: product 2.74 ms;
+// one step per launch moves every field twice as often, 4.39 ms.)
 //
 // Bound: the fields' traffic, one read and one write per S steps (0.44 ms per launch at a
 // copy's 4.9 TB/s for 512 members on 512 x 512 cells), and vector issue, about 300
@@ -74,6 +76,9 @@ struct MarchArgs {
   long long bv_stride;
   double *gS;                 // adjoint: [mem][Nb*Nb] control gradient of the time block
   long long gS_stride;
+  // where the launch's two steps lie in two time blocks: the second one's
+  const double *W2, *bv2;
+  double *gS2;
   int gS_add;                 // 0: gS is written, 1: added to
   // cells sampled (forward: observations) or forced (adjoint: unique cells) in this group, in
   // the order of the march: entries [ptr[r], ptr[r + 1]) lie in rows (r - lev) mod N, which
@@ -124,12 +129,12 @@ __device__ __forceinline__ d2 own_copy(d2 v) {
 
 __device__ __forceinline__ int wrap(int i, int N) { return i < 0 ? i + N : (i >= N ? i - N : i); }
 
-template <bool ADJ, int S>
+template <bool ADJ, int S, bool TWO = false>
 __global__ void __launch_bounds__(64, S > 4 ? 2 : 3)
     tracer_march_kernel(TracerView tv, MarchArgs a, const double *__restrict__ ca0,
                         const double *__restrict__ caW, const int *__restrict__ ptr) {
   constexpr int R = S <= 4 ? 4 : kMaxS;  // rows of the rings below, unrolled iterations
-  static_assert(S >= 1 && S <= kMaxS && kHalo >= kMaxS && R % kAhead == 0, "");
+  static_assert(S >= 1 && S <= kMaxS && kHalo >= kMaxS && R % kAhead == 0 && (!TWO || S == 2), "");
   __shared__ double rows[S][kCells];  // levels' rows sampled, or their forcing, at one iteration
   const int N = tv.N, lane = threadIdx.x;
   // Workgroups are dealt round-robin to the 8 XCDs: the strips of one chunk go to one XCD,
@@ -159,22 +164,27 @@ __global__ void __launch_bounds__(64, S > 4 ? 2 : 3)
   const unsigned xo8 = 8u * x, xb8 = 8u * (x >> sh),
                  xc8 = 8u * ((x + 1) >> sh);  // byte offsets of this lane in a row
   const double *bvm = ADJ ? nullptr : a.bv + mem * a.bv_stride;
+  const double *bvm2 = !ADJ && TWO ? a.bv2 + mem * a.bv_stride : nullptr;
   double *gSm = ADJ ? a.gS + mem * a.gS_stride : nullptr;
+  double *gSm2 = ADJ && TWO ? a.gS2 + mem * a.gS_stride : nullptr;
   const int iters = ye - ys + 2 * S;
 
   d2 q[S], cold[S], ring[R];  // ring: emission terms (forward) or sums of lam (adjoint)
+  d2 ring2[2];  // TWO: the second block's term of this row and of the one before (forward)
 #pragma unroll
   for (int s = 0; s < S; ++s) q[s] = cold[s] = d2{0.0, 0.0};
 #pragma unroll
   for (int s = 0; s < R; ++s) ring[s] = d2{0.0, 0.0};
+  ring2[0] = ring2[1] = d2{0.0, 0.0};
   double r0[R], rW[R];  // a0 and aW of the last R rows
 #pragma unroll
   for (int s = 0; s < R; ++s) r0[s] = rW[s] = 0.0;
 
   // rows in flight: input field and (forward: emission weights and controls of the same row;
   // adjoint: weights of the row whose sums complete at that iteration)
-  constexpr int kAW = ADJ ? kAheadG : kAhead;
+  constexpr int kAW = ADJ || TWO ? kAheadG : kAhead;  // (TWO: four rows of both blocks would spill)
   d2 fb[kAhead], wb[kAW], eb[kAW];  // eb: controls (forward), old gS of that row (adjoint)
+  d2 wb2[kAW], eb2[kAW];            // TWO: the second block's
   int rl = wrap(ys - S, N), rw = ADJ ? wrap(wrap(ys - S - (S - 1), N), N) : rl;  // next rows to load
   auto issue_f = [&](int k) {
     fb[k] = *row_at<d2>(src + (size_t)rl * N, xo8);
@@ -185,6 +195,14 @@ __global__ void __launch_bounds__(64, S > 4 ? 2 : 3)
     const double *bp = (ADJ ? gSm : bvm) + (size_t)(rw >> sh) * tv.Nb;
     eb[k].x = *row_at<double>(bp, xb8);
     eb[k].y = *row_at<double>(bp, xc8);
+    if constexpr (TWO) {
+      wb2[k] = *row_at<d2>(a.W2 + (size_t)rw * N, xo8);
+      if constexpr (!ADJ) {
+        const double *bp2 = bvm2 + (size_t)(rw >> sh) * tv.Nb;
+        eb2[k].x = *row_at<double>(bp2, xb8);
+        eb2[k].y = *row_at<double>(bp2, xc8);
+      }
+    }
     rw = rw + 1 == N ? 0 : rw + 1;
   };
   int rc = wrap(ys - S, N);            // row taken in by this iteration
@@ -212,7 +230,7 @@ __global__ void __launch_bounds__(64, S > 4 ? 2 : 3)
     if (k < kAheadG) issue_e(k);
   }
   double na0 = ca0[rc], naW = caW[rc];
-  d2 bsum = {0.0, 0.0};
+  d2 bsum = {0.0, 0.0}, bsum2 = {0.0, 0.0};
 
   for (int i0 = 0; i0 < iters; i0 += R) {
 #pragma unroll
@@ -224,6 +242,9 @@ __global__ void __launch_bounds__(64, S > 4 ? 2 : 3)
       if (!has_in) cin = d2{0.0, 0.0};
       const d2 wrow = wb[u % kAW];
       const d2 ev = eb[u % kAW];
+      d2 wrow2 = wrow, ev2 = ev, lam2 = {0.0, 0.0};
+      if constexpr (TWO) wrow2 = wb2[u % kAW];
+      if constexpr (TWO && !ADJ) ev2 = eb2[u % kAW];
       issue_f(u % kAhead);
       if constexpr (!ADJ) issue_w(u % kAW);
       r0[u] = na0;
@@ -245,6 +266,7 @@ __global__ void __launch_bounds__(64, S > 4 ? 2 : 3)
       }
       if constexpr (!ADJ) {
         ring[u] = d2{tv.dt * wrow.x * ev.x, tv.dt * wrow.y * ev.y};
+        if constexpr (TWO) ring2[u & 1] = d2{tv.dt * wrow2.x * ev2.x, tv.dt * wrow2.y * ev2.y};
       } else if (some) {
         // forcing of the levels' rows, scattered in LDS (a cell may sit at several places of
         // the strip when the strip is wider than the period)
@@ -277,10 +299,14 @@ __global__ void __launch_bounds__(64, S > 4 ? 2 : 3)
         t.x = fma(cp, cin.y, t.x);
         t.y = fma(cp, xp, t.y);
         if constexpr (ADJ) {
-          ring[d] = s == 1 ? cin : d2{ring[d].x + cin.x, ring[d].y + cin.y};
+          if (TWO && s == 2)
+            lam2 = cin;
+          else
+            ring[d] = s == 1 ? cin : d2{ring[d].x + cin.x, ring[d].y + cin.y};
         } else {
-          t.x += ring[d].x;
-          t.y += ring[d].y;
+          const d2 em = TWO && s == 2 ? ring2[(u - 1) & 1] : ring[d];
+          t.x += em.x;
+          t.y += em.y;
         }
         q[s - 1] = t;
         cold[s - 1] = cin;
@@ -316,24 +342,27 @@ __global__ void __launch_bounds__(64, S > 4 ? 2 : 3)
         const int yg = yo + 1;  // row whose sums of lam are complete
         issue_w(u % kAW);
         if (yg >= ys && yg < ye) {
-          const d2 sl = ring[(u - (S - 1)) & (R - 1)];
-          const d2 w = {tv.dt * wrow.x * sl.x, tv.dt * wrow.y * sl.y};
           const int bm = (1 << sh) - 1;
-          bsum = (yg & bm) == 0 ? w : bsum + w;
-          if ((yg & bm) == bm) {  // last row of its control blocks
-            const d2 old = a.gS_add ? ev : d2{0.0, 0.0};
-            gmem<double> *g = row_at<double>(gSm + (size_t)(yg >> sh) * tv.Nb, xb8);
+          auto add = [&](double *gm, d2 old, d2 wr, d2 sl, d2 &bs) {
+            const d2 w = {tv.dt * wr.x * sl.x, tv.dt * wr.y * sl.y};
+            bs = (yg & bm) == 0 ? w : bs + w;
+            if ((yg & bm) != bm) return;  // not the last row of its control blocks
+            gmem<double> *g = row_at<double>(gm + (size_t)(yg >> sh) * tv.Nb, xb8);
             if (sh == 0) {
               if (own) {
-                g[0] = old.x + bsum.x;
-                g[1] = old.y + bsum.y;
+                g[0] = old.x + bs.x;
+                g[1] = old.y + bs.y;
               }
             } else {
-              double t = bsum.x + bsum.y;
+              double t = bs.x + bs.y;
               if (sh == 2) t += dpp_shift<0xB1>(t);  // the other lane of the pair
               if (own && (sh < 2 || (lane & 1) == 0)) g[0] = old.x + t;
             }
-          }
+          };
+          // TWO: level 1 is the later step (its gradient needs no old value: one step per block)
+          const d2 old = !TWO && a.gS_add ? ev : d2{0.0, 0.0};
+          add(gSm, old, wrow, TWO ? lam2 : ring[(u - (S - 1)) & (R - 1)], bsum);
+          if constexpr (TWO) add(gSm2, old, wrow2, ring[(u - 1) & (R - 1)], bsum2);
         }
       }
       rc = rn;
@@ -476,11 +505,12 @@ bool tracer_desc_ok(const riot_tracer_desc *d) {
 }
 
 // The launches of a sweep: each time block's steps in equal groups of at most kMaxS (a group
-// does not cross a time block: one emission field per launch). First steps, then nsteps.
+// does not cross a time block: one emission field per launch), time blocks of one step in pairs.
+// First steps, then nsteps.
 std::vector<int> step_groups(const riot_tracer_desc &d) {
   std::vector<int> g;
   const int spb = d.nsteps / d.ntb, ng = (spb + riot::kMaxS - 1) / riot::kMaxS;
-  for (int b = 0; b < d.ntb; ++b)
+  for (int b = 0; b < d.ntb; b += spb == 1 ? 2 : 1)
     for (int k = 0; k < ng; ++k) g.push_back(b * spb + (int)((long long)spb * k / ng));
   g.push_back(d.nsteps);
   return g;
@@ -532,7 +562,9 @@ size_t tracer_carve(riot_tracer &h, void *base) {
 // leaves kWaves waves in the launch (two per SIMD, twice over so that the last ones even
 // out: 512 members at 512 x 512 take 17.1 ms per product with 4096, 19.4 with 2048, 17.4
 // with 8192), and at least kMinRows rows (value and gradient of one member at 512 x 512:
-// 16 rows 15 % slower than 8; 4 rows gain 2 % there and lose 25 % at 64 x 64).
+// 16 rows 15 % slower than 8; 4 rows gain 2 % there and lose 25 % at 64 x 64). The two rows of halo
+// a side of a launch of two steps cost less: 4 rows where 8 leave a SIMD without a wave (64 x 64, 48
+// blocks of one step, one member: product 404 -> 324 us; 64 members of 256 x 256 would lose 10 %).
 constexpr long long kWaves = 4096;
 constexpr int kMinRows = 8;
 
@@ -542,8 +574,10 @@ void march_geometry(const riot_tracer *h, int m, riot::MarchArgs &a) {
   a.ns = (N + use - 1) / use;
   a.width = ((N + a.ns - 1) / a.ns + 3) / 4 * 4;
   const long long per = (long long)m * a.ns;  // waves per chunk row
-  const int want = (int)std::min<long long>((kWaves + per - 1) / per, N / kMinRows);
-  a.rows = ((N + want - 1) / want + 7) / 8 * 8;
+  const bool few = h->tv.spb == 1 && per * (N / kMinRows) <= 1024;
+  const int lo = few ? kMinRows / 2 : kMinRows;
+  const int want = (int)std::min<long long>((kWaves + per - 1) / per, N / lo);
+  a.rows = ((N + want - 1) / want + lo - 1) / lo * lo;
   a.nch = (N + a.rows - 1) / a.rows;
 }
 
@@ -553,6 +587,11 @@ riot_status launch_march(const riot_tracer *h, int S, const riot::MarchArgs &a) 
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(64), 0, h->st, h->tv, a, h->tv.a0, h->tv.aW, a.ptr);
   };
+  if (S == 2 && h->tv.spb == 1) {  // two time blocks
+    go(riot::tracer_march_kernel<ADJ, 2, true>);
+    TR_HIP(hipGetLastError());
+    return RIOT_OK;
+  }
   switch (S) {
     case 1: go(riot::tracer_march_kernel<ADJ, 1>); break;
     case 2: go(riot::tracer_march_kernel<ADJ, 2>); break;
@@ -585,6 +624,7 @@ riot_status tracer_forward_sweep(riot_tracer *h, int m, const double *Wfield, lo
     a.out = g + 1 < ng ? bufs[g & 1] : nullptr;
     a.W = Wfield + Wstride * tau;
     a.bv = bv + (size_t)tau * Nbb;
+    a.W2 = a.W + Wstride, a.bv2 = a.bv + Nbb;
     a.ptr = h->optr + (size_t)g * (d.N + 1);
     riot_status rs = launch_march<false>(h, h->gstep[g + 1] - t, a);
     if (rs != RIOT_OK) return rs;
@@ -613,6 +653,7 @@ riot_status tracer_adjoint_sweep(riot_tracer *h, int m, const double *f, double 
     a.out = g ? bufs[k & 1] : nullptr;
     a.W = h->Wb + NN * tau;
     a.gS = gS + (size_t)tau * Nbb;
+    a.W2 = a.W + NN, a.gS2 = a.gS + Nbb;
     a.gS_add = g + 1 < ng && h->gstep[g + 1] / h->tv.spb == tau;  // not the block's first launch
     a.ptr = h->gptr + (size_t)g * (d.N + 1);
     riot_status rs = launch_march<true>(h, h->gstep[g + 1] - t, a);

@@ -37,3 +37,11 @@ def test_marching_sweeps_match_oracle(N, spb, ntb, block, m):
     assert rel(to_np(tr.tangent(dS)), advdiff.tangent(g, E, s0, obs, dS)) < 1e-12
     f = rng.standard_normal((t.size, m))
     assert rel(to_np(tr.adjoint(f)), advdiff.adjoint(g, E, s0, obs, f)) < 1e-12
+
+
+@pytest.mark.parametrize("N,ntb,block,m", [
+    (64, 1, 4, 1), (64, 2, 1, 2), (128, 4, 2, 3), (192, 5, 4, 2), (256, 6, 4, 5),
+])
+def test_time_blocks_of_one_step(N, ntb, block, m):
+    """A launch takes the steps of two time blocks (and an odd last one alone)."""
+    test_marching_sweeps_match_oracle(N, 1, ntb, block, m)
