@@ -506,12 +506,19 @@ bool tracer_desc_ok(const riot_tracer_desc *d) {
 
 // The launches of a sweep: each time block's steps in equal groups of at most kMaxS (a group
 // does not cross a time block: one emission field per launch), time blocks of one step in pairs.
+int block_groups(const riot_tracer_desc &d) {  // launches per time block (pair)
+  return (d.nsteps / d.ntb - 1) / riot::kMaxS + 1;
+}
+size_t step_group_count(const riot_tracer_desc &d) {
+  return d.nsteps == d.ntb ? (size_t)(d.ntb / 2) + d.ntb % 2 : (size_t)d.ntb * block_groups(d);
+}
 // First steps, then nsteps.
 std::vector<int> step_groups(const riot_tracer_desc &d) {
   std::vector<int> g;
-  const int spb = d.nsteps / d.ntb, ng = (spb + riot::kMaxS - 1) / riot::kMaxS;
-  for (int b = 0; b < d.ntb; b += spb == 1 ? 2 : 1)
-    for (int k = 0; k < ng; ++k) g.push_back(b * spb + (int)((long long)spb * k / ng));
+  g.reserve(step_group_count(d) + 1);
+  const int spb = d.nsteps / d.ntb, ng = block_groups(d);
+  for (long long b = 0; b < d.ntb; b += spb == 1 ? 2 : 1)
+    for (int k = 0; k < ng; ++k) g.push_back((int)(b * spb + (long long)spb * k / ng));
   g.push_back(d.nsteps);
   return g;
 }
@@ -536,8 +543,8 @@ size_t tracer_carve(riot_tracer &h, void *base) {
   h.ent = c.take<int>(d.nobs);
   h.forig = c.take<int>(d.nobs);
   h.uent = c.take<int>(d.nobs);
-  h.optr = c.take<int>(step_groups(d).size() * (d.N + 1));
-  h.gptr = c.take<int>(step_groups(d).size() * (d.N + 1));
+  h.optr = c.take<int>((step_group_count(d) + 1) * (d.N + 1));
+  h.gptr = c.take<int>((step_group_count(d) + 1) * (d.N + 1));
   h.F0 = c.take<double>(NN * m);
   h.F1 = c.take<double>(NN * m);
   h.CA = c.take<double>(nc * m);
