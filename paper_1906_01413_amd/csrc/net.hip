@@ -463,24 +463,25 @@ size_t n256(size_t b) { return (b + 255) / 256 * 256; }
 // points as give one per compute unit (256) with the tiles.
 struct WgradPlan {
   int wc, wi, chunks, per, parts, fl;
+  int most;  // parts beside the tiles that fill the compute units
 };
 WgradPlan wgrad_plan(int batch, int n, int cin, int cout) {
   WgradPlan p;
   p.wc = cin <= 16 ? 4 : (cout <= 16 ? 1 : 2);
   p.wi = 4 / p.wc;
   const int tiles = ((cin + 16 * p.wi - 1) / (16 * p.wi)) * ((cout + 16 * p.wc - 1) / (16 * p.wc));
+  p.most = 256 / tiles;
   p.chunks = batch * (n / riot::kCP);
   p.fl = n % 256 == 0 ? 4 : (n % 128 == 0 ? 2 : 1);
-  p.per = (p.chunks / p.fl + 256 / tiles - 1) / (256 / tiles) * p.fl;
+  p.per = (p.chunks / p.fl + p.most - 1) / p.most * p.fl;
   p.parts = (p.chunks + p.per - 1) / p.per;
   return p;
 }
 
-// The most parts of any batch up to batch_max (a larger batch need not have more).
-int wgrad_max_parts(int batch_max, int n, int cin, int cout) {
-  int mx = 0;
-  for (int b = 1; b <= batch_max; ++b) mx = std::max(mx, wgrad_plan(b, n, cin, cout).parts);
-  return mx;
+// As many parts as any batch up to batch_max can have: one per fl chunks, and no more than `most`.
+long long wgrad_max_parts(int batch_max, int n, int cin, int cout) {
+  const WgradPlan p = wgrad_plan(1, n, cin, cout);
+  return std::min((long long)batch_max * (p.chunks / p.fl), (long long)p.most);
 }
 
 struct NCarve {
