@@ -88,10 +88,15 @@ __device__ __forceinline__ void frag_put(const Frag &f, long long i, float v,
   if (l > 0) frag[f.bwd[l] + frag_at(cout, W, ci, co * W + W - 1 - j)] = v;
 }
 
-__global__ void frag_kernel(long long count, Frag f, const float *__restrict__ p,
-                            float *__restrict__ frag) {
+// New parameters: the flat copy and the operand order in one launch (6 us; a copy and a
+// launch after it 7.8, the copy alone 4.7).
+__global__ void set_params_kernel(long long count, Frag f, const float *__restrict__ in,
+                                  float *__restrict__ p, float *__restrict__ frag) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) frag_put(f, i, p[i], frag);
+  if (i >= count) return;
+  const float v = in[i];
+  p[i] = v;
+  frag_put(f, i, v, frag);
 }
 
 // z[c, i] = b[c] + sum_{c', j} W[c, c', j] h[c', (i + j - r) mod n], ReLU when relu != 0, on
@@ -711,10 +716,8 @@ int64_t riot_net_param_count(const riot_net *h) { return h ? h->nparams : 0; }
 riot_status riot_net_set_params(riot_net *h, const float *params, const float *grads) {
   if (!h) return RIOT_E_ARG;
   if (params) {
-    NET_HIP(hipMemcpyAsync(h->params, params, h->nparams * sizeof(float),
-                           hipMemcpyDeviceToDevice, h->st));
-    hipLaunchKernelGGL(riot::frag_kernel, dim3(riot::nblocks(h->nparams)), dim3(256), 0, h->st,
-                       (long long)h->nparams, h->fm, h->params, h->frag);
+    hipLaunchKernelGGL(riot::set_params_kernel, dim3(riot::nblocks(h->nparams)), dim3(256), 0, h->st,
+                       (long long)h->nparams, h->fm, params, h->params, h->frag);
     NET_HIP(hipGetLastError());
   }
   if (grads)
