@@ -28,8 +28,9 @@ constexpr int kWaveLds = 400 + 64 * 17;
 // mv.K RK4 steps do the waves refresh their halos through LDS, one barrier each time.
 //
 // How far it creeps (positions invalid after s stages, from the left / right): the nonlinear
-// stage and the TL use i-2 .. i+1: 2 s / s. The trajectory refreshes every step, so the
-// stored stage s = 0..3 of a step is wrong on 2 s / s positions. The AD uses i-1 .. i+2 of
+// stage and the TL use i-2 .. i+1: 2 s / s. A trajectory whose stages are stored refreshes every
+// step, so the stored stage s = 0..3 of a step is wrong on 2 s / s positions; one whose stages are
+// not (a forecast, observed values only) every mv.K steps. The AD uses i-1 .. i+2 of
 // its own state and i-2 .. i+2 of stages 3, 2, 1, 0 of the base: the first stage leaves
 // 8 / 5 wrong, each further one 1 / 2 more. After K steps: TL 8 K / 4 K, AD 4 K + 7 / 8 K + 3.
 // The layout (strip_layout, in the API layer) leaves HL = max(8 K, 4 K + 7), HR = 8 K + 3.
@@ -617,6 +618,7 @@ __device__ __forceinline__ void trajectory_window(const ModelView &mv, int nstep
                                                   int shard = -1) {
   Strip<E> S(mv, lds, threadIdx.x);
   if (S.w >= mv.NW) return;
+  const int every = xs64 ? 1 : mv.K;  // steps between refreshes
   if (shard >= 0 && S.w != shard) xs64 = nullptr;
   if (shard > 0) xout = nullptr;
   const double h = mv.h, F = mv.F;
@@ -631,6 +633,7 @@ __device__ __forceinline__ void trajectory_window(const ModelView &mv, int nstep
       S.obs_store(o, x, nullptr, xu);
     }
   };
+  int since = 0;
   for (int t = 0; t < nsteps; ++t) {
     if (xu) sample(t);
     S.extend(x, xe);
@@ -665,7 +668,10 @@ __device__ __forceinline__ void trajectory_window(const ModelView &mv, int nstep
       acc[j] += k[j];
       x[j] = x[j] + (h / 6.0) * acc[j];
     }
-    S.refresh(xw);
+    if (++since == every) {
+      S.refresh(xw);
+      since = 0;
+    }
   }
   if (xu) sample(nsteps);
   if (xs64) store_block<E>(mv, xs64, nsteps, 0, S.w, S.lane, x);
