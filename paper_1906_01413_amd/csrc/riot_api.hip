@@ -73,8 +73,13 @@ int choose_E(int n, int requested) {
 // the first that works at all. A single problem's members are latency-bound (one stage after
 // the other on one compute unit), so they take many short strips; n <= 141 fits one wave, which
 // needs no barrier. A batch is bound by throughput: one wave per member up to n = 1037, so that
-// members run independently and little is recomputed, and four beyond. E = 0: none fits (more
-// than 4207 elements; the lane layout then).
+// members run independently and little is recomputed, and four beyond. Where all its members are
+// no more than kFewMembers (a wave per SIMD), the widest one-wave strips are latency-bound again
+// and four waves take them: 8 problems of n = 1000, m = 64 run in 1.26 ms (one wave 1.35), 16 in
+// 1.40 (1.41), 32 in 1.68 (1.62); single calls on one's handle take half as long (a product
+// 53 us, one wave 107). E = 0: none fits (more than 4207 elements; the lane layout then).
+enum class LayoutFor { single, few, many };  // single calls, a batch of few members, of many
+constexpr long long kFewMembers = 1024;
 struct StripLayout {
   int E = 0, NW = 0, own = 0, HL = 0, HR = 0, K = 0;
   int NT = 0, A = 0;  // lane layout: threads and active threads (0: strips)
@@ -87,12 +92,13 @@ StripLayout lane_layout(int n, int requested) {
   s.NT = (s.A + 63) / 64 * 64;
   return s;
 }
-StripLayout strip_layout(int n, bool batch) {
+StripLayout strip_layout(int n, LayoutFor use) {
   static constexpr int single[][2] = {{2, 1}, {3, 1}, {2, 4}, {3, 4}, {5, 1},
                                       {5, 4}, {5, 8}, {9, 8}};
+  static constexpr int few[][2] = {{3, 1}, {5, 1}, {9, 1}, {5, 4}, {9, 4}};
   static constexpr int many[][2] = {{3, 1}, {5, 1}, {9, 1}, {17, 1}, {9, 4}};
-  const int(*cand)[2] = batch ? many : single;
-  const int ncand = batch ? 5 : 8;
+  const int(*cand)[2] = use == LayoutFor::single ? single : (use == LayoutFor::few ? few : many);
+  const int ncand = use == LayoutFor::single ? 8 : 5;
   for (int kmin : {3, 1})
     for (int c = 0; c < ncand; ++c) {
       StripLayout s;
@@ -175,7 +181,7 @@ struct riot_handle {
   riot_desc d{};
   hipStream_t st = nullptr;
   StripLayout sl;
-  bool batch = false;  // laid out for a batch (throughput, not latency)
+  LayoutFor use = LayoutFor::single;
   int S = 0, U = 0, w = 0;
   int cus = 256;  // compute units of the device the handle was created on
   int splitk = 16;  // splits of a contraction that `partial` holds
@@ -327,7 +333,7 @@ bool desc_valid(const riot_desc *d) {
 bool prepare(riot_handle &h, const riot_desc *d, ObsPlan *plan) {
   h.d = *d;
   h.fp32 = d->prec == RIOT_FP32_TLAD;
-  if (!h.fp32) h.sl = strip_layout(d->n, h.batch);
+  if (!h.fp32) h.sl = strip_layout(d->n, h.use);
   if (!h.sl.E) h.sl = lane_layout(d->n, d->elems_per_lane);
   if (!h.sl.E) return false;
   h.w = d->l_halfwidth;
@@ -572,10 +578,10 @@ riot_status hess_apply_impl(riot_handle *h, int m, const double *W, double *Y, i
 }  // namespace
 
 // Workspace of one handle, laid out for single calls or for a batch.
-static size_t handle_bytes(const riot_desc *desc, bool batch) {
+static size_t handle_bytes(const riot_desc *desc, LayoutFor use) {
   if (!desc_valid(desc)) return 0;
   riot_handle h;
-  h.batch = batch;
+  h.use = use;
   if (!prepare(h, desc, nullptr)) return 0;
   return carve(h, nullptr);
 }
@@ -583,7 +589,7 @@ static size_t handle_bytes(const riot_desc *desc, bool batch) {
 extern "C" {
 
 size_t riot_workspace_bytes(const riot_desc *desc) {
-  return handle_bytes(desc, false);
+  return handle_bytes(desc, LayoutFor::single);
 }
 
 // Set up a handle in `workspace` (shared by riot_init and the batch): carve, host tables,
@@ -1413,6 +1419,12 @@ bool batch_desc_ok(const riot_desc &d) {
          d.m_max <= d.n && d.ckpt_stride == 0;
 }
 
+LayoutFor batch_layout(int32_t nprob, const riot_desc *descs) {
+  long long members = 0;
+  for (int j = 0; j < nprob; ++j) members += descs[j].m_max;
+  return members <= kFewMembers ? LayoutFor::few : LayoutFor::many;
+}
+
 // Workspace of the batch-level part: packed buffers and job tables.
 struct BatchCarve {
   size_t off = 0;
@@ -1670,11 +1682,12 @@ extern "C" {
 size_t riot_batch_workspace_bytes(int32_t nprob, const riot_desc *descs) {
   if (nprob < 1 || !descs) return 0;
   size_t tot = 0, tn = 0, tm = 0, tnm = 0, tobs = 0, tiles = 0;
+  const LayoutFor use = batch_layout(nprob, descs);
   for (int j = 0; j < nprob; ++j) {
     riot_desc d = descs[j];
     d.elems_per_lane = 8;
     if (!batch_desc_ok(d)) return 0;
-    const size_t w = handle_bytes(&d, true);
+    const size_t w = handle_bytes(&d, use);
     if (!w) return 0;
     tot += align256(w);
     tn += d.n;
@@ -1703,6 +1716,7 @@ riot_status riot_batch_init(int32_t nprob, const riot_desc *descs, void *workspa
   b->nprob = nprob;
   b->st = static_cast<hipStream_t>(hip_stream);
   b->fp32 = descs[0].prec == RIOT_FP32_TLAD;
+  const LayoutFor use = batch_layout(nprob, descs);
   char *base = static_cast<char *>(workspace);
   size_t off = 0;
   riot_status rs = RIOT_OK;
@@ -1719,8 +1733,8 @@ riot_status riot_batch_init(int32_t nprob, const riot_desc *descs, void *workspa
       break;
     }
     b->hs.push_back(h);
-    h->batch = true;
-    const size_t w = handle_bytes(&d, true);
+    h->use = use;
+    const size_t w = handle_bytes(&d, use);
     rs = init_handle(h, &d, base + off, w, b->st);
     off += align256(w);
     b->n.push_back(d.n);
