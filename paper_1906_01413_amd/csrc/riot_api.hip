@@ -21,9 +21,13 @@ namespace {
 
 // Splits of a contraction over n that the scratch holds for an n x m problem: 16, and 24 where a
 // block of the problem is 32 MiB or more (65536 x 512: 36 tiles of the Gram product times 24
-// splits are 864 of 1024 waves; sketch 12.2 ms, with 16 splits 12.7). Smaller problems keep the
-// scratch small: riot_sketch_eig_noalloc takes those that fit 32 MiB in all.
-inline int split_k(size_t n, size_t m) { return n * m >= (size_t)1 << 22 ? 24 : 16; }
+// splits are 864 of 1024 waves; sketch 12.2 ms, with 16 splits 12.7) and 24 splits have the 1024
+// rows each that the wave products need (gemm_f64; 20000 x 512: with 24 splits 7.53 ms, with 16
+// 7.20). Smaller problems keep the scratch small: riot_sketch_eig_noalloc takes those that fit
+// 32 MiB in all.
+inline int split_k(size_t n, size_t m) {
+  return n >= 24 * 1024 && n * m >= (size_t)1 << 22 ? 24 : 16;
+}
 
 // Scratch of the linear algebra: the split-K partial products of an m x m Gram matrix,
 // later reused for the inverses of the Cholesky factor's 32 x 32 diagonal blocks.

@@ -130,3 +130,15 @@ def test_noalloc_entry_point_refuses_sizes_beyond_its_scratch():
     # the largest m that fits at the benchmarked n, as the header states
     fits = [m for m in range(256, 400) if lib.riot_sketch_workspace_bytes(4096, m) <= 32 << 20]
     assert max(fits) == 316
+
+
+def test_scratch_of_wide_blocks_grows_smoothly():
+    """One more probe column adds that column's share of the scratch, not more partial products of
+    the whole block (whose splits follow the rows alone)."""
+    from paper_1906_01413_amd.riot import load_library
+    lib = load_library()
+    size = {}
+    for m in (1022, 1023, 1024):
+        d, keep = _desc(n=4096, m_max=m)
+        size[m] = lib.riot_workspace_bytes(ctypes.byref(d))
+    assert 0 < size[1024] - size[1023] < 1.1 * (size[1023] - size[1022])
