@@ -2,11 +2,11 @@
 // consecutive elements each, the periodic halo exchanged through LDS once per RK4 stage.
 //
 // The strips (l96.hip) recompute their halos instead and meet every few steps. What stays here:
-//  - Handles with FP32 tangent-linear and adjoint sweeps. Another kernel means another order of
-//    the fused multiply-adds, and a rounding of 2^-24 that falls differently at one stage moves
-//    the Gauss-Newton products by 2e-7; the results of these handles stay what they were, digit
-//    for digit.
-//  - FP64 handles of more than 4207 elements, the most that eight strips of 9 positions per lane
+//  - Handles with FP32 tangent-linear and adjoint sweeps. A rounding of 2^-24 that falls
+//    differently at one stage moves the Gauss-Newton products by 2e-7, and the order of the fused
+//    multiply-adds is the compiler's choice here: strips that write them in their own order gave
+//    such results. Strips that write out this kernel's order are still to be tried.
+//  - FP64 handles of more than 4432 elements, the most that eight strips of 9 positions per lane
 //    take. Strips of 17 need more registers than a wave of eight has: n = 6000, T = 50, m = 128
 //    a block product takes 0.52 ms here and 0.59 ms there, n = 8192 0.60 and 0.64 ms.
 

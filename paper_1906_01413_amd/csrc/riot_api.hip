@@ -74,14 +74,17 @@ int choose_E(int n, int requested) {
 }
 
 // Strips of a member (see l96.hip): the first candidate whose halo lasts three RK4 steps, else
-// the first that works at all. A single problem's members are latency-bound (one stage after
-// the other on one compute unit), so they take many short strips; n <= 141 fits one wave, which
-// needs no barrier. A batch is bound by throughput: one wave per member up to n = 1037, so that
+// the first that works at all: handles of n = 4208 to 4320, whose halos last two steps, and to
+// 4432, one step (128 columns over 40 steps: 179 and 206 us, on the lane layout 367). A single
+// problem's members are latency-bound (one stage after the other on one compute unit), so they
+// take many short strips; up to n = 211, and for some n to 217, one wave, which needs no barrier.
+// The choice holds for wide blocks too, where waves queue (m = 1088 columns over 20 steps, lanes
+// and strips: n = 309 122 and 88 us, 565 221 and 128, 2048 316 and 272, 4096 495 and 412). A batch is bound by throughput: one wave per member up to n = 1037, so that
 // members run independently and little is recomputed, and four beyond. Where all its members are
 // no more than kFewMembers (a wave per SIMD), the widest one-wave strips are latency-bound again
 // and four waves take them: 8 problems of n = 1000, m = 64 run in 1.26 ms (one wave 1.35), 16 in
 // 1.40 (1.41), 32 in 1.68 (1.62); single calls on one's handle take half as long (a product
-// 53 us, one wave 107). E = 0: none fits (more than 4207 elements; the lane layout then).
+// 53 us, one wave 107). E = 0: none fits (more than 4432 elements; the lane layout then).
 enum class LayoutFor { single, few, many };  // single calls, a batch of few members, of many
 constexpr long long kFewMembers = 1024;
 struct StripLayout {

@@ -110,8 +110,8 @@ struct PhiloxJob {
 // that a wave reads contiguous segments.
 //
 // A handle whose TL/AD integrations run in FP32, and any of more elements than the strips take
-// (4207), has the lane layout (l96_lanes.hip): one workgroup of NT threads per member, active thread l (l < A = n / E) owning the elements
-// l*E .. l*E+E-1. Its stage blocks are E + 4 rows of NT values: row j < E holds x[l*E + j] in
+// (4432), has the lane layout (l96_lanes.hip): one workgroup of NT threads per member, active
+// thread l (l < A = n / E) owning the elements l*E .. l*E+E-1. Its stage blocks are E + 4 rows of NT values: row j < E holds x[l*E + j] in
 // column l, rows E..E+3 the four halo values x[a-2], x[a-1], x[a+E], x[a+E+1] (a = l*E).
 // ---------------------------------------------------------------------------
 

@@ -46,3 +46,10 @@ def test_strips_match_oracle(n, T, m):
     assert rel(to_np(g), lin.g) < 1e-11
     W = np.random.default_rng(n).standard_normal((n, m))
     assert rel(to_np(r.hess_apply(W)), fourdvar.hvp(p, lin, W)) < 1e-11
+
+
+@pytest.mark.parametrize("n,T,m", [(4208, 9, 3), (4320, 7, 2), (4336, 5, 3), (4432, 4, 257), (4448, 4, 2)])
+def test_last_strips_match_oracle(n, T, m):
+    """The largest strips, whose halos last two steps (n = 4208 .. 4320) and one (.. 4432), and the
+    first size of the lane layout (4448)."""
+    test_strips_match_oracle(n, T, m)

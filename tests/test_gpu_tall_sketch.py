@@ -25,3 +25,10 @@ def test_tall_sketch_matches_oracle(n, m):
     assert np.max(np.abs(lam - ro.lam)) <= 1e-10 * ro.lam[0]
     X = rng.standard_normal((n, 3))
     assert rel((V * lam) @ (V.T @ X), (ro.V * ro.lam) @ (ro.V.T @ X)) < 1e-10
+
+
+@pytest.mark.parametrize("n,m", [(16385, 470), (24601, 401), (33001, 449)])
+def test_wide_tall_sketch_matches_oracle(n, m):
+    """Wide enough (22 tiles of the lower half and more, 16 or 24 splits of 1024 rows) that the
+    Gram matrices themselves go to the wave kernel, at ragged rows, columns and splits."""
+    test_tall_sketch_matches_oracle(n, m)
