@@ -11,6 +11,7 @@
 //    a block product takes 0.52 ms here and 0.59 ms there, n = 8192 0.60 and 0.64 ms.
 
 #include <cstdlib>
+#include <type_traits>
 
 #include "l96_common.h"
 #include "riot_internal.h"
@@ -1179,6 +1180,19 @@ static bool tlad_ring_enabled() {
       return hipErrorInvalidValue; \
   }
 
+// The same for kernels on Real: an FP64 handle has this layout from 4448 elements on, where only 16
+// per lane fit a workgroup.
+template <typename Real, typename F>
+static hipError_t dispatch_real(int E, F launch) {
+  if constexpr (sizeof(Real) == sizeof(double)) {
+    if (E != 16) return hipErrorInvalidValue;
+    launch(std::integral_constant<int, 16>{});
+  } else {
+    RIOT_DISPATCH_E(E, launch(std::integral_constant<int, EE>{}));
+  }
+  return hipGetLastError();
+}
+
 hipError_t lanes_trajectory(const ModelView &mv, int nsteps, const double *x0, double *xout,
                             double *xs64, float *xs32, hipStream_t st) {
   const size_t lds = (size_t)kLdsSlots * 2 * mv.NT * sizeof(double);
@@ -1217,25 +1231,27 @@ static hipError_t tlad(const ModelView &mv, int m, int mode, const double *dx0, 
                        Real *f, const Real *fsrc, hipStream_t st) {
   const bool flags = (mode & ~7) != 0;
   const bool full = mv.A == mv.NT;
-  if (mode == 0 && full && mv.E == 16 && mv.NT == kRingNT && mv.T >= 1 && tlad_ring_enabled()) {
-    const dim3 grid((m + kRingMembers - 1) / kRingMembers), block(kRingMembers * kRingNT);
-    hipLaunchKernelGGL((tlad_ring_kernel<Real, 16>), grid, block, 0, st, mv, m, dx0, lam0, f,
-                       mv.stepk, mv.ustart, mv.umask, reinterpret_cast<const Real *>(mv.wgt));
-    return hipGetLastError();
+  if constexpr (sizeof(Real) == sizeof(float)) {  // (NT = 256: n = 4096)
+    if (mode == 0 && full && mv.E == 16 && mv.NT == kRingNT && mv.T >= 1 && tlad_ring_enabled()) {
+      const dim3 grid((m + kRingMembers - 1) / kRingMembers), block(kRingMembers * kRingNT);
+      hipLaunchKernelGGL((tlad_ring_kernel<Real, 16>), grid, block, 0, st, mv, m, dx0, lam0, f,
+                         mv.stepk, mv.ustart, mv.umask, reinterpret_cast<const Real *>(mv.wgt));
+      return hipGetLastError();
+    }
   }
   const size_t lds = (size_t)kLdsSlots * 2 * mv.NT * sizeof(Real);
-#define RIOT_TLAD(F_, U_)                                                                        \
-  RIOT_DISPATCH_E(mv.E, hipLaunchKernelGGL((tlad_kernel<Real, EE, F_, U_>), dim3(m),             \
-                                           dim3(mv.NT), lds, st, mv, mode, dx0, lam0, f, fsrc))
-  if (flags) {
-    RIOT_TLAD(true, false);
-  } else if (full) {
-    RIOT_TLAD(false, true);
-  } else {
-    RIOT_TLAD(false, false);
-  }
-#undef RIOT_TLAD
-  return hipGetLastError();
+  return dispatch_real<Real>(mv.E, [&](auto e) {
+    constexpr int E = decltype(e)::value;
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(m), dim3(mv.NT), lds, st, mv, mode, dx0, lam0, f, fsrc);
+    };
+    if (flags)
+      go(tlad_kernel<Real, E, true, false>);
+    else if (full)
+      go(tlad_kernel<Real, E, false, true>);
+    else
+      go(tlad_kernel<Real, E, false, false>);
+  });
 }
 
 hipError_t lanes_tlad(const ModelView &mv, int m, int mode, const double *dx0, double *lam0,
@@ -1264,10 +1280,11 @@ static hipError_t cg(const ModelView &mv, int w, const double *taps, const doubl
   const size_t ext_bytes = (size_t)(mv.n + 2 * w) * sizeof(double);
   const int use_ext = (ext_off + ext_bytes) <= 60 * 1024 ? 1 : 0;
   const size_t lds = use_ext ? ext_off + ext_bytes : xb;
-  RIOT_DISPATCH_E(mv.E, hipLaunchKernelGGL((cg_kernel<Real, EE>), dim3(1), dim3(mv.NT), lds, st,
-                                           mv, w, taps, g, iters, rtol, x, iterates, vec_scratch,
-                                           f, used, (int)ext_off, use_ext));
-  return hipGetLastError();
+  return dispatch_real<Real>(mv.E, [&](auto e) {
+    hipLaunchKernelGGL((cg_kernel<Real, decltype(e)::value>), dim3(1), dim3(mv.NT), lds, st, mv, w,
+                       taps, g, iters, rtol, x, iterates, vec_scratch, f, used, (int)ext_off,
+                       use_ext);
+  });
 }
 
 hipError_t lanes_cg(const ModelView &mv, int w, const double *taps, const double *g, int iters,

@@ -1650,20 +1650,15 @@ __global__ void __launch_bounds__(256)
 // blocks go from registers into the following block's product and every lane reads back only
 // what it wrote itself. -X is the accumulators' start; operands come two chunks of 16 columns
 // ahead. n = 65536, m = 512: 0.41 ms, four waves per 32 rows with the partial sums in LDS 1.1 ms;
-// it needs a wave per SIMD (rows >= kWaveRows), below which those end sooner.
+// half a wave per SIMD is enough (rows >= kWaveRows); with fewer rows those end sooner.
 constexpr int kWaveRows = 16384;
 
 __global__ void __launch_bounds__(64, 2)
     trsm_rlt_inv_wave_kernel(int rows, int m, double *X, int ldx, const double *__restrict__ L,
-                             const double *__restrict__ dinv, const int *__restrict__ run,
-                             int rows2, double *X2, int ldx2) {
+                             const double *__restrict__ dinv, const int *__restrict__ run) {
   if (run && run[0] == 0) return;
   const int lane = threadIdx.x, li = lane & 15, lg = lane >> 4;
-  int r0 = blockIdx.x * 32;
-  const int nblk1 = (rows + 31) / 32;
-  if ((int)blockIdx.x >= nblk1) {  // a block of the second matrix
-    r0 = ((int)blockIdx.x - nblk1) * 32, rows = rows2, X = X2, ldx = ldx2;
-  }
+  const int r0 = blockIdx.x * 32;
   if (r0 >= rows) return;
   // lane offsets from a uniform column: this lane's rows (clamped; a clamped row's results are
   // not stored)
@@ -2351,9 +2346,9 @@ hipError_t launch_trsm_rlt_inv(int rows, int m, double *X, int ldx, const double
     hipLaunchKernelGGL(trsm_rlt_inv_strip_kernel,
                        dim3((rows + kSR - 1) / kSR + (rows2 + kSR - 1) / kSR), dim3(256), 0, st,
                        rows, m, X, ldx, L, dinv, run, rows2, X2, ldx2, Xsrc, nullptr);
-  else if (rows + rows2 >= kWaveRows)
-    hipLaunchKernelGGL(trsm_rlt_inv_wave_kernel, dim3((rows + 31) / 32 + (rows2 + 31) / 32),
-                       dim3(64), 0, st, rows, m, X, ldx, L, dinv, run, rows2, X2, ldx2);
+  else if (rows >= kWaveRows && rows2 == 0)
+    hipLaunchKernelGGL(trsm_rlt_inv_wave_kernel, dim3((rows + 31) / 32), dim3(64), 0, st, rows, m, X,
+                       ldx, L, dinv, run);
   else
     hipLaunchKernelGGL(trsm_rlt_inv_kernel, dim3((rows + 31) / 32 + (rows2 + 31) / 32), dim3(256),
                        0, st, rows, m, X, ldx, L, dinv, run, rows2, X2, ldx2);
