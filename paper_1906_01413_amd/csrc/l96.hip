@@ -675,7 +675,10 @@ __device__ __forceinline__ void trajectory_window(const ModelView &mv, int nstep
   }
   if (xu) sample(nsteps);
   if (xs64) store_block<E>(mv, xs64, nsteps, 0, S.w, S.lane, x);
-  if (xout) S.store_vec(xout, x);
+  if (xout) {
+    if (mv.NW > 1) __syncthreads();  // (xout may be x0: every wave has taken its window from it)
+    S.store_vec(xout, x);
+  }
 }
 
 template <int E, int TH>

@@ -53,3 +53,21 @@ def test_last_strips_match_oracle(n, T, m):
     """The largest strips, whose halos last two steps (n = 4208 .. 4320) and one (.. 4432), and the
     first size of the lane layout (4448)."""
     test_strips_match_oracle(n, T, m)
+
+
+@pytest.mark.parametrize("n,T", [(40, 2), (212, 1), (309, 2), (1001, 3), (1080, 5), (2160, 1), (4096, 2), (4208, 1)])
+def test_forecast_in_place(n, T):
+    """x0 and xout the same buffer, fewer steps than between two halo refreshes."""
+    import ctypes
+    import torch
+    from paper_1906_01413_amd.riot import load_library
+    p = _problem(n, 4, n)
+    r = riot_for(p, m_max=1)
+    x = torch.as_tensor(p.xb, device="cuda")
+    ref = to_np(r.forecast(x, T))
+    assert rel(ref, l96.forecast(p.xb, T, p.h, p.F)) < 1e-13
+    for _ in range(20):
+        y = x.clone()
+        ptr = ctypes.c_void_p(y.data_ptr())
+        assert load_library().riot_forecast(r.h, ptr, T, ptr) == 0
+        assert np.array_equal(to_np(y), ref)
