@@ -52,7 +52,7 @@ struct TracerView {
 // copy's 4.9 TB/s for 512 members on 512 x 512 cells), and vector issue, about 300
 // instructions per row of 8 levels at two waves per SIMD. Measured there, 96 steps: 0.60 ms
 // (forward) and 0.70 ms (adjoint) per 8 steps, the Hessian product of 512 probes 62.4 ms (two
-// steps per launch through LDS tiles, 3.1 TB/s) -> 17.5 ms; S = 6: 19.5 ms, S = 4: 27.2 ms.
+// steps per launch through LDS tiles, 3.1 TB/s) -> 16.8 ms; S = 6: 18.9 ms, S = 4: 26.6 ms.
 // Held to three waves per SIMD the registers spill (71 ms). One member, where a launch lasts
 // as long as one march: value and gradient 810 -> 520 us.
 // ---------------------------------------------------------------------------
@@ -567,7 +567,7 @@ size_t tracer_carve(riot_tracer &h, void *base) {
 // Strips and chunks of a sweep over m members. Strips: as few as hold the width with the
 // halo. Chunks: a wave's march costs 2 S rows on top of its own, so a chunk is as tall as
 // leaves kWaves waves in the launch (two per SIMD, twice over so that the last ones even
-// out: 512 members at 512 x 512 take 17.1 ms per product with 4096, 19.4 with 2048, 17.4
+// out: 512 members at 512 x 512 take 16.8 ms per product with 4096, 19.2 with 2048, 16.9
 // with 8192), and at least kMinRows rows (value and gradient of one member at 512 x 512:
 // 16 rows 15 % slower than 8; 4 rows gain 2 % there and lose 25 % at 64 x 64). The two rows of halo
 // a side of a launch of two steps cost less: 4 rows where 8 leave a SIMD without a wave (64 x 64, 48
