@@ -77,7 +77,10 @@ int choose_E(int n, int requested) {
 // the first that works at all: handles of n = 4208 to 4320, whose halos last two steps, and to
 // 4432, one step (128 columns over 40 steps: 179 and 206 us, on the lane layout 367). A single
 // problem's members are latency-bound (one stage after the other on one compute unit), so they
-// take many short strips; up to n = 211, and for some n to 217, one wave, which needs no barrier.
+// take many short strips; up to n = 141 one wave, which needs no barrier. Four waves need strips
+// longer than two halos and a lane (n >= 212, and not every n to 217); two of three positions per
+// lane in between: n = 211, 30 steps, 64 columns, 50 us with a fifth of the steps observed and 70
+// with every variable of every step, one wave of five positions 59 and 95, the lanes 60 and 75.
 // The choice holds for wide blocks too, where waves queue (m = 1088 columns over 20 steps, lanes
 // and strips: n = 309 122 and 88 us, 565 221 and 128, 2048 316 and 272, 4096 495 and 412). A batch is bound by throughput: one wave per member up to n = 1037, so that
 // members run independently and little is recomputed, and four beyond. Where all its members are
@@ -100,7 +103,7 @@ StripLayout lane_layout(int n, int requested) {
   return s;
 }
 StripLayout strip_layout(int n, LayoutFor use) {
-  static constexpr int single[][2] = {{2, 1}, {3, 1}, {2, 4}, {3, 4}, {5, 1},
+  static constexpr int single[][2] = {{2, 1}, {3, 1}, {2, 4}, {3, 4}, {3, 2},
                                       {5, 4}, {5, 8}, {9, 8}};
   static constexpr int few[][2] = {{3, 1}, {5, 1}, {9, 1}, {5, 4}, {9, 4}};
   static constexpr int many[][2] = {{3, 1}, {5, 1}, {9, 1}, {17, 1}, {9, 4}};
