@@ -77,15 +77,18 @@ int choose_E(int n, int requested) {
 // the first that works at all: handles of n = 4208 to 4320, whose halos last two steps, and to
 // 4432, one step (128 columns over 40 steps: 179 and 206 us, on the lane layout 367). A single
 // problem's members are latency-bound (one stage after the other on one compute unit), so they
-// take many short strips; up to n = 141 one wave, which needs no barrier. Four waves need strips
-// longer than two halos and a lane (n >= 212, and not every n to 217); two of three positions per
-// lane in between: n = 211, 30 steps, 64 columns, 50 us with a fifth of the steps observed and 70
-// with every variable of every step, one wave of five positions 59 and 95, the lanes 60 and 75.
+// take many short strips; up to n = 128 one wave, which needs no barrier (a longer strip's third 64
+// observations of a step are not loaded ahead; n = 141, every variable of every step observed,
+// 30 steps, 64 columns: 75 us, two waves 64). Four waves need strips longer than two halos and a
+// lane (n >= 212, and not every n to 217); two of three positions per lane in between: n = 211, 50 us
+// with a fifth of the steps observed and 70 with all, one wave of five positions 59 and 95, the
+// lanes 60 and 75.
 // The choice holds for wide blocks too, where waves queue (m = 1088 columns over 20 steps, lanes
-// and strips: n = 309 122 and 88 us, 565 221 and 128, 2048 316 and 272, 4096 495 and 412). A batch is bound by throughput: one wave per member up to n = 1037, so that
-// members run independently and little is recomputed, and four beyond. Where all its members are
-// no more than kFewMembers (a wave per SIMD), the widest one-wave strips are latency-bound again
-// and four waves take them: 8 problems of n = 1000, m = 64 run in 1.26 ms (one wave 1.35), 16 in
+// and strips: n = 309 122 and 88 us, 565 221 and 128, 2048 316 and 272, 4096 495 and 412).
+// A batch is bound by throughput: one wave per member up to n = 1037, so that members run
+// independently and little is recomputed, and four beyond. Where all its members are no more than
+// kFewMembers (a wave per SIMD), the widest one-wave strips are latency-bound again and four waves
+// take them: 8 problems of n = 1000, m = 64 run in 1.26 ms (one wave 1.35), 16 in
 // 1.40 (1.41), 32 in 1.68 (1.62); single calls on one's handle take half as long (a product
 // 53 us, one wave 107). E = 0: none fits (more than 4432 elements; the lane layout then).
 enum class LayoutFor { single, few, many };  // single calls, a batch of few members, of many
@@ -103,16 +106,17 @@ StripLayout lane_layout(int n, int requested) {
   return s;
 }
 StripLayout strip_layout(int n, LayoutFor use) {
-  static constexpr int single[][2] = {{2, 1}, {3, 1}, {2, 4}, {3, 4}, {3, 2},
+  static constexpr int single[][2] = {{2, 1}, {3, 1}, {2, 2}, {2, 4}, {3, 4}, {3, 2},
                                       {5, 4}, {5, 8}, {9, 8}};
   static constexpr int few[][2] = {{3, 1}, {5, 1}, {9, 1}, {5, 4}, {9, 4}};
   static constexpr int many[][2] = {{3, 1}, {5, 1}, {9, 1}, {17, 1}, {9, 4}};
   const int(*cand)[2] = use == LayoutFor::single ? single : (use == LayoutFor::few ? few : many);
-  const int ncand = use == LayoutFor::single ? 8 : 5;
+  const int ncand = use == LayoutFor::single ? 9 : 5;
   for (int kmin : {3, 1})
     for (int c = 0; c < ncand; ++c) {
       StripLayout s;
       s.E = cand[c][0], s.NW = cand[c][1];
+      if (use == LayoutFor::single && s.NW == 1 && n > 128) continue;
       s.own = (n + s.NW - 1) / s.NW;
       const int last = n - (s.NW - 1) * s.own;
       for (s.K = 8; s.K >= kmin; --s.K) {

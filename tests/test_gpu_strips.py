@@ -73,7 +73,9 @@ def test_forecast_in_place(n, T):
         assert np.array_equal(to_np(y), ref)
 
 
-@pytest.mark.parametrize("n,T,m", [(142, 9, 3), (143, 17, 1), (211, 6, 2), (213, 12, 2), (217, 7, 2)])
+@pytest.mark.parametrize("n,T,m", [
+    (129, 9, 2), (130, 4, 1), (141, 17, 3), (142, 9, 3), (143, 17, 1), (211, 6, 2), (213, 12, 2), (217, 7, 2),
+])
 def test_two_strips_match_oracle(n, T, m):
     """Two waves: what is too long for one and too short for four."""
     test_strips_match_oracle(n, T, m)
